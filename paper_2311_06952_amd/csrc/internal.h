@@ -223,14 +223,11 @@ TileHdr tile_layout(uint32_t n_sub, uint32_t F, uint32_t K, uint32_t n_problems)
 mh_status launch_rank_encode(Ctx *ctx, const float *X, uint32_t n, uint32_t F,
                              uint32_t ld, uint32_t *ranks, uint32_t *n_unique,
                              uint32_t *nan_out = nullptr, bool retry = true);
-// Sorts (key, value) pairs by the low `key_bits` of key (stable LSD radix
-// sort, 8 bits per pass).  Buffers are ping-ponged; the sorted result ends in
-// (*keys, *vals) which may point at the alternate buffers on return.
-mh_status radix_sort_pairs(Ctx *ctx, uint64_t **keys, uint32_t **vals, uint64_t *keys_alt,
-                           uint32_t *vals_alt, uint32_t count, uint32_t key_bits);
-
-// Exclusive or inclusive scan of n u32 values (in may equal out).
-mh_status scan_u32(Ctx *ctx, const uint32_t *in, uint32_t *out, uint32_t n, bool inclusive);
+// One stable 8-bit pass of the segmented radix sort: F segments of n pairs
+// (value << 32 | sample) from src to dst, by the pair's bits [shift, shift +
+// 8) or, with sub, by bits [shift, shift + 8) of sub[sample].  F n < 2^32.
+mh_status seg_radix_pass(Ctx *ctx, const uint64_t *src, uint64_t *dst, uint32_t n, uint32_t F,
+                         uint32_t shift, const uint32_t *sub);
 
 // tiles.hip
 // Builds the tiled layout at `base` for samples idx[0..n_sub) (all if
@@ -426,15 +423,31 @@ mh_status launch_deoct_persist_multi(Ctx *ctx, const void *tiles, uint32_t F, ui
                                      const uint32_t *n_unique, double *pop, double *cost,
                                      uint32_t *best, uint32_t *err, bool *used);
 
-// mh.hip
+// split.hip
 // Exact best depth-1 split (Algorithm 2, horizon-1 branch) of every subset
 // {i : sub_of[i] == s}, s < nsub (samples with sub_of >= nsub are ignored;
 // sub_of == nullptr puts every sample in subset 0).  tot: device [nsub][K]
 // class totals of the subsets.  Writes feat/tau/correct (device, [nsub];
-// correct may be null).  gini: CART's Gini split instead (correct gets 0).
+// correct may be null).
 mh_status launch_split1(Ctx *ctx, const mh_dataset *ds, const uint32_t *sub_of, uint32_t nsub,
-                        const uint32_t *tot, uint8_t *feat, uint32_t *tau, uint32_t *correct,
-                        bool gini = false);
+                        const uint32_t *tot, uint8_t *feat, uint32_t *tau, uint32_t *correct);
+// The exact split of an explicit subset (host outputs; synchronises).
+mh_status split1_subset(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub,
+                        uint8_t *feat, uint32_t *tau, uint32_t *correct);
+// CART (Gini) of depth D on each subset {i : sub_of[i] == s}, s < nsub:
+// feat / tau device [nsub][2^D - 1].  cart_subset: one explicit subset, host
+// outputs, synchronises.
+mh_status cart_batched(Ctx *ctx, const mh_dataset *ds, const uint32_t *sub_of, uint32_t nsub,
+                       uint32_t D, uint8_t *feat, uint32_t *tau);
+mh_status cart_subset(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub,
+                      uint32_t D, uint8_t *feat, uint32_t *tau);
+
+// mh.hip
+// p[0..n) = v.
+mh_status launch_fill(Ctx *ctx, uint32_t *p, uint32_t n, uint32_t v);
+// Adds the class counts of nodes t0 .. t0 + width - 1 to hist [width][K].
+mh_status launch_level_hist(Ctx *ctx, const uint32_t *node_of, const uint8_t *labels, uint32_t n,
+                            uint32_t K, uint32_t t0, uint32_t width, uint32_t *hist);
 // DEOCT for n_problems subproblems at once (problem ids prob_ids, device),
 // samples assigned by sub_of (device [n], >= n_problems = not in any).
 // Writes the decoded best tree of each problem to feat_out/tau_out (device,
@@ -446,20 +459,9 @@ mh_status deoct_batched(Ctx *ctx, const mh_dataset *ds, const uint32_t *sub_of,
                         uint32_t n_problems, const uint64_t *prob_ids, uint32_t D,
                         const mh_de_params *prm, const uint32_t *class_counts,
                         const double *warm, uint32_t W, uint8_t *feat_out, uint32_t *tau_out);
-// CART (Gini) of depth D on each subset {i : sub_of[i] == s}, s < nsub:
-// feat / tau device [nsub][2^D - 1].  cart_subset: one explicit subset, host
-// outputs, synchronises.
-mh_status cart_batched(Ctx *ctx, const mh_dataset *ds, const uint32_t *sub_of, uint32_t nsub,
-                       uint32_t D, uint8_t *feat, uint32_t *tau);
-mh_status cart_subset(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub,
-                      uint32_t D, uint8_t *feat, uint32_t *tau);
-
-// Sequential-form helpers: the samples at node t (device idx, atomics
-// order), the exact split of an explicit subset (host outputs), and the
-// moving-horizon driver itself.
+// Sequential-form helper: the samples at node t (device idx, atomics order);
+// and the moving-horizon driver itself.
 mh_status launch_compact(Ctx *ctx, const uint32_t *node_of, uint32_t n, uint32_t t, uint32_t *idx);
-mh_status split1_subset(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub,
-                        uint8_t *feat, uint32_t *tau, uint32_t *correct);
 typedef mh_status (*SolveNodeFn)(Ctx *, const mh_dataset *, const uint32_t *node_of, uint32_t t,
                                  uint32_t De, const mh_de_params *, const double *warm,
                                  uint32_t W, uint8_t *feat, uint32_t *tau);

@@ -35,10 +35,9 @@ namespace {
 constexpr uint32_t RS_THREADS = 256;
 constexpr uint32_t RS_ITEMS = 16;
 constexpr uint32_t RS_CHUNK = RS_THREADS * RS_ITEMS;  // keys per block
-constexpr uint32_t RS_BINS = 256;
 
 // ---------------------------------------------------------------------------
-// u32 scan (exclusive or inclusive) in three kernels
+// exclusive u32 scan in three kernels
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(RS_THREADS) void k_scan_sums(const uint32_t *__restrict__ in, uint32_t n,
                                                           uint32_t *__restrict__ sums) {
@@ -83,10 +82,8 @@ __global__ __launch_bounds__(1024) void k_scan_top(uint32_t *__restrict__ sums, 
 }
 
 // Blocked local scan: thread t owns items [t*ITEMS, (t+1)*ITEMS) of the chunk.
-__global__ __launch_bounds__(RS_THREADS) void k_scan_apply(const uint32_t *__restrict__ in,
-                                                           uint32_t *__restrict__ out, uint32_t n,
-                                                           const uint32_t *__restrict__ sums,
-                                                           int inclusive) {
+__global__ __launch_bounds__(RS_THREADS) void k_scan_apply(uint32_t *__restrict__ io, uint32_t n,
+                                                           const uint32_t *__restrict__ sums) {
   __shared__ uint32_t part[RS_THREADS];
   const uint32_t b0 = blockIdx.x * RS_CHUNK + threadIdx.x * RS_ITEMS;
   uint32_t v[RS_ITEMS];
@@ -94,7 +91,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_scan_apply(const uint32_t *__res
 #pragma unroll
   for (uint32_t k = 0; k < RS_ITEMS; ++k) {
     uint32_t j = b0 + k;
-    v[k] = j < n ? in[j] : 0u;
+    v[k] = j < n ? io[j] : 0u;
     tot += v[k];
   }
   part[threadIdx.x] = tot;
@@ -109,119 +106,8 @@ __global__ __launch_bounds__(RS_THREADS) void k_scan_apply(const uint32_t *__res
 #pragma unroll
   for (uint32_t k = 0; k < RS_ITEMS; ++k) {
     uint32_t j = b0 + k;
-    if (inclusive) run += v[k];
-    if (j < n) out[j] = run;
-    if (!inclusive) run += v[k];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// radix sort passes
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint64_t *__restrict__ keys, uint32_t n,
-                                                        uint32_t shift, uint32_t nb,
-                                                        uint32_t *__restrict__ hist) {
-  __shared__ uint32_t h[RS_BINS];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t b0 = blockIdx.x * RS_CHUNK;
-  for (uint32_t k = 0; k < RS_ITEMS; ++k) {
-    uint32_t j = b0 + k * RS_THREADS + threadIdx.x;
-    if (j < n) atomicAdd(&h[(uint32_t)(keys[j] >> shift) & 0xFFu], 1u);
-  }
-  __syncthreads();
-  hist[threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
-}
-
-// Stable scatter.  Keys of the block are taken in order, 256 at a time (a
-// round); inside a round wave w holds keys [64w, 64w + 64).  A key's rank
-// among the block's keys of its digit counts the earlier ones: earlier rounds
-// (running), earlier waves of this round, and earlier lanes of this wave
-// (ballot match); its destination is its digit's global offset for this
-// block plus that rank.  The keys are first placed in LDS in digit order (the
-// digit's start inside the block plus the rank) and then written out in that
-// order, so that consecutive threads store consecutive slots of a digit's run.
-__global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(
-    const uint64_t *__restrict__ keys, const uint32_t *__restrict__ vals, uint32_t n, uint32_t shift,
-    uint32_t nb, const uint32_t *__restrict__ offs, uint64_t *__restrict__ okeys,
-    uint32_t *__restrict__ ovals) {
-  static_assert(RS_BINS == RS_THREADS, "one digit per thread");
-  __shared__ uint64_t s_key[RS_CHUNK];
-  __shared__ uint32_t s_val[RS_CHUNK];
-  __shared__ uint32_t running[RS_BINS], lstart[RS_BINS], gstart[RS_BINS];
-  __shared__ uint32_t wcnt[RS_THREADS / 64][RS_BINS];
-  __shared__ uint32_t wsum[RS_THREADS / 64];
-  const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
-  const uint32_t b0 = blockIdx.x * RS_CHUNK;
-  // this block's count of digit d = threadIdx.x: the next entry of the scanned
-  // [digit][block] offsets less its own (the last entry's next is n)
-  const uint32_t o = threadIdx.x * nb + blockIdx.x;
-  const uint32_t g = offs[o];
-  const uint32_t c = (o + 1 < RS_BINS * nb ? offs[o + 1] : n) - g;
-  uint32_t x = c;
-#pragma unroll
-  for (uint32_t d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d, 64);
-    if (lane >= d) x += y;
-  }
-  if (lane == 63) wsum[w] = x;
-  __syncthreads();
-  uint32_t ex = x - c;
-  for (uint32_t q = 0; q < w; ++q) ex += wsum[q];
-  lstart[threadIdx.x] = ex;
-  gstart[threadIdx.x] = g;
-  running[threadIdx.x] = ex;
-  for (uint32_t q = 0; q < RS_THREADS / 64; ++q) wcnt[q][threadIdx.x] = 0;
-  __syncthreads();
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  // the block's keys and values loaded up front (one round trip)
-  uint64_t kr[RS_ITEMS];
-  uint32_t vr[RS_ITEMS];
-#pragma unroll
-  for (uint32_t k = 0; k < RS_ITEMS; ++k) {
-    const uint32_t j = b0 + k * RS_THREADS + threadIdx.x;
-    kr[k] = j < n ? keys[j] : 0ull;
-    vr[k] = j < n ? vals[j] : 0u;
-  }
-#pragma unroll
-  for (uint32_t k = 0; k < RS_ITEMS; ++k) {
-    const uint32_t j = b0 + k * RS_THREADS + threadIdx.x;
-    const bool valid = j < n;
-    const uint64_t key = kr[k];
-    const uint32_t val = vr[k];
-    const uint32_t d = (uint32_t)(key >> shift) & 0xFFu;
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (uint32_t b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t bal = __ballot(bit);
-      peers &= bit ? bal : ~bal;
-    }
-    const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
-    if (valid && below == 0) wcnt[w][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t pre = running[d] + below;
-      for (uint32_t q = 0; q < w; ++q) pre += wcnt[q][d];
-      s_key[pre] = key;
-      s_val[pre] = val;
-    }
-    __syncthreads();
-    uint32_t add = 0;
-    for (uint32_t q = 0; q < RS_THREADS / 64; ++q) {
-      add += wcnt[q][threadIdx.x];
-      wcnt[q][threadIdx.x] = 0;
-    }
-    running[threadIdx.x] += add;
-    __syncthreads();
-  }
-  const uint32_t cnt = n - b0 < RS_CHUNK ? n - b0 : RS_CHUNK;
-  for (uint32_t p = threadIdx.x; p < cnt; p += RS_THREADS) {
-    const uint64_t key = s_key[p];
-    const uint32_t d = (uint32_t)(key >> shift) & 0xFFu;
-    const uint32_t dst = gstart[d] + (p - lstart[d]);
-    okeys[dst] = key;
-    ovals[dst] = s_val[p];
+    if (j < n) io[j] = run;
+    run += v[k];
   }
 }
 
@@ -357,11 +243,22 @@ __device__ __forceinline__ void wave_hist_add(uint32_t *h, uint32_t d, bool vali
   if ((pending >> lane) & 1ull) atomicAdd(&h[d], 1u);
 }
 
+// A pass's digit of a pair: eight of its bits or, with sub, eight bits of the
+// subset its sample belongs to.
+template <bool SUB>
+__device__ __forceinline__ uint32_t seg_digit(uint64_t v, uint32_t shift,
+                                              const uint32_t *__restrict__ sub) {
+  if constexpr (SUB) return (sub[(uint32_t)v] >> shift) & 0xFFu;
+  else return (uint32_t)(v >> shift) & 0xFFu;
+}
+
 // Digit counts of block (f, j): positions [j SG_R, (j + 1) SG_R) of segment f,
 // into hist[(f 256 + digit) nbf + j].
+template <bool SUB>
 __global__ __launch_bounds__(SG_THREADS) void k_seg_hist(const uint64_t *__restrict__ src,
                                                          uint32_t n, uint32_t F, uint32_t nbf,
                                                          uint32_t shift,
+                                                         const uint32_t *__restrict__ sub,
                                                          uint32_t *__restrict__ hist) {
   __shared__ uint32_t h[SG_THREADS / 64][256];
   const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
@@ -377,7 +274,7 @@ __global__ __launch_bounds__(SG_THREADS) void k_seg_hist(const uint64_t *__restr
 #pragma unroll
   for (uint32_t k = 0; k < SG_ITEMS; ++k) {
     const uint32_t q = lo + k * SG_THREADS + threadIdx.x;
-    d[k] = q < hi ? (uint32_t)(seg[q] >> shift) & 0xFFu : 256u;
+    d[k] = q < hi ? seg_digit<SUB>(seg[q], shift, sub) : 256u;
   }
 #pragma unroll
   for (uint32_t k = 0; k < SG_ITEMS; ++k)
@@ -389,16 +286,59 @@ __global__ __launch_bounds__(SG_THREADS) void k_seg_hist(const uint64_t *__restr
   hist[((size_t)f * 256 + threadIdx.x) * nbf + j] = t;
 }
 
+// Block f: exclusive scan of feature f's len digit counts in place, from the
+// segment's first position f n.  One launch of a block per feature instead of
+// the three of a scan over all features' counts; its serial chain of 4,096
+// counts per step is the shorter way up to SEG_SCAN_MAX_NBF chunks a feature
+// (20 against 25 us at 245 chunks of 32 features; at 489 chunks the chain is
+// twice as long, the three launches stay at 25).
+constexpr uint32_t SEG_SCAN_MAX_NBF = 256;
+__global__ __launch_bounds__(1024) void k_seg_scan(uint32_t *__restrict__ hist, uint32_t n,
+                                                   uint32_t len) {
+  __shared__ uint32_t s_w[16];
+  const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+  uint4 *h = reinterpret_cast<uint4 *>(hist + (size_t)blockIdx.x * len);  // len % 256 == 0
+  const uint32_t len4 = len / 4;
+  uint32_t run = blockIdx.x * n;
+  uint4 next = make_uint4(0u, 0u, 0u, 0u);
+  if (threadIdx.x < len4) next = h[threadIdx.x];
+  for (uint32_t q0 = 0; q0 < len4; q0 += 1024u) {
+    const uint32_t q = q0 + threadIdx.x;
+    const uint4 v = next;
+    next = make_uint4(0u, 0u, 0u, 0u);
+    if (q + 1024u < len4) next = h[q + 1024u];  // in flight during the scan
+    const uint32_t t = v.x + v.y + v.z + v.w;
+    uint32_t x = t;
+#pragma unroll
+    for (uint32_t d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(x, d, 64);
+      if (lane >= d) x += y;
+    }
+    if (lane == 63) s_w[w] = x;
+    __syncthreads();
+    uint32_t before = run + x - t;
+#pragma unroll
+    for (uint32_t u = 0; u < 16; ++u) {
+      before += u < w ? s_w[u] : 0u;
+      run += s_w[u];
+    }
+    __syncthreads();
+    if (q < len4) h[q] = make_uint4(before, before + v.x, before + v.x + v.y, before + v.x + v.y + v.z);
+  }
+}
+
 // Block (f, j) of a pass: its pairs (wave w holds the span of SG_WSPAN
 // positions w SG_WSPAN ..., 64 at a time in registers) stably sorted by digit
 // into LDS (a wave's digit counts and their offsets in the block's order,
 // then each pair's rank among the earlier pairs of its wave with the same
 // digit by ballot match), and written out: digit d's run goes to offs[(f 256
 // + d) nbf + j], the global position the scan gave it.
+template <bool SUB>
 __global__ __launch_bounds__(SG_THREADS) void k_seg_scatter(const uint64_t *__restrict__ src,
                                                             uint64_t *__restrict__ dst,
                                                             uint32_t n, uint32_t F, uint32_t nbf,
                                                             uint32_t shift,
+                                                            const uint32_t *__restrict__ sub,
                                                             const uint32_t *__restrict__ offs) {
   __shared__ uint64_t kv[SG_R];
   __shared__ uint32_t wc[SG_THREADS / 64][256];
@@ -420,7 +360,7 @@ __global__ __launch_bounds__(SG_THREADS) void k_seg_scatter(const uint64_t *__re
   for (uint32_t k = 0; k < RND; ++k) {
     const uint32_t q = w * SG_WSPAN + k * 64 + lane;
     v[k] = q < cnt ? seg[q] : 0ull;
-    d[k] = q < cnt ? (uint32_t)(v[k] >> shift) & 0xFFu : 256u;
+    d[k] = q < cnt ? seg_digit<SUB>(v[k], shift, sub) : 256u;
   }
   __syncthreads();
 #pragma unroll
@@ -469,7 +409,7 @@ __global__ __launch_bounds__(SG_THREADS) void k_seg_scatter(const uint64_t *__re
   __syncthreads();
   for (uint32_t q = threadIdx.x; q < cnt; q += SG_THREADS) {
     const uint64_t x = kv[q];
-    dst[gpos[(uint32_t)(x >> shift) & 0xFFu] + q] = x;
+    dst[gpos[seg_digit<SUB>(x, shift, sub)] + q] = x;
   }
 }
 
@@ -769,46 +709,47 @@ __global__ __launch_bounds__(RC_THREADS) void k_rank_coop(RankCoopArgs a) {
 }
 }  // namespace
 
-mh_status scan_u32(Ctx *ctx, const uint32_t *in, uint32_t *out, uint32_t n, bool inclusive) {
+namespace {
+// Exclusive scan of n u32 values in place, in three launches.
+mh_status scan_u32(Ctx *ctx, uint32_t *v, uint32_t n) {
   uint32_t nb = (n + RS_CHUNK - 1) / RS_CHUNK;
   uint32_t *sums = (uint32_t *)arena_get(ctx, "scan_sums", (size_t)(nb ? nb : 1) * 4);
   if (!sums) return MH_ENOMEM;
   hipStream_t st = ctx->stream;
-  k_scan_sums<<<nb, RS_THREADS, 0, st>>>(in, n, sums);
+  k_scan_sums<<<nb, RS_THREADS, 0, st>>>(v, n, sums);
   MH_LAUNCHED(ctx, "k_scan_sums");
   k_scan_top<<<1, 1024, 0, st>>>(sums, nb);
   MH_LAUNCHED(ctx, "k_scan_top");
-  k_scan_apply<<<nb, RS_THREADS, 0, st>>>(in, out, n, sums, inclusive ? 1 : 0);
+  k_scan_apply<<<nb, RS_THREADS, 0, st>>>(v, n, sums);
   MH_LAUNCHED(ctx, "k_scan_apply");
   return MH_OK;
 }
 
-mh_status radix_sort_pairs(Ctx *ctx, uint64_t **keys, uint32_t **vals, uint64_t *keys_alt,
-                           uint32_t *vals_alt, uint32_t count, uint32_t key_bits) {
-  if (count == 0) return MH_OK;
-  uint32_t nb = (count + RS_CHUNK - 1) / RS_CHUNK;
-  uint32_t nh = nb * RS_BINS;
-  uint32_t *hist = (uint32_t *)arena_get(ctx, "rs_hist", (size_t)nh * 4);
+}  // namespace
+
+mh_status seg_radix_pass(Ctx *ctx, const uint64_t *src, uint64_t *dst, uint32_t n, uint32_t F,
+                         uint32_t shift, const uint32_t *sub) {
+  const uint32_t nbf = (n + SG_R - 1) / SG_R, nh = F * 256 * nbf, grid = xcd_grid(F * nbf);
+  uint32_t *hist = (uint32_t *)arena_get(ctx, "re_seg_hist", (size_t)nh * 4);
   if (!hist) return MH_ENOMEM;
   hipStream_t st = ctx->stream;
-  uint64_t *k0 = *keys, *k1 = keys_alt;
-  uint32_t *v0 = *vals, *v1 = vals_alt;
-  for (uint32_t shift = 0; shift < key_bits; shift += 8) {
-    k_rs_hist<<<nb, RS_THREADS, 0, st>>>(k0, count, shift, nb, hist);
-    MH_LAUNCHED(ctx, "k_rs_hist");
-    mh_status s = scan_u32(ctx, hist, hist, nh, false);
+  if (sub)
+    k_seg_hist<true><<<grid, SG_THREADS, 0, st>>>(src, n, F, nbf, shift, sub, hist);
+  else
+    k_seg_hist<false><<<grid, SG_THREADS, 0, st>>>(src, n, F, nbf, shift, sub, hist);
+  MH_LAUNCHED(ctx, "k_seg_hist");
+  if (nbf <= SEG_SCAN_MAX_NBF) {
+    k_seg_scan<<<F, 1024, 0, st>>>(hist, n, 256u * nbf);
+    MH_LAUNCHED(ctx, "k_seg_scan");
+  } else {
+    mh_status s = scan_u32(ctx, hist, nh);
     if (s) return s;
-    k_rs_scatter<<<nb, RS_THREADS, 0, st>>>(k0, v0, count, shift, nb, hist, k1, v1);
-    MH_LAUNCHED(ctx, "k_rs_scatter");
-    uint64_t *tk = k0;
-    k0 = k1;
-    k1 = tk;
-    uint32_t *tv = v0;
-    v0 = v1;
-    v1 = tv;
   }
-  *keys = k0;
-  *vals = v0;
+  if (sub)
+    k_seg_scatter<true><<<grid, SG_THREADS, 0, st>>>(src, dst, n, F, nbf, shift, sub, hist);
+  else
+    k_seg_scatter<false><<<grid, SG_THREADS, 0, st>>>(src, dst, n, F, nbf, shift, sub, hist);
+  MH_LAUNCHED(ctx, "k_seg_scatter");
   return MH_OK;
 }
 
@@ -908,10 +849,9 @@ mh_status launch_rank_encode(Ctx *ctx, const float *X, uint32_t n, uint32_t F, u
   if (!done) {
     uint64_t *ka = (uint64_t *)arena_get(ctx, "re_keys_a", (size_t)total * 8);
     uint64_t *kb = (uint64_t *)arena_get(ctx, "re_keys_b", (size_t)total * 8);
-    const uint32_t nbf = (n + SG_R - 1) / SG_R, nh = F * 256 * nbf;
-    uint32_t *hist = (uint32_t *)arena_get(ctx, "re_seg_hist", (size_t)nh * 4);
+    const uint32_t nbf = (n + SG_R - 1) / SG_R;
     uint32_t *ucnt = (uint32_t *)arena_get(ctx, "re_ucnt", (size_t)F * nbf * 4);
-    if (!ka || !kb || !hist || !ucnt) return MH_ENOMEM;
+    if (!ka || !kb || !ucnt) return MH_ENOMEM;
     // rows per transposing block: an LDS tile of rows x (F + 1) words
     const uint32_t rows = std::max(1u, std::min(256u, (uint32_t)(16384u / (F + 1u))));
     const uint32_t kblocks = (n + rows - 1) / rows;
@@ -920,13 +860,8 @@ mh_status launch_rank_encode(Ctx *ctx, const float *X, uint32_t n, uint32_t F, u
     MH_LAUNCHED(ctx, "k_seg_keys");
     uint64_t *a = ka, *b = kb;
     for (uint32_t pass = 0; pass < 4; ++pass) {
-      const uint32_t shift = 32 + 8 * pass;
-      k_seg_hist<<<xcd_grid(F * nbf), SG_THREADS, 0, st>>>(a, n, F, nbf, shift, hist);
-      MH_LAUNCHED(ctx, "k_seg_hist");
-      mh_status s = scan_u32(ctx, hist, hist, nh, false);
+      mh_status s = seg_radix_pass(ctx, a, b, n, F, 32 + 8 * pass, nullptr);
       if (s) return s;
-      k_seg_scatter<<<xcd_grid(F * nbf), SG_THREADS, 0, st>>>(a, b, n, F, nbf, shift, hist);
-      MH_LAUNCHED(ctx, "k_seg_scatter");
       std::swap(a, b);
     }
     k_seg_ucount<<<xcd_grid(F * nbf), SG_THREADS, 0, st>>>(a, n, F, nbf, ucnt);

@@ -1,0 +1,55 @@
+"""GPU parity of the batched depth-1 split and of CART's level-to-level
+partition at the sizes where their kernels change course (spans of 512
+positions, waves of 64, blocks of four spans, subset runs that share a span,
+more than 64 classes, samples past the packed class byte).  Bar: equal trees
+and counts; scores are exact integers or one f64 expression on both sides."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2311_06952_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mh():
+    import paper_2311_06952_amd as m
+    return m
+
+
+def _check(mh, X, y, K, D):
+    ods, ds = oracle.dataset_from_X(X, y, K), mh.dataset(X, y, K)
+    feat, tau = mh.cart(ds, D)
+    want = oracle.cart(ods, D)
+    np.testing.assert_array_equal(feat, want[0])
+    np.testing.assert_array_equal(tau, want[1])
+    assert mh.split1(ds) == tuple(int(v) for v in oracle.split1(ods))
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 511, 512, 513, 2047, 2048, 2049, 4097])
+@pytest.mark.parametrize("levels", [None, 3])
+def test_span_edges(mh, n, levels):
+    X, y = synth.random_small(n, n, 5, 3, levels)
+    _check(mh, X, y, 3, 4)
+
+
+@pytest.mark.parametrize("K", [1, 2, 63, 64, 65, 255])
+def test_class_counts(mh, K):
+    X, y = synth.random_small(100 + K, 3001, 4, K, 40)
+    _check(mh, X, y, K, 5)
+
+
+def test_many_small_runs(mh):
+    """Depth 10 on 1,500 samples: hundreds of runs, most spans cross several."""
+    X, y = synth.random_small(7, 1500, 3, 4)
+    _check(mh, X, y, 4, 10)
+
+
+def test_class_read_from_labels(mh):
+    """More than 2^24 samples: ranks need the byte that carries the class."""
+    n = (1 << 24) + 1001
+    rng = np.random.default_rng(5)
+    X = rng.random((n, 2), dtype=np.float32)
+    y = ((X[:, 0] > 0.4).astype(np.uint8) + (rng.random(n) < 0.1)).astype(np.uint8)
+    _check(mh, X, y, 3, 2)
