@@ -535,6 +535,8 @@ mh_status mh_ctx_create(int device, void *hip_stream, mh_ctx **out) {
     c->c.persist_halves = atoi(v) >= 4 ? 4u : (atoi(v) == 1 ? 1u : 2u);
   if (const char *v = std::getenv("MHDEOCT_PERSIST_BLOCKS_PER_CU"))
     c->c.persist_blocks_per_cu = (uint32_t)std::max(1, atoi(v));
+  if (const char *v = std::getenv("MHDEOCT_RESIDENT_BLOCKS"))
+    c->c.resident_blocks = (uint32_t)std::max(0, atoi(v));
   if (const char *v = std::getenv("MHDEOCT_RANK_COOP")) c->c.rank_coop = atoi(v) != 0;
   if (const char *v = std::getenv("MHDEOCT_DEBUG")) c->c.debug = atoi(v) != 0;
   if (const char *v = std::getenv("MHDEOCT_WALK_IT")) c->c.walk_it = (uint32_t)std::max(0, atoi(v));

@@ -55,6 +55,7 @@ struct Ctx {
   uint32_t persist_blocks_per_cu = 0;  // its blocks per CU; 0 = by size (MHDEOCT_PERSIST_BLOCKS_PER_CU)
   uint32_t persist_halves = 2;         // tile streams per block, 1, 2 or 4 (MHDEOCT_PERSIST_HALVES)
   bool persist_resident = true;        // tiles kept in LDS when they fit (MHDEOCT_PERSIST_RESIDENT)
+  uint32_t resident_blocks = 0;  // blocks of a resident run; 0 = by size (MHDEOCT_RESIDENT_BLOCKS)
   bool coop = false;     // the device supports cooperative launches
   uint32_t max_lds = 64u * 1024u;  // dynamic LDS one block may use
   // launch configurations chosen by mh_autotune, by problem shape
@@ -415,12 +416,12 @@ mh_status launch_deoct_persist(Ctx *ctx, const void *tiles, uint32_t F, uint32_t
 // counters and barrier, and its DE state at problem stride in pop ([m][P]
 // per problem), cost ([P] per problem) and best ([n_problems]).
 // class_counts: HOST [n_problems][K] samples per class (as in the layout);
-// prob_ids: device [n_problems].
+// prob_ids: device [n_problems]; host_ids: the same on the host.
 mh_status launch_deoct_persist_multi(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K,
                                      uint32_t n_sub, uint32_t n_problems,
                                      const uint32_t *class_counts, uint32_t D,
                                      const mh_de_params *prm, const uint64_t *prob_ids,
-                                     const uint32_t *n_unique, double *pop, double *cost,
+                                     const uint64_t *host_ids, const uint32_t *n_unique, double *pop, double *cost,
                                      uint32_t *best, uint32_t *err, bool *used);
 
 // split.hip
@@ -456,8 +457,8 @@ mh_status launch_level_hist(Ctx *ctx, const uint32_t *node_of, const uint8_t *la
 // one cooperative launch.
 // warm: device [n_problems][W][2 SB] warm-start genes (W may be 0).
 mh_status deoct_batched(Ctx *ctx, const mh_dataset *ds, const uint32_t *sub_of,
-                        uint32_t n_problems, const uint64_t *prob_ids, uint32_t D,
-                        const mh_de_params *prm, const uint32_t *class_counts,
+                        uint32_t n_problems, const uint64_t *prob_ids, const uint64_t *host_ids,
+                        uint32_t D, const mh_de_params *prm, const uint32_t *class_counts,
                         const double *warm, uint32_t W, uint8_t *feat_out, uint32_t *tau_out);
 // Sequential-form helper: the samples at node t (device idx, atomics order);
 // and the moving-horizon driver itself.

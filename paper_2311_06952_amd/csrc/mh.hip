@@ -136,8 +136,8 @@ mh_status launch_compact(Ctx *ctx, const uint32_t *node_of, uint32_t n, uint32_t
 // Multi-problem DEOCT: one tile set over all problems, one fitness launch and
 // one fused epilogue + DE step (a block per problem) per generation.
 mh_status deoct_batched(Ctx *ctx, const mh_dataset *ds, const uint32_t *sub_of,
-                        uint32_t n_problems, const uint64_t *prob_ids, uint32_t D,
-                        const mh_de_params *prm, const uint32_t *class_counts,
+                        uint32_t n_problems, const uint64_t *prob_ids, const uint64_t *host_ids,
+                        uint32_t D, const mh_de_params *prm, const uint32_t *class_counts,
                         const double *warm, uint32_t W, uint8_t *feat_out, uint32_t *tau_out) {
   const uint32_t P = prm->P, SB = (1u << D) - 1u, m = 2 * SB, K = ds->K, F = ds->F;
   if (D > 5 || F > 80) return fail(ctx, MH_EINVAL, "batched DEOCT needs depth <= 5 and F <= 80");
@@ -168,7 +168,7 @@ mh_status deoct_batched(Ctx *ctx, const mh_dataset *ds, const uint32_t *sub_of,
     if (!err) return MH_ENOMEM;
     bool used = false;
     s = launch_deoct_persist_multi(ctx, tiles, F, K, ds->n, n_problems, class_counts, D, prm,
-                                   prob_ids, ds->n_unique, pop, cost, best, err, &used);
+                                   prob_ids, host_ids, ds->n_unique, pop, cost, best, err, &used);
     if (s) return s;
     if (used) {
       s = launch_decode(ctx, pop, P, D, F, ds->n_unique, feat_out, tau_out, n_problems, best, true);
@@ -380,7 +380,7 @@ mh_status mh_train_impl(Ctx *ctx, const mh_dataset *ds, uint32_t D, uint32_t D_M
                            ws_cart ? cf : nullptr, ct, W, wg);
           if (s) return s;
         }
-        mh_status s = deoct_batched(ctx, ds, sub_of, na, pids, De, prm, cc.data(), wg, W, rf, rt);
+        mh_status s = deoct_batched(ctx, ds, sub_of, na, pids, pid.data(), De, prm, cc.data(), wg, W, rf, rt);
         if (s) return s;
       } else {
         std::vector<uint8_t> hf(na);

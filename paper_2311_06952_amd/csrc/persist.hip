@@ -26,6 +26,7 @@
 // operations.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cfloat>
 #include <cstdio>
 #include <type_traits>
@@ -36,6 +37,7 @@
 #include "fitness_core.h"
 #include "grid_sync.h"
 #include "internal.h"
+#include "persist.h"
 
 namespace mh {
 namespace {
@@ -71,40 +73,6 @@ struct PersistArgs {
   double *out_cost;
   uint64_t wait_ticks;  // barrier time limit, device wall-clock ticks
 };
-
-__host__ __device__ __forceinline__ uint32_t align16u(uint32_t x) { return (x + 15u) & ~15u; }
-
-// (cost, index) of the wave's smallest cost, ties to the lower index: DPP
-// row shifts (1, 2, 4, 8) reduce each row of 16 lanes into its last lane,
-// two row broadcasts fold the four rows into lane 63, which is read back.
-// A lane with no source in a step sees the (largest cost, largest index)
-// sentinel, which never wins.
-__device__ __forceinline__ void wave_argmin(double &c, uint32_t &i) {
-  auto step = [&](auto ctrl_tag, auto mask_tag) {
-    constexpr int ctrl = decltype(ctrl_tag)::value, rmask = decltype(mask_tag)::value;
-    const uint32_t lo = (uint32_t)__double2loint(c), hi = (uint32_t)__double2hiint(c);
-    const uint32_t nlo = (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFFu, (int)lo, ctrl,
-                                                               rmask, 0xF, false);
-    const uint32_t nhi = (uint32_t)__builtin_amdgcn_update_dpp((int)0x7FEFFFFFu, (int)hi, ctrl,
-                                                               rmask, 0xF, false);
-    const uint32_t ni = (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFFu, (int)i, ctrl,
-                                                              rmask, 0xF, false);
-    const double cn = __hiloint2double((int)nhi, (int)nlo);
-    const bool better = (cn < c) | ((cn == c) & (ni < i));
-    c = better ? cn : c;
-    i = better ? ni : i;
-  };
-  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});  // row_shr:1
-  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});  // row_shr:2
-  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});  // row_shr:4
-  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});  // row_shr:8
-  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});  // row_bcast:15
-  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});  // row_bcast:31
-  const int lo = __builtin_amdgcn_readlane(__double2loint(c), 63);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(c), 63);
-  c = __hiloint2double(hi, lo);
-  i = (uint32_t)__builtin_amdgcn_readlane((int)i, 63);
-}
 
 // LDS after n_unique: argmin scratch (32 costs, 32 indices) and the info
 // words of resident tiles (MAX_TPH per group, 4 groups at most).
@@ -905,11 +873,107 @@ mh_status launch_dh(Ctx *ctx, uint32_t waves, uint32_t H, const PersistArgs &pa,
   return launch_d<D, 1>(ctx, waves, pa, lds, max_tiles, gr, used);
 }
 
+// The same run with its tiles resident in LDS (resident.hip), when every
+// problem's share fits.
+mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint32_t n_sub,
+                       uint64_t n_eval, uint32_t n_problems, uint32_t D, const mh_de_params *prm,
+                       uint64_t prob, const uint64_t *host_ids,
+                       const std::vector<uint32_t> *ptiles, const uint32_t *n_unique, double *pop,
+                       double *cost, uint32_t *best, uint32_t *err, const PersistFinal *fin,
+                       bool *used) {
+  *used = false;
+  const uint32_t P = prm->P, SB = (1u << D) - 1u, m = 2 * SB, cus = (uint32_t)ctx->num_cu;
+  if (n_problems > cus) return MH_OK;
+  // blocks: each problem's own best number; scaled down to the CUs in
+  // proportion where they do not suffice
+  const uint32_t max_tiles = tile_layout(n_sub, F, K, n_problems).max_tiles;
+  std::vector<RunShape> sh(n_problems);
+  auto tiles_of = [&](uint32_t i) { return ptiles ? (*ptiles)[i] : max_tiles; };
+  uint64_t total = 0, all_tiles = 0;
+  for (uint32_t i = 0; i < n_problems; ++i) {
+    sh[i] = resident_shape(ctx, D, P, F, K, tiles_of(i), cus);
+    if (!sh[i].nblk) return MH_OK;
+    total += sh[i].nblk;
+    all_tiles += tiles_of(i);
+  }
+  if (total > cus) {
+    for (uint32_t i = 0; i < n_problems; ++i) {
+      const uint64_t room = cus - n_problems;
+      const uint32_t nb = 1u + (uint32_t)(all_tiles ? room * tiles_of(i) / all_tiles : 0);
+      sh[i] = resident_shape(ctx, D, P, F, K, tiles_of(i), nb);
+      if (!sh[i].nblk) return MH_OK;
+    }
+  }
+  const size_t cstride = (size_t)SB * K * pad64(P);
+  const uint32_t bar_words = barrier_words(cus);
+  uint32_t *cnt = (uint32_t *)arena_get(ctx, "ps_cnt", (size_t)n_problems * 3 * cstride * 4);
+  uint32_t *bar = (uint32_t *)arena_get(ctx, "ps_bar", (size_t)n_problems * bar_words * 4);
+  RunArgs *runs_dev = (RunArgs *)arena_get(ctx, "ps_runs", n_problems * sizeof(RunArgs));
+  uint32_t *map_dev = (uint32_t *)arena_get(ctx, "ps_map", (size_t)cus * 4);
+  if (!cnt || !bar || !runs_dev || !map_dev) return MH_ENOMEM;
+  std::vector<RunArgs> runs(n_problems);
+  uint32_t t0 = 0, blk = 0, lds = 0;
+  bool solo = true;
+  for (uint32_t i = 0; i < n_problems; ++i) {
+    RunArgs &a = runs[i];
+    a.hdr = reinterpret_cast<const TileHdr *>(tiles);
+    a.n_unique = n_unique;
+    a.pop = pop + (size_t)i * P * m;
+    a.cost = cost + (size_t)i * P;
+    a.best = best + i;
+    a.cnt = cnt + (size_t)i * 3 * cstride;
+    a.bar = bar + (size_t)i * bar_words;
+    a.err = err;
+    a.out_feat = fin ? fin->feat : nullptr;
+    a.out_tau = fin ? fin->tau : nullptr;
+    a.out_label = fin ? fin->label : nullptr;
+    a.out_correct = fin ? fin->correct : nullptr;
+    a.out_cost = fin ? fin->cost : nullptr;
+    a.M = prm->M;
+    a.CR = prm->CR;
+    a.alpha = prm->alpha;
+    a.seed = prm->seed;
+    a.prob = host_ids ? host_ids[i] : prob;
+    a.P = P;
+    a.G = prm->G;
+    a.n_min = prm->n_min;
+    a.F = F;
+    a.K = K;
+    a.tile0 = t0;
+    a.tile1 = t0 + tiles_of(i);
+    a.sub = i;
+    a.blk0 = blk;
+    a.nblk = sh[i].nblk;
+    a.tiles_max = sh[i].tiles_max;
+    a.slots = sh[i].slots;
+    t0 += tiles_of(i);
+    blk += sh[i].nblk;
+    lds = std::max(lds, sh[i].lds);
+    solo = solo && sh[i].nblk == 1;
+  }
+  // (runs of one block use neither the counters nor the barrier)
+  mh_status s = launch_zero(ctx, {{solo ? nullptr : cnt, (size_t)n_problems * 3 * cstride * 4},
+                                  {solo ? nullptr : bar, (size_t)n_problems * bar_words * 4},
+                                  {err, 4}});
+  if (s) return s;
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  const bool timed = prof_pair(ctx, &e0, &e1);
+  if (timed) MH_HIP(ctx, hipEventRecord(e0, ctx->stream));
+  s = launch_resident(ctx, D, runs, lds, runs_dev, map_dev, used);
+  if (s) return s;
+  if (timed) {
+    MH_HIP(ctx, hipEventRecord(e1, ctx->stream));
+    if (*used) ctx->prof_launches += 1;
+  }
+  if (*used) ctx->prof_evals += (uint64_t)(prm->G + 1) * n_eval * P;
+  return MH_OK;
+}
+
 // One problem (ptiles == null) or the problems of a multi-problem tile set.
 mh_status persist_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint32_t n_sub,
                       uint64_t n_eval, uint32_t n_problems, uint32_t D, const mh_de_params *prm,
-                      uint64_t prob,
-                      const uint64_t *prob_ids, const std::vector<uint32_t> *ptiles,
+                      uint64_t prob, const uint64_t *prob_ids, const uint64_t *host_ids,
+                      const std::vector<uint32_t> *ptiles,
                       const uint32_t *n_unique, double *pop, double *cost, uint32_t *best,
                       uint32_t *err, const PersistFinal *fin, bool *used) {
   *used = false;
@@ -919,6 +983,11 @@ mh_status persist_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint3
     return MH_OK;
   // barrier targets (G + 2) * blocks must fit the 32-bit arrival counters
   if ((uint64_t)(prm->G + 2) * (uint64_t)ctx->num_cu * 8u >= (1ull << 31)) return MH_OK;
+  if (ctx->persist_resident) {
+    const mh_status rs = resident_run(ctx, tiles, F, K, n_sub, n_eval, n_problems, D, prm, prob,
+                                      host_ids, ptiles, n_unique, pop, cost, best, err, fin, used);
+    if (rs || *used) return rs;
+  }
   uint32_t waves = pad64(P) / 64;
   waves = waves > 4 ? 8 : (waves > 2 ? 4 : waves);
   // up to persist_halves tile streams per block, as the LDS and the
@@ -1008,7 +1077,7 @@ mh_status launch_deoct_persist(Ctx *ctx, const void *tiles, uint32_t F, uint32_t
                                const uint32_t *n_unique, double *pop, double *cost,
                                uint32_t *best, uint32_t *err, const PersistFinal *fin,
                                bool *used) {
-  return persist_run(ctx, tiles, F, K, n_sub, n_sub, 1, D, prm, prob, nullptr, nullptr, n_unique,
+  return persist_run(ctx, tiles, F, K, n_sub, n_sub, 1, D, prm, prob, nullptr, nullptr, nullptr, n_unique,
                      pop, cost, best, err, fin, used);
 }
 
@@ -1016,6 +1085,7 @@ mh_status launch_deoct_persist_multi(Ctx *ctx, const void *tiles, uint32_t F, ui
                                      uint32_t n_sub, uint32_t n_problems,
                                      const uint32_t *class_counts, uint32_t D,
                                      const mh_de_params *prm, const uint64_t *prob_ids,
+                                     const uint64_t *host_ids,
                                      const uint32_t *n_unique, double *pop, double *cost,
                                      uint32_t *best, uint32_t *err, bool *used) {
   // tiles per problem, in the layout's order (problem-major, then class)
@@ -1026,7 +1096,7 @@ mh_status launch_deoct_persist_multi(Ctx *ctx, const void *tiles, uint32_t F, ui
       tl[i] += (class_counts[(size_t)i * K + k] + TILE_CAP - 1) / TILE_CAP;
       n_eval += class_counts[(size_t)i * K + k];
     }
-  return persist_run(ctx, tiles, F, K, n_sub, n_eval, n_problems, D, prm, 0, prob_ids, &tl,
+  return persist_run(ctx, tiles, F, K, n_sub, n_eval, n_problems, D, prm, 0, prob_ids, host_ids, &tl,
                      n_unique, pop, cost, best, err, nullptr, used);
 }
 
