@@ -12,6 +12,7 @@
 #include "de_body.h"
 #include "device_common.h"
 #include "internal.h"
+#include "small.h"
 
 
 namespace mh {
@@ -279,7 +280,7 @@ static size_t eval_scratch_bytes(const mh_dataset *ds, uint32_t n_sub, uint32_t 
 static mh_status prepare_eval(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub,
                               uint32_t D, uint32_t P, const char *tile_name, const char *cnt_name,
                               EvalSet &es, uint8_t *static_base = nullptr,
-                              uint32_t min_trees = 0) {
+                              uint32_t min_trees = 0, const SmallJob *init = nullptr) {
   es.ds = ds;
   es.idx = idx;
   es.n_sub = n_sub;
@@ -295,7 +296,7 @@ static mh_status prepare_eval(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
                       ? reinterpret_cast<uint32_t *>(static_base + align256(h.total_bytes))
                       : (uint32_t *)arena_get(ctx, cnt_name, cnt_bytes(1, D, ds->K, P));
   if (!tiles || !cnt) return MH_ENOMEM;
-  mh_status s = launch_tile_build(ctx, ds, idx, nullptr, n_sub, 1, tiles, h.total_bytes);
+  mh_status s = launch_tile_build(ctx, ds, idx, nullptr, n_sub, 1, tiles, h.total_bytes, init);
   if (s) return s;
   es.tiles = tiles;
   es.cnt = cnt;
@@ -310,9 +311,20 @@ static mh_status deoct(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint
   const uint32_t P = prm->P, SB = (1u << D) - 1u, SL = 1u << D, m = 2 * SB, K = ds->K;
   hipStream_t st = ctx->stream;
   EvalSet es;
-  mh_status s = prepare_eval(ctx, ds, idx, n_sub, D, P, "ss_tiles", "ss_cnt", es);
-  if (s) return s;
   double *pop = (double *)arena_get(ctx, "ss_pop", (size_t)P * m * 8);
+  if (!pop) return MH_ENOMEM;
+  // small data without warm starts: the initial population in the tile plan's
+  // launch
+  SmallJob init{};
+  init.pop = pop;
+  init.seed = prm->seed;
+  init.prob = prob;
+  init.P = P;
+  init.SB = SB;
+  const bool init_done = W == 0 && tile_path_ok(D, ds->F, ds->n) && tiles_small(ds, n_sub);
+  mh_status s = prepare_eval(ctx, ds, idx, n_sub, D, P, "ss_tiles", "ss_cnt", es, nullptr, 0,
+                             init_done ? &init : nullptr);
+  if (s) return s;
   double *trial = (double *)arena_get(ctx, "ss_trial", (size_t)P * m * 8);
   double *cost = (double *)arena_get(ctx, "ss_cost", (size_t)P * 8);
   double *tcost = (double *)arena_get(ctx, "ss_tcost", (size_t)P * 8);
@@ -331,15 +343,17 @@ static mh_status deoct(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint
     // host genes from the C ABI; device genes from the moving horizon
     MH_HIP(ctx, hipMemcpyAsync(warm, warm_host, (size_t)W * m * 8, hipMemcpyDefault, st));
   }
-  if (!pop || !trial || !cost || !tcost || !feat || !tau || !best || !f1 || !t1 || !lab1 ||
+  if (!trial || !cost || !tcost || !feat || !tau || !best || !f1 || !t1 || !lab1 ||
       !corr1 || !cost1)
     return MH_ENOMEM;
   DeDev de{P, D, ds->F, prm->G, prm->M, prm->CR, prm->seed, ds->n_unique, true};
   uint32_t *err = (uint32_t *)arena_get(ctx, "ss_err", 256);
   if (!err) return MH_ENOMEM;
   // g = 0: initialise, decode, evaluate
-  s = launch_de_init(ctx, P, D, ds->F, prm->seed, nullptr, prob, 1, warm, W, pop, true);
-  if (s) return s;
+  if (!init_done) {
+    s = launch_de_init(ctx, P, D, ds->F, prm->seed, nullptr, prob, 1, warm, W, pop, true);
+    if (s) return s;
+  }
   bool persisted = false;
   if (es.tiles && ctx->persist) {
     const PersistFinal fin{f1, t1, lab1, corr1, cost1};

@@ -31,6 +31,7 @@ struct Arena {
 };
 
 struct ResultOut;
+struct SmallJob;
 
 struct Ctx {
   int device = 0;
@@ -236,7 +237,11 @@ mh_status seg_radix_pass(Ctx *ctx, const uint64_t *src, uint64_t *dst, uint32_t 
 // subproblem < n_problems.
 mh_status launch_tile_build(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx,
                             const uint32_t *sub_of, uint32_t n_sub, uint32_t n_problems,
-                            void *base, size_t bytes);
+                            void *base, size_t bytes, const SmallJob *init = nullptr);
+// Whether one problem of n_sub samples is planned by one block (small.hip);
+// only then may launch_tile_build be given init: the fields of the initial
+// population to make in the same launch (pop, seed, prob, P, SB).
+bool tiles_small(const mh_dataset *ds, uint32_t n_sub);
 
 // fitness.hip
 struct FitnessOut {

@@ -66,9 +66,11 @@ struct RunArgs {
   uint8_t *out_label;
   uint32_t *out_correct;
   double *out_cost;
+  double *xcost;             // [P] the costs shared out over the blocks (null: every
+                             // block scores all individuals)
   double M, CR, alpha;
   uint64_t seed, prob;
-  uint32_t P, G, n_min, F, K;
+  uint32_t P, G, n_min, F, K, D;
   uint32_t tile0, tile1;     // clipped to the tiles built
   uint32_t sub;              // the run's subproblem in the tile set
   uint32_t blk0, nblk;       // its blocks
@@ -81,16 +83,28 @@ struct RunArgs {
 // the run does not fit the kernel.
 struct RunShape {
   uint32_t nblk = 0, tiles_max = 0, slots = 0, lds = 0;
+  bool split = false;  // costs shared out over the blocks (needs RunArgs::xcost)
 };
-RunShape resident_shape(Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K, uint32_t tiles,
-                        uint32_t max_blocks);
-// Launches the runs of one depth and one population width (P padded to a
-// power of two of waves) together: `runs` on the host, their blocks numbered
-// from 0 (blk0, nblk) and at most one per CU in all.  lds: the largest of
-// their shapes.  runs_dev / map_dev: device room for the runs and the block
-// map (unused for a single run).  Sets *used to false when the launch is
+// resident_shape: the number of blocks (up to max_blocks) expected to be the
+// fastest; resident_fit: nb blocks, if the run fits them.
+RunShape resident_shape(const Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K,
+                        uint32_t tiles, uint32_t max_blocks);
+RunShape resident_fit(const Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K,
+                      uint32_t tiles, uint32_t nb);
+// Launches runs of one depth and one population width (P padded to a power of
+// two of waves) together: `runs` on the host, their blocks numbered from 0
+// (blk0, nblk) and at most one per CU in all.  lds: the largest of their
+// shapes.  runs_dev / map_dev: device room for the runs and the run of each
+// block (unused for a single run).  Sets *used to false when the launch is
 // refused.
-mh_status launch_resident(Ctx *ctx, uint32_t D, const std::vector<RunArgs> &runs, uint32_t lds,
+mh_status launch_resident(Ctx *ctx, const std::vector<RunArgs> &runs, uint32_t lds,
                           RunArgs *runs_dev, uint32_t *map_dev, bool *used);
+// Launches any number of runs of up to P_max <= 128 individuals, of any
+// depths: their n_blocks blocks are numbered from 0 in the order of the runs,
+// none with more than one block per CU; runs_dev and map_dev (the run of each
+// block) on the device; ticket: a device word, zero on entry.
+mh_status launch_resident_queue(Ctx *ctx, uint32_t P_max, uint32_t n_blocks, uint32_t lds,
+                                const RunArgs *runs_dev, const uint32_t *map_dev,
+                                uint32_t *ticket, bool *used);
 
 }  // namespace mh

@@ -906,6 +906,8 @@ mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint
   }
   const size_t cstride = (size_t)SB * K * pad64(P);
   const uint32_t bar_words = barrier_words(cus);
+  double *xcost = (double *)arena_get(ctx, "ps_xcost", (size_t)n_problems * P * 8);
+  if (!xcost) return MH_ENOMEM;
   uint32_t *cnt = (uint32_t *)arena_get(ctx, "ps_cnt", (size_t)n_problems * 3 * cstride * 4);
   uint32_t *bar = (uint32_t *)arena_get(ctx, "ps_bar", (size_t)n_problems * bar_words * 4);
   RunArgs *runs_dev = (RunArgs *)arena_get(ctx, "ps_runs", n_problems * sizeof(RunArgs));
@@ -929,6 +931,7 @@ mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint
     a.out_label = fin ? fin->label : nullptr;
     a.out_correct = fin ? fin->correct : nullptr;
     a.out_cost = fin ? fin->cost : nullptr;
+    a.xcost = sh[i].split ? xcost + (size_t)i * P : nullptr;
     a.M = prm->M;
     a.CR = prm->CR;
     a.alpha = prm->alpha;
@@ -939,6 +942,7 @@ mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint
     a.n_min = prm->n_min;
     a.F = F;
     a.K = K;
+    a.D = D;
     a.tile0 = t0;
     a.tile1 = t0 + tiles_of(i);
     a.sub = i;
@@ -959,7 +963,7 @@ mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint
   hipEvent_t e0 = nullptr, e1 = nullptr;
   const bool timed = prof_pair(ctx, &e0, &e1);
   if (timed) MH_HIP(ctx, hipEventRecord(e0, ctx->stream));
-  s = launch_resident(ctx, D, runs, lds, runs_dev, map_dev, used);
+  s = launch_resident(ctx, runs, lds, runs_dev, map_dev, used);
   if (s) return s;
   if (timed) {
     MH_HIP(ctx, hipEventRecord(e1, ctx->stream));
@@ -981,7 +985,8 @@ mh_status persist_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint3
   if (!ctx->coop || D < 1 || D > 5 || P > 512 || F > 80 || n_problems == 0 ||
       n_problems > 65535)
     return MH_OK;
-  // barrier targets (G + 2) * blocks must fit the 32-bit arrival counters
+  // barrier targets (G + 2) * blocks, up to two barriers per generation, must
+  // fit the 32-bit arrival counters
   if ((uint64_t)(prm->G + 2) * (uint64_t)ctx->num_cu * 8u >= (1ull << 31)) return MH_OK;
   if (ctx->persist_resident) {
     const mh_status rs = resident_run(ctx, tiles, F, K, n_sub, n_eval, n_problems, D, prm, prob,

@@ -27,6 +27,7 @@
 #include "device_common.h"
 #include "grid_sync.h"
 #include "internal.h"
+#include "small.h"
 #include "xcd.h"
 
 namespace mh {
@@ -834,19 +835,37 @@ mh_status launch_rank_encode(Ctx *ctx, const float *X, uint32_t n, uint32_t F, u
   if (!words) return MH_ENOMEM;
   uint32_t *nan_flag = nan_out ? nan_out : words;
   // the cooperative form's barrier words are cleared with the flags
-  const uint32_t R = rank_coop_R(ctx, n, F);
+  // few samples: a block sorts a whole feature in LDS (small.hip).  Its time
+  // grows with n on one CU per feature, the cooperative form's with n F over
+  // all CUs: n = 500, F = 4 10.9 against 28.2 us, n = 5000, F = 30 33.5 against
+  // 43.2, but n = 10^4, F = 16 54.0 against 46.5 and n = 2 10^4, F = 32 99
+  // against 62; at n = 22,528, F = 80 both take 118, F = 200 132 against 276.
+  const bool small = (n <= 6144 || (n <= SMALL_MAX_N && F >= 96)) && ctx->rank_coop &&
+                     !ctx->rank_coop_R;
+  const uint32_t R = small ? 0u : rank_coop_R(ctx, n, F);
   const size_t bar_bytes = R ? (size_t)barrier_words(F * ((n + R - 1) / R)) * 4 : 0;
   uint32_t *bar = R ? (uint32_t *)arena_get(ctx, "re_bar", bar_bytes) : nullptr;
   if (R && !bar) return MH_ENOMEM;
   mh_status zs = launch_zero(ctx, {{words, 8}, {nan_out, nan_out ? 4u : 0u}, {bar, bar_bytes}});
   if (zs) return zs;
   bool done = false;
+  if (small) {
+    SmallJob j{};
+    j.X = X;
+    j.ranks = ranks;
+    j.n_unique = n_unique;
+    j.nan = nan_flag;
+    j.n = n;
+    j.F = F;
+    j.ld = ld;
+    if (mh_status s = launch_prep_small(ctx, {j}, nullptr, PREP_RANK)) return s;
+  }
   if (R) {
     mh_status s =
         rank_encode_coop(ctx, X, n, F, ld, R, ranks, n_unique, nan_flag, words + 1, bar, &done);
     if (s) return s;
   }
-  if (!done) {
+  if (!done && !small) {
     uint64_t *ka = (uint64_t *)arena_get(ctx, "re_keys_a", (size_t)total * 8);
     uint64_t *kb = (uint64_t *)arena_get(ctx, "re_keys_b", (size_t)total * 8);
     const uint32_t nbf = (n + SG_R - 1) / SG_R;

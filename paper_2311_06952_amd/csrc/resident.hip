@@ -48,13 +48,15 @@ constexpr uint32_t RES_THREADS = 1024;
 constexpr uint32_t RES_MAX_TILES = 160;  // info words of a block's tiles
 
 // LDS: rows f64 [2 SB][P] | thresholds u32 [SB][P] | column offsets u16 [SB][P]
-// | counters u32 [SB][slots][P] | per-individual scratch u32 [3][P] | n_unique
+// | counters u32 [SB][slots][P] (or, with split costs, the block's individuals'
+// counts [own][SB][K], own = own_max) | per-individual scratch u32 [3][P] | n_unique
 // [F] | class totals [K] | argmin scratch | info words | tiles.
 struct ResLds {
   uint32_t thr, col, cnt, ind, nu, tot, best, info, tiles, total;
 };
 __host__ __device__ __forceinline__ ResLds res_lds(uint32_t SB, uint32_t P, uint32_t F, uint32_t K,
-                                                   uint32_t slots, uint32_t tiles) {
+                                                   uint32_t slots, uint32_t tiles,
+                                                   uint32_t own_max) {
   ResLds l;
   uint32_t o = align16u(2 * SB * P * 8);
   l.thr = o;
@@ -62,7 +64,8 @@ __host__ __device__ __forceinline__ ResLds res_lds(uint32_t SB, uint32_t P, uint
   l.col = o;
   o += align16u(SB * P * 2);
   l.cnt = o;
-  o += align16u(SB * slots * P * 4);
+  const uint32_t c1 = SB * slots * P, c2 = own_max * SB * K;
+  o += align16u((c1 > c2 ? c1 : c2) * 4);
   l.ind = o;
   o += align16u(3 * P * 4);
   l.nu = o;
@@ -128,10 +131,13 @@ __device__ __forceinline__ uint32_t part_node(uint32_t part, int i) {
   return (((1u << L) + part) << d) + (uint32_t)(s - (1 << d)) - 1u;
 }
 
-template <int D, int WAVES>
-__global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
-    RunArgs one, const RunArgs *__restrict__ runs, const uint32_t *__restrict__ run_of_block,
-    uint64_t wait_ticks) {
+// The arguments are read as scalars where they are used.
+typedef const __attribute__((address_space(4))) RunArgs *ArgPtr;
+
+// SPLIT: whether a run may share out its costs (xcost).
+template <int D, int WAVES, bool SPLIT>
+__device__ __forceinline__ void resident_body(const ArgPtr pa, uint32_t bx, uint64_t wait_ticks,
+                                              uint8_t *lds) {
   constexpr int SB = (1 << D) - 1, m = 2 * SB;
   constexpr uint32_t NTH = WAVES * 64, H = RES_THREADS / NTH;
   constexpr int NA = (SB + H - 1) / H;            // nodes a group mutates
@@ -140,15 +146,8 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
   constexpr int NN = L + (1 << (D - L)) - 1;      // nodes of a counting task
   constexpr uint32_t LN = 1u << (D - 1);          // last-level nodes
   constexpr int XN = (int)((LN + H - 1) / H);     // of them per group
-  extern __shared__ __align__(16) uint8_t lds[];
-  // the arguments are read as scalars where they are used, from the array or
-  // from the kernel's own argument block (its first argument)
-  typedef const __attribute__((address_space(4))) RunArgs *ArgPtr;
-  const ArgPtr pa =
-      runs ? (ArgPtr)(uintptr_t)(runs + __builtin_amdgcn_readfirstlane((int)run_of_block[blockIdx.x]))
-           : (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
   const uint32_t P = pa->P, Ppad = pad64(P), K = pa->K, F = pa->F, slots = pa->slots;
-  const uint32_t b = blockIdx.x - pa->blk0, nb = pa->nblk;
+  const uint32_t b = bx - pa->blk0, nb = pa->nblk;
   // groups are whole waves, so the group index is wave-uniform
   const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / NTH));
   uint32_t r = threadIdx.x % NTH;
@@ -156,6 +155,13 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
   const int n_lo = (int)h * NA < SB ? (int)h * NA : SB;  // this group's nodes
   const int n_hi = n_lo + NA < SB ? n_lo + NA : SB;
   const bool solo = nb == 1;
+  // split costs: the block scores the individuals [i0, i1) alone
+  const bool split = SPLIT && pa->xcost != nullptr;
+  const uint32_t own_max = split ? (P + nb - 1) / nb : 0u;
+  const uint32_t i0 = (uint32_t)((uint64_t)P * b / nb);
+  const uint32_t i1 = (uint32_t)((uint64_t)P * (b + 1) / nb);
+  const uint32_t n_cnt = max(SB * slots * P, own_max * SB * K);  // words of the counters
+  uint32_t bk = 0;  // grid barriers passed
 
   const uint8_t *base = reinterpret_cast<const uint8_t *>(pa->hdr);
   // the range comes from host-side counts; never past the built tiles
@@ -174,7 +180,7 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
     nt = pa->tiles_max;
     if (threadIdx.x == 0) __hip_atomic_store(pa->err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  const ResLds lo = res_lds(SB, P, F, K, slots, pa->tiles_max);
+  const ResLds lo = res_lds(SB, P, F, K, slots, pa->tiles_max, own_max);
   double *rows = reinterpret_cast<double *>(lds);
   uint32_t *x_thr = reinterpret_cast<uint32_t *>(lds + lo.thr);
   uint16_t *x_col = reinterpret_cast<uint16_t *>(lds + lo.col);  // (feature - 1) SCOL
@@ -204,7 +210,7 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
     for (uint32_t i = threadIdx.x; i < nt; i += RES_THREADS) s_info[i] = info[t_begin + i];
     for (uint32_t k = threadIdx.x; k < K; k += RES_THREADS) s_tot[k] = ctot[k];
     for (uint32_t f = threadIdx.x; f < F; f += RES_THREADS) s_nu[f] = pa->n_unique[f];
-    for (uint32_t e = threadIdx.x; e < SB * slots * P; e += RES_THREADS) s_cnt[e] = 0;
+    for (uint32_t e = threadIdx.x; e < n_cnt; e += RES_THREADS) s_cnt[e] = 0;
     for (uint32_t e = threadIdx.x; e < 3 * P; e += RES_THREADS) s_cor[e] = 0;
   }
   uint32_t n_sub = 0;
@@ -247,6 +253,7 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
   const uint32_t part = h % PARTS;
   const uint32_t cls0 = nt ? (s_info[0] >> 8) & 0xFFu : 0u;  // slot of class c: c - cls0
   const bool whole = slots == K;  // a counter for every class: slot = class
+  double *const xcost = pa->xcost;
   const uint32_t cbase = whole ? 0u : cls0;
   // generation G + 1, when the best tree is wanted, counts that tree alone
   const uint32_t g_end = pa->out_label ? pa->G + 1 : pa->G;
@@ -309,14 +316,14 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
             if (v) atomicAdd(cnt + (size_t)y * Ppad + r, v);
           }
       } else if (live) {
-        const uint32_t ce = min(slots, K - cls0);
-        for (uint32_t t = h; t < SB; t += H)
-          for (uint32_t c = 0; c < ce; ++c) {
-            const uint32_t v = s_cnt[(t * slots + c) * P + r];
-            if (v) atomicAdd(cnt + ((size_t)t * K + cls0 + c) * Ppad + r, v);
-          }
+        const uint32_t ce = min(slots, K - cls0), inv = 0xFFFFFFFFu / slots + 1u;
+        for (uint32_t y = h; y < SB * slots; y += H) {
+          const uint32_t t = slots == 1 ? y : __umulhi(y, inv), c = y - t * slots;
+          const uint32_t v = c < ce ? s_cnt[y * P + r] : 0u;
+          if (v) atomicAdd(cnt + ((size_t)t * K + cls0 + c) * Ppad + r, v);
+        }
       }
-      barrier_arrive(pa->bar, g, b, nb);
+      barrier_arrive(pa->bar, bk, b, nb);
     }
 
     // ---- the random draws of generation g + 1 (they depend only on the seed,
@@ -348,7 +355,7 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
         if (to_unit(draw(4u + q)) <= pa->CR || q == qr) cross |= 1u << jj;
       }
     }
-    if (!solo) barrier_wait(pa->bar, g, pa->err, wait_ticks);
+    if (!solo) barrier_wait(pa->bar, bk++, pa->err, wait_ticks);
 
     if (g > pa->G) {
       // ---- the best tree's nodes, leaf classes (the largest count, ties to
@@ -396,89 +403,139 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
       break;
     }
 
-    // ---- costs (eq. opt_all and the soft-constraint fitness): a group scores
-    // its last-level nodes' leaves over all classes, the groups' sums meet in
-    // LDS
-    {
-      uint32_t nl[2 * XN], bl[2 * XN];
-#pragma unroll
-      for (int q = 0; q < 2 * XN; ++q) nl[q] = bl[q] = 0;
-      for (uint32_t k0 = 0; k0 < K; k0 += slots) {
-        const uint32_t kc = min(slots, K - k0);
-        if (!solo) {
-          // counts of classes k0 .. k0 + kc - 1: group h takes the (node,
-          // class) pairs h, h + H, ..., up to 12 loads in flight; a batch's
-          // loads past the last pair repeat it, so that none carries a branch
-          if (k0) __syncthreads();  // the last chunk is scored
-          const uint32_t *src = cnt + (live ? r : 0u), ny = SB * kc;
-          auto batch = [&](uint32_t y0, auto size) {
-            constexpr uint32_t CB = decltype(size)::value;
-            uint32_t v[CB], at[CB];
-#pragma unroll
-            for (uint32_t u = 0; u < CB; ++u) {
-              const uint32_t y = min(y0 + u * H, ny - 1u);
-              at[u] = y;
-              uint32_t m_y = y;  // in memory: [node][K]
-              if (!whole) {
-                const uint32_t t = y / kc, c = y - t * kc;
-                at[u] = t * slots + c;
-                m_y = t * K + k0 + c;
-              }
-              v[u] = __hip_atomic_load(src + (size_t)m_y * Ppad, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < CB; ++u)
-              if (live) s_cnt[at[u] * P + r] = v[u];
-          };
-          uint32_t y0 = h;
-          for (; y0 + 8 * H < ny; y0 += 12 * H) batch(y0, std::integral_constant<uint32_t, 12>{});
-          if (y0 + 4 * H < ny) batch(y0, std::integral_constant<uint32_t, 8>{});
-          else if (y0 + H < ny) batch(y0, std::integral_constant<uint32_t, 4>{});
-          else if (y0 < ny) batch(y0, std::integral_constant<uint32_t, 1>{});
-          __syncthreads();
-        }
-        if (live)
-#pragma unroll 2
-          for (uint32_t kk = 0; kk < kc; ++kk) {
-            const uint32_t tot = s_tot[k0 + kk];
-#pragma unroll
-            for (int q = 0; q < XN; ++q) {
-              const uint32_t x = h + (uint32_t)q * H;
-              if (x >= LN) continue;
-              uint32_t v = tot, node = 1;
-#pragma unroll
-              for (int d = D - 2; d >= 0; --d) {
-                const uint32_t left = s_cnt[((node - 1) * slots + kk) * P + r];
-                const uint32_t bit = (x >> d) & 1u;
-                v = bit ? v - left : left;
-                node = 2 * node + bit;
-              }
-              const uint32_t a = s_cnt[((node - 1) * slots + kk) * P + r], c = v - a;
-              nl[2 * q] += a;
-              nl[2 * q + 1] += c;
-              bl[2 * q] = a > bl[2 * q] ? a : bl[2 * q];
-              bl[2 * q + 1] = c > bl[2 * q + 1] ? c : bl[2 * q + 1];
-            }
-          }
-      }
-      uint32_t cor = 0, vio = 0;
-#pragma unroll
-      for (int q = 0; q < 2 * XN; ++q) {
-        cor += bl[q];
-        vio += (nl[q] > 0 && nl[q] < pa->n_min) ? 1u : 0u;
-      }
-      if (live && h < LN) {
-        atomicAdd(&s_cor[r], cor);
-        if (vio) atomicAdd(&s_vio[r], vio);
-      }
-    }
-    __syncthreads();
+    // ---- costs (eq. opt_all and the soft-constraint fitness)
     double tc = 0.0;
-    if (live) {
-      tc = (double)(n_sub - s_cor[r]);
-      tc = __dadd_rn(tc, __dmul_rn(pa->alpha, (double)s_spl[r]));
-      tc = __dadd_rn(tc, (double)s_vio[r]);
+    if (split) {
+      // The block's own individuals: their counts into LDS (consecutive
+      // threads load consecutive individuals of one counter), a thread per
+      // individual and last-level node, and every cost back through memory
+      // and a second barrier.
+      const uint32_t own = i1 - i0, ny = SB * K;
+      for (uint32_t e = threadIdx.x; e < own * ny; e += RES_THREADS) {
+        const uint32_t y = e / own, i = e - y * own;
+        s_cnt[i * ny + y] = __hip_atomic_load(cnt + (size_t)y * Ppad + i0 + i, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __syncthreads();
+      for (uint32_t e = threadIdx.x; e < own * LN; e += RES_THREADS) {
+        const uint32_t i = e / LN, x = e % LN;
+        const uint32_t *c = s_cnt + i * ny;
+        uint32_t nl0 = 0, nl1 = 0, b0 = 0, b1 = 0;
+#pragma unroll 2
+        for (uint32_t k = 0; k < K; ++k) {
+          uint32_t v = s_tot[k], node = 1;
+#pragma unroll
+          for (int d = D - 2; d >= 0; --d) {
+            const uint32_t left = c[(node - 1) * K + k], bit = (x >> d) & 1u;
+            v = bit ? v - left : left;
+            node = 2 * node + bit;
+          }
+          const uint32_t a = c[(node - 1) * K + k], z = v - a;
+          nl0 += a;
+          nl1 += z;
+          b0 = a > b0 ? a : b0;
+          b1 = z > b1 ? z : b1;
+        }
+        const uint32_t vio = (nl0 > 0 && nl0 < pa->n_min ? 1u : 0u) + (nl1 > 0 && nl1 < pa->n_min ? 1u : 0u);
+        atomicAdd(&s_cor[i0 + i], b0 + b1);
+        if (vio) atomicAdd(&s_vio[i0 + i], vio);
+      }
+      __syncthreads();
+      if (threadIdx.x < own) {
+        const uint32_t i = i0 + threadIdx.x;
+        double v = (double)(n_sub - s_cor[i]);
+        v = __dadd_rn(v, __dmul_rn(pa->alpha, (double)s_spl[i]));
+        v = __dadd_rn(v, (double)s_vio[i]);
+        __hip_atomic_store(xcost + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      barrier_arrive(pa->bar, bk, b, nb);
+      barrier_wait(pa->bar, bk++, pa->err, wait_ticks);
+      if (live) tc = __hip_atomic_load(xcost + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      // a group scores its last-level nodes' leaves over all classes, the
+      // groups' sums meet in LDS
+    {
+        uint32_t nl[2 * XN], bl[2 * XN];
+#pragma unroll
+        for (int q = 0; q < 2 * XN; ++q) nl[q] = bl[q] = 0;
+        for (uint32_t k0 = 0; k0 < K; k0 += slots) {
+          const uint32_t kc = min(slots, K - k0);
+          if (!solo) {
+            // counts of classes k0 .. k0 + kc - 1: group h takes the (node,
+            // class) pairs h, h + H, ..., up to 12 loads in flight; a batch's
+            // loads past the last pair repeat it, so that none carries a branch
+            if (k0) __syncthreads();  // the last chunk is scored
+            const uint32_t *src = cnt + (live ? r : 0u), ny = SB * kc;
+            // y / kc by a reciprocal (exact: y kc < 2^32)
+            const uint32_t inv = 0xFFFFFFFFu / kc + 1u;
+            auto batch = [&](uint32_t y0, auto size) {
+              constexpr uint32_t CB = decltype(size)::value;
+              uint32_t v[CB], at[CB];
+#pragma unroll
+              for (uint32_t u = 0; u < CB; ++u) {
+                const uint32_t y = min(y0 + u * H, ny - 1u);
+                at[u] = y;
+                uint32_t m_y = y;  // in memory: [node][K]
+                if (!whole) {
+                  const uint32_t t = kc == 1 ? y : __umulhi(y, inv), c = y - t * kc;
+                  at[u] = t * slots + c;
+                  m_y = t * K + k0 + c;
+                }
+                v[u] = __hip_atomic_load(src + (size_t)m_y * Ppad, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+              }
+#pragma unroll
+              for (uint32_t u = 0; u < CB; ++u)
+                if (live) s_cnt[at[u] * P + r] = v[u];
+            };
+            uint32_t y0 = h;
+            for (; y0 + 8 * H < ny; y0 += 12 * H) batch(y0, std::integral_constant<uint32_t, 12>{});
+            if (y0 + 4 * H < ny) batch(y0, std::integral_constant<uint32_t, 8>{});
+            else if (y0 + H < ny) batch(y0, std::integral_constant<uint32_t, 4>{});
+            else if (y0 < ny) batch(y0, std::integral_constant<uint32_t, 1>{});
+            __syncthreads();
+          }
+          if (live)
+#pragma unroll 2
+            for (uint32_t kk = 0; kk < kc; ++kk) {
+              const uint32_t tot = s_tot[k0 + kk];
+#pragma unroll
+              for (int q = 0; q < XN; ++q) {
+                const uint32_t x = h + (uint32_t)q * H;
+                if (x >= LN) continue;
+                uint32_t v = tot, node = 1;
+#pragma unroll
+                for (int d = D - 2; d >= 0; --d) {
+                  const uint32_t left = s_cnt[((node - 1) * slots + kk) * P + r];
+                  const uint32_t bit = (x >> d) & 1u;
+                  v = bit ? v - left : left;
+                  node = 2 * node + bit;
+                }
+                const uint32_t a = s_cnt[((node - 1) * slots + kk) * P + r], c = v - a;
+                nl[2 * q] += a;
+                nl[2 * q + 1] += c;
+                bl[2 * q] = a > bl[2 * q] ? a : bl[2 * q];
+                bl[2 * q + 1] = c > bl[2 * q + 1] ? c : bl[2 * q + 1];
+              }
+            }
+        }
+        uint32_t cor = 0, vio = 0;
+#pragma unroll
+        for (int q = 0; q < 2 * XN; ++q) {
+          cor += bl[q];
+          vio += (nl[q] > 0 && nl[q] < pa->n_min) ? 1u : 0u;
+        }
+        if (live && h < LN) {
+          atomicAdd(&s_cor[r], cor);
+          if (vio) atomicAdd(&s_vio[r], vio);
+        }
+      }
+      __syncthreads();
+      if (live) {
+        tc = (double)(n_sub - s_cor[r]);
+        tc = __dadd_rn(tc, __dmul_rn(pa->alpha, (double)s_spl[r]));
+        tc = __dadd_rn(tc, (double)s_vio[r]);
+      }
     }
     // ---- selection (eq. selection; the trial wins ties), or the initial cost
     if (g == 0) {
@@ -506,7 +563,7 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
         s_bi[threadIdx.x >> 6] = bi;
       }
     }
-    for (uint32_t e = threadIdx.x; e < SB * slots * P; e += RES_THREADS) s_cnt[e] = 0;
+    for (uint32_t e = threadIdx.x; e < n_cnt; e += RES_THREADS) s_cnt[e] = 0;
     __syncthreads();
     for (uint32_t e = threadIdx.x; e < 3 * P; e += RES_THREADS) s_cor[e] = 0;
     double bc = s_bc[0];
@@ -566,14 +623,59 @@ __global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
   }
 }
 
+// Block bx's run: from the array, or the kernel's own first argument.
+__device__ __forceinline__ ArgPtr run_args(const RunArgs *runs, const uint32_t *run_of_block,
+                                           uint32_t bx) {
+  return runs ? (ArgPtr)(uintptr_t)(runs + __builtin_amdgcn_readfirstlane((int)run_of_block[bx]))
+              : (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+template <int D, int WAVES, bool SPLIT>
+__global__ __launch_bounds__(RES_THREADS) void k_deoct_resident(
+    RunArgs one, const RunArgs *__restrict__ runs, const uint32_t *__restrict__ run_of_block,
+    uint64_t wait_ticks) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  resident_body<D, WAVES, SPLIT>(run_args(runs, run_of_block, blockIdx.x), blockIdx.x, wait_ticks, lds);
+}
+
+// Runs of different depths, more of them than the CUs hold at once: the runs'
+// blocks are numbered in order, and a block of the launch takes the next
+// number whenever it is free.  A run's blocks so start in order, and every
+// block with a lower number has started: only the last run started can still
+// wait at its barrier for members, and these come as earlier runs, all of whose
+// blocks are running, end.
+template <int WAVES>
+__global__ __launch_bounds__(RES_THREADS) void k_deoct_resident_queue(
+    const RunArgs *__restrict__ runs, const uint32_t *__restrict__ run_of_block,
+    uint32_t n_blocks, uint32_t *__restrict__ ticket, uint64_t wait_ticks) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  __shared__ uint32_t s_next;
+  for (;;) {
+    if (threadIdx.x == 0) s_next = atomicAdd(ticket, 1u);
+    __syncthreads();
+    const uint32_t bx = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next);
+    if (bx >= n_blocks) return;
+    const ArgPtr pa = run_args(runs, run_of_block, bx);
+    switch (pa->D) {
+      case 1: resident_body<1, WAVES, true>(pa, bx, wait_ticks, lds); break;
+      case 2: resident_body<2, WAVES, true>(pa, bx, wait_ticks, lds); break;
+      case 3: resident_body<3, WAVES, true>(pa, bx, wait_ticks, lds); break;
+      case 4: resident_body<4, WAVES, true>(pa, bx, wait_ticks, lds); break;
+      default: resident_body<5, WAVES, true>(pa, bx, wait_ticks, lds); break;
+    }
+    __syncthreads();  // the LDS and s_next are free again
+  }
+}
+
+template <bool SPLIT>
 const void *resident_kernel(uint32_t D, uint32_t waves) {
 #define MH_RES(DD)                                                                     \
   case DD:                                                                             \
     switch (waves) {                                                                   \
-      case 1: return reinterpret_cast<const void *>(k_deoct_resident<DD, 1>);          \
-      case 2: return reinterpret_cast<const void *>(k_deoct_resident<DD, 2>);          \
-      case 4: return reinterpret_cast<const void *>(k_deoct_resident<DD, 4>);          \
-      default: return reinterpret_cast<const void *>(k_deoct_resident<DD, 8>);         \
+      case 1: return reinterpret_cast<const void *>(k_deoct_resident<DD, 1, SPLIT>);   \
+      case 2: return reinterpret_cast<const void *>(k_deoct_resident<DD, 2, SPLIT>);   \
+      case 4: return reinterpret_cast<const void *>(k_deoct_resident<DD, 4, SPLIT>);   \
+      default: return reinterpret_cast<const void *>(k_deoct_resident<DD, 8, SPLIT>);  \
     }
   switch (D) {
     MH_RES(1)
@@ -582,9 +684,9 @@ const void *resident_kernel(uint32_t D, uint32_t waves) {
     MH_RES(4)
     case 5:  // (at depth 5 more than 256 individuals do not fit the LDS)
       switch (waves) {
-        case 1: return reinterpret_cast<const void *>(k_deoct_resident<5, 1>);
-        case 2: return reinterpret_cast<const void *>(k_deoct_resident<5, 2>);
-        case 4: return reinterpret_cast<const void *>(k_deoct_resident<5, 4>);
+        case 1: return reinterpret_cast<const void *>(k_deoct_resident<5, 1, SPLIT>);
+        case 2: return reinterpret_cast<const void *>(k_deoct_resident<5, 2, SPLIT>);
+        case 4: return reinterpret_cast<const void *>(k_deoct_resident<5, 4, SPLIT>);
       }
   }
 #undef MH_RES
@@ -598,34 +700,53 @@ uint32_t waves_of(uint32_t P) {
 
 }  // namespace
 
-RunShape resident_shape(Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K, uint32_t tiles,
-                        uint32_t max_blocks) {
+// Whether the blocks of a run share out the costs.  Every block reading all P
+// SB K counts takes one batch of 12 loads per thread and group; past that, each
+// block scores its own individuals and a second barrier (about 3,500 cycles)
+// brings the costs back, with counters only for the classes of the block's own
+// tiles.  Measured, cycles of a generation: n = 10^4, F = 20, K = 10, depth 4, P
+// = 128 on 34 blocks 36,900 -> 29,300, on 85 blocks 29,300 -> 25,200; n = 3
+// 10^4, F = 13, K = 5, depth 5, P = 100 on 256 blocks 39,500 -> 35,800.
+bool split_costs(uint32_t P, uint32_t SB, uint32_t K, uint32_t nb) {
+  return nb > 1 && SB * K > 12u * (RES_THREADS / (waves_of(P) * 64));
+}
+
+RunShape resident_fit(const Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K,
+                      uint32_t tiles, uint32_t nb) {
+  RunShape r;
+  if (!ctx->coop || D < 1 || D > 5 || P > 512 || F > 80 || nb == 0) return r;
+  if (!resident_kernel<false>(D, waves_of(P))) return r;
+  const uint32_t SB = (1u << D) - 1u, max_lds = ctx->max_lds - 2048;  // (coop_per_cu's margin)
+  const uint32_t tm = (std::max(tiles, 1u) + nb - 1) / nb;
+  if (tm > RES_MAX_TILES) return r;
+  // class counters: as many as fit (a block's counts of the classes past them
+  // add to memory, and the costs take the classes in chunks of them); all for
+  // one block
+  const bool split = split_costs(P, SB, K, nb);
+  const uint32_t own = split ? (P + nb - 1) / nb : 0u;
+  uint32_t slots = split ? std::min(K, tm) : K;
+  while (nb > 1 && slots > 1 && res_lds(SB, P, F, K, slots, tm, own).total > max_lds) --slots;
+  const uint32_t lds = res_lds(SB, P, F, K, slots, tm, own).total;
+  if (lds <= max_lds) r = RunShape{nb, tm, slots, lds, split};
+  return r;
+}
+
+RunShape resident_shape(const Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K,
+                        uint32_t tiles, uint32_t max_blocks) {
   RunShape best;
-  if (!ctx->coop || D < 1 || D > 5 || P > 512 || F > 80 || max_blocks == 0) return best;
   const uint32_t waves = waves_of(P), H = RES_THREADS / (waves * 64), SB = (1u << D) - 1u;
-  if (!resident_kernel(D, waves)) return best;
-  const uint32_t parts = D < 4 ? 1u : (D == 5 && H >= 4 ? 4u : 2u);
-  const uint32_t max_lds = ctx->max_lds - 2048;  // (the margin of coop_per_cu)
-  tiles = std::max(tiles, 1u);
   double best_t = 1e300;
   auto consider = [&](uint32_t nb) {
-    const uint32_t tm = (tiles + nb - 1) / nb;
-    if (tm > RES_MAX_TILES) return;
-    // class counters: as many as fit (a block's counts of the classes past them
-    // add to memory, and the costs take the classes in chunks of them); all
-    // for one block
-    uint32_t slots = K;
-    while (nb > 1 && slots > 1 && res_lds(SB, P, F, K, slots, tm).total > max_lds) --slots;
-    const uint32_t lds = res_lds(SB, P, F, K, slots, tm).total;
-    if (lds > max_lds) return;
+    const RunShape r = resident_fit(ctx, D, P, F, K, tiles, nb);
+    if (!r.nblk) return;
     // cycles of a generation that depend on nb: the block's searches (a CU's
     // LDS serves a wave's search in about 33 cycles), and the exchange
-    const double nodes = D < 4 ? SB : (parts == 4 ? 36 : (D == 4 ? 16 : 32));
-    const double t = tm * waves * nodes * 33.0 + (nb > 1 ? 9000.0 + 12.0 * nb : 0.0) +
-                     (slots < K ? 8000.0 : 0.0);
+    const double nodes = D < 4 ? SB : (D == 4 ? 16 : (H >= 4 ? 36 : 32));
+    const double t = r.tiles_max * waves * nodes * 33.0 + (nb > 1 ? 9000.0 + 12.0 * nb : 0.0) +
+                     (!r.split && r.slots < K ? 8000.0 : 0.0);
     if (ctx->resident_blocks ? nb == ctx->resident_blocks : t < best_t) {
       best_t = t;
-      best = RunShape{nb, tm, slots, lds};
+      best = r;
     }
   };
   // Several blocks only where the groups are many: up to 128 individuals (eight
@@ -642,7 +763,7 @@ RunShape resident_shape(Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K
   return best;
 }
 
-mh_status launch_resident(Ctx *ctx, uint32_t D, const std::vector<RunArgs> &runs, uint32_t lds,
+mh_status launch_resident(Ctx *ctx, const std::vector<RunArgs> &runs, uint32_t lds,
                           RunArgs *runs_dev, uint32_t *map_dev, bool *used) {
   *used = false;
   uint32_t grid = 0, Pmax = 0;
@@ -650,7 +771,10 @@ mh_status launch_resident(Ctx *ctx, uint32_t D, const std::vector<RunArgs> &runs
     grid += r.nblk;
     Pmax = std::max(Pmax, r.P);
   }
-  const void *kern = resident_kernel(D, waves_of(Pmax));
+  const uint32_t D = runs[0].D, waves = waves_of(Pmax);
+  bool split = false;
+  for (const RunArgs &r : runs) split = split || r.xcost;
+  const void *kern = split ? resident_kernel<true>(D, waves) : resident_kernel<false>(D, waves);
   if (!kern || grid == 0 || grid > (uint32_t)ctx->num_cu) return MH_OK;
   if (coop_per_cu(ctx, kern, RES_THREADS, lds) < 1 || coop_is_bad(ctx, kern, grid)) return MH_OK;
   RunArgs one = runs[0];
@@ -670,7 +794,7 @@ mh_status launch_resident(Ctx *ctx, uint32_t D, const std::vector<RunArgs> &runs
   uint64_t ticks = ctx->wait_ticks;
   if (ctx->debug)
     std::fprintf(stderr, "k_deoct_resident<%u,%u>: %zu runs, grid %u, tiles %u per block, %u class slots, LDS %u bytes\n",
-                 D, waves_of(Pmax), runs.size(), grid, one.tiles_max, one.slots, lds);
+                 D, waves, runs.size(), grid, one.tiles_max, one.slots, lds);
   void *args[] = {&one, &rd, &md, &ticks};
   const hipError_t e = launch_grid_sync(ctx, kern, dim3(grid), dim3(RES_THREADS), args, lds);
   if (e == hipErrorInvalidValue || e == hipErrorCooperativeLaunchTooLarge ||
@@ -679,6 +803,35 @@ mh_status launch_resident(Ctx *ctx, uint32_t D, const std::vector<RunArgs> &runs
     return MH_OK;
   }
   if (e != hipSuccess) return hip_fail(ctx, e, "k_deoct_resident");
+  ctx->last_coop_kern = kern;
+  ctx->last_coop_grid = grid;
+  *used = true;
+  return MH_OK;
+}
+
+mh_status launch_resident_queue(Ctx *ctx, uint32_t P_max, uint32_t n_blocks, uint32_t lds,
+                                const RunArgs *runs_dev, const uint32_t *map_dev,
+                                uint32_t *ticket, bool *used) {
+  *used = false;
+  const uint32_t waves = waves_of(P_max);
+  const void *kern = waves == 1   ? reinterpret_cast<const void *>(k_deoct_resident_queue<1>)
+                     : waves == 2 ? reinterpret_cast<const void *>(k_deoct_resident_queue<2>)
+                                  : nullptr;
+  const uint32_t grid = std::min(n_blocks, (uint32_t)ctx->num_cu);
+  if (!kern || grid == 0) return MH_OK;
+  if (coop_per_cu(ctx, kern, RES_THREADS, lds) < 1 || coop_is_bad(ctx, kern, grid)) return MH_OK;
+  uint64_t ticks = ctx->wait_ticks;
+  if (ctx->debug)
+    std::fprintf(stderr, "k_deoct_resident_queue<%u>: %u blocks of work, grid %u, LDS %u bytes\n",
+                 waves, n_blocks, grid, lds);
+  void *args[] = {&runs_dev, &map_dev, &n_blocks, &ticket, &ticks};
+  const hipError_t e = launch_grid_sync(ctx, kern, dim3(grid), dim3(RES_THREADS), args, lds);
+  if (e == hipErrorInvalidValue || e == hipErrorCooperativeLaunchTooLarge ||
+      e == hipErrorInvalidConfiguration) {
+    (void)hipGetLastError();
+    return MH_OK;
+  }
+  if (e != hipSuccess) return hip_fail(ctx, e, "k_deoct_resident_queue");
   ctx->last_coop_kern = kern;
   ctx->last_coop_grid = grid;
   *used = true;
