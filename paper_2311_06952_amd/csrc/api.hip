@@ -553,9 +553,6 @@ mh_status mh_ctx_create(int device, void *hip_stream, mh_ctx **out) {
     c->c.resident_blocks = (uint32_t)std::max(0, atoi(v));
   if (const char *v = std::getenv("MHDEOCT_RANK_COOP")) c->c.rank_coop = atoi(v) != 0;
   if (const char *v = std::getenv("MHDEOCT_DEBUG")) c->c.debug = atoi(v) != 0;
-  if (const char *v = std::getenv("MHDEOCT_WALK_IT")) c->c.walk_it = (uint32_t)std::max(0, atoi(v));
-  if (const char *v = std::getenv("MHDEOCT_WALK_LDS"))
-    c->c.walk_lds = atoi(v) > 0 ? (size_t)std::min(std::max(atoi(v), 8192), 150 * 1024) : 0;
   if (const char *v = std::getenv("MHDEOCT_SELECT_TPI")) {
     const int t = atoi(v);
     c->c.de_select_tpi = (t == 1 || t == 2 || t == 4 || t == 8) ? (uint32_t)t : 0u;

@@ -300,189 +300,298 @@ __device__ __forceinline__ void leaf_epilogue_tree(uint32_t *__restrict__ leafcn
 }
 
 // ---------------------------------------------------------------------------
-// Walk kernel (any depth): lane = sample.  A block owns a range of samples
-// and a group of up to TG trees.  It stages its samples tile by tile in LDS
-// (every rank column and the labels, coalesced 16-byte loads), then walks
-// each tile through every tree of its group (Algorithm 1: t <- 2t if
-// rank < tau else 2t + 1, D steps), adding one to the (tree, leaf, class)
-// histogram in LDS; each tile is read from memory once for the whole group.
-// A node is one 64-bit LDS word: tau above, and below the byte offset of its
-// rank column in the tile (a no-split node reads column 0 with tau = 0, so
-// every sample goes right).  A walk keeps the LDS address of its current
-// node and advances it directly (node t at base + 8 (t - 1), so that child
-// 2t + b sits at 2 addr - base + 8 + 8b).  With the tile in LDS as [F][T],
-// lane i reads word f * T + i whatever feature its node splits on, so the
-// rank reads of a wave never conflict.  Each thread walks GI trees at once
-// (independent chains of dependent LDS reads).  The histogram goes to memory
-// once per block (global atomics directly when it does not fit).  With many
-// features (a tile of 256 samples over 48 KiB) only the labels are staged
-// and the ranks are read from memory at each step (the node then holds the
-// column index).
+// Walk kernel (any depth): lane = sample.  A block owns a range of samples and
+// a group of TG trees.  It stages its samples T at a time in LDS, every rank
+// column and the labels, and walks them through its trees (Algorithm 1: t <-
+// 2t if rank < tau else 2t + 1, D steps), adding to the (tree, leaf, class)
+// histogram in LDS, which goes to memory once per block (global adds directly
+// where it does not fit).  The block's 1,024 threads are NG = 1024 / T sets of
+// T lanes; set s walks every sample through the trees s GI .. s GI + GI - 1,
+// then + NG GI, ..., GI independent chains of dependent LDS reads per lane.
+//
+// The LDS pipe bounds it (a read that no bank conflict slows takes a CU 2.7
+// cycles per wave, one of 64 random words 4.4, of 128 5.9), and next the
+// vector unit.  A node is one LDS word, tau << 8 | 2 column, and a staged rank
+// is rank << 8 | 2 column, so that the comparison needs no unpacking: per step
+// a read of the node, a byte product for the rank's address (columns of 64
+// samples are 256 bytes; from 129 features on, whose doubled column passes a
+// byte, a mask and a shift), its read, a compare, a select and a shift-add
+// for the child's address (node t at base + 4 (t - 1): child 2t + b at 2 addr
+// - base + 4 + 4 b).  The nodes of a level are consecutive words, and lane i
+// reads word i of a column whatever column its node names, so the rank reads
+// never conflict.  That takes ranks and thresholds below 2^24 - 1; larger ones
+// (WIDE, from that many samples on) use 64-bit nodes and plain ranks.  The
+// next tile's chunks are loaded into registers while the current one is
+// walked.
+//
+// Measured per launch, against 256-thread blocks of up to 32 64-bit-node trees
+// without prefetch: depth 8, n = 10^5, F = 16, P = 100: 40.9 -> 37.2 us;
+// depth 6, n = 2 10^5, F = 100, P = 64 (ranks read from memory at every step
+// before): 810 -> 55 us.
 // ---------------------------------------------------------------------------
-constexpr uint32_t WT_THREADS = 256;
+constexpr uint32_t WT_THREADS = 1024;
+constexpr uint32_t WT_NPF = 8;  // 16-byte chunks of the next tile per thread
+constexpr uint32_t WT_RANK_MAX = 0xFFFFFFu;
 
 struct WalkArgs {
   const uint32_t *ranks;
   uint32_t ld;
   const uint8_t *labels;
-  const uint32_t *idx;
+  const uint32_t *idx;     // the samples (null: 0 .. n_sub - 1)
+  const uint32_t *weight;  // times each sample counts (null: once)
+  const uint32_t *n_unique;
   uint32_t n_sub, n;
   const uint8_t *feat;
   const uint32_t *tau;
   uint32_t P, D, F, K;
-  uint32_t T;       // samples per tile (a multiple of WT_THREADS)
   uint32_t TG;      // trees per block
-  uint32_t ranges;  // sample ranges (gridDim.x)
+  uint32_t per;     // samples per block (gridDim.x ranges), a multiple of 64
   uint32_t hist_in_lds;
   uint32_t vec4;  // rank columns readable as 16-byte chunks (aligned, ld % 4 == 0)
   uint32_t *leafcnt;  // [P][2^D][K]
 };
 
-template <int IT, int GI, bool STAGED>
+// The sample at position j of the evaluation: its index, class (0xFF: left
+// out) and weight.
+__device__ __forceinline__ uint32_t walk_label(const WalkArgs &a, uint32_t j, uint32_t &i,
+                                               uint32_t &w) {
+  i = a.idx ? a.idx[j] : j;
+  w = 1;
+  if (i >= a.n) return 0xFFu;
+  if (a.weight) w = a.weight[i];
+  const uint32_t y = a.labels[i];
+  return y < a.K && w ? y : 0xFFu;
+}
+
+// The block's share straight from memory: for a data set whose ranks do not
+// fit the packed words although its sample count promised it (columns cut out
+// of a larger encoding).
+__device__ __forceinline__ void walk_plain(const WalkArgs &a, uint32_t r0, uint32_t tg, uint32_t s0,
+                                        uint32_t s1) {
+  const uint32_t SB = (1u << a.D) - 1u, SL = 1u << a.D;
+  for (uint32_t j = s0 + threadIdx.x; j < s1; j += WT_THREADS) {
+    uint32_t i, w;
+    const uint32_t y = walk_label(a, j, i, w);
+    if (y == 0xFFu) continue;
+    for (uint32_t g = 0; g < tg; ++g) {
+      const size_t tr = (size_t)(r0 + g) * SB;
+      uint32_t t = 1;
+      for (uint32_t d = 0; d < a.D; ++d) {
+        const uint32_t f = a.feat[tr + t - 1];
+        const bool left = f != 0 && f <= a.F && a.ranks[(size_t)(f - 1) * a.ld + i] < a.tau[tr + t - 1];
+        t = left ? 2 * t : 2 * t + 1;
+      }
+      atomicAdd(&a.leafcnt[((size_t)(r0 + g) * SL + (t - SL)) * a.K + y], w);
+    }
+  }
+}
+
+template <uint32_t T, int GI, bool WIDE>
 __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
   extern __shared__ __align__(16) uint32_t wl[];
-  const uint32_t SB = (1u << a.D) - 1u, SL = 1u << a.D, T = a.T, K = a.K;
-  const uint32_t FT = STAGED ? a.F * T : 0u;
-  uint32_t *tile = wl;                                   // [F][T] when staged
-  uint8_t *ylab = reinterpret_cast<uint8_t *>(wl + FT);  // [T]
-  uint64_t *nodes = reinterpret_cast<uint64_t *>(wl + FT + T / 4);  // [TG][SB]
-  uint32_t *hist = reinterpret_cast<uint32_t *>(nodes + (size_t)a.TG * SB);  // [TG][SL][K]
+  __shared__ uint32_t s_wide;
+  constexpr uint32_t NG = WT_THREADS / T, NW = WIDE ? 8u : 4u;  // bytes of a node
+  // the column is held shifted left by FS
+  constexpr uint32_t FS = T > 128 ? 1 : 0;
+  const uint32_t SB = (1u << a.D) - 1u, SL = 1u << a.D, K = a.K, F = a.F;
+  uint32_t *tile = wl;                                           // [T / 64][F][64]
+  uint32_t *wgt = wl + F * T;                                    // [T] weights
+  uint8_t *ylab = reinterpret_cast<uint8_t *>(wgt + T);          // [T]
+  uint32_t *nodes = wgt + T + T / 4;                             // [TG][SB] words of NW bytes
+  uint32_t *hist = nodes + ((a.TG * SB * (NW / 4) + 1u) & ~1u);  // [TG][SL][K]
   // absolute LDS byte addresses
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint32_t *)wl);
-  const uint32_t node0 = lds0 + 4u * (FT + T / 4);
+  const uint32_t node0 = lds0 + 4u * (F * T + T + T / 4);
+  const uint32_t hist0 = lds0 + 4u * (uint32_t)(hist - wl);
   const uint32_t r0 = blockIdx.y * a.TG;
   const uint32_t tg = min(a.TG, a.P - r0);
+  // the block's sample range (a multiple of 64, so that every tile starts at
+  // a multiple of 4 samples for the 16-byte loads)
+  const uint32_t s0 = min(a.n_sub, blockIdx.x * a.per), s1 = min(a.n_sub, s0 + a.per);
+  if (!WIDE) {
+    if (threadIdx.x == 0) s_wide = 0;
+    __syncthreads();
+    for (uint32_t f = threadIdx.x; f < F; f += WT_THREADS)
+      if (a.n_unique[f] >= WT_RANK_MAX) s_wide = 1;
+    __syncthreads();
+    if (s_wide) {
+      walk_plain(a, r0, tg, s0, s1);
+      return;
+    }
+  }
+  const uint32_t i = threadIdx.x & (T - 1u);
+  const uint32_t set = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / T));
+  // the sample's rank in column 0; column f is 256 f bytes on
+  const uint32_t lane_off = lds0 + 4u * (i % 64u) + 256u * F * (i / 64u);
+  constexpr uint32_t T4 = T / 4;
+  const uint32_t nch = F * T4;
+  uint4 pf[WT_NPF];
+  const bool chunked = !a.idx && a.vec4;  // (from four samples on)
+  // the thread's number, opaque: what follows from it is worked out in place
+  // rather than kept in registers across the walk
+  auto thread = [] {
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+  };
+  // Loads without a branch (a skipped one would make each of the next wait
+  // for those before it): columns and samples past the end come as the last
+  // whole chunk, and the last samples of a ragged column when it is stored.
+  const uint32_t j_last = (a.n - 4u) & ~3u;
+  auto prefetch = [&](uint32_t base) {
+    const uint32_t tid = thread();
+#pragma unroll
+    for (uint32_t k = 0; k < WT_NPF; ++k) {
+      if (k * WT_THREADS >= nch) break;
+      const uint32_t c = min(k * WT_THREADS + tid, nch - 1u), j = min(base + 4u * (c % T4), j_last);
+      pf[k] = *reinterpret_cast<const uint4 *>(a.ranks + (size_t)(c / T4) * a.ld + j);
+    }
+  };
+  auto word = [&](uint32_t rank, uint32_t f) {
+    return WIDE ? rank : (min(rank, WT_RANK_MAX) << 8) | (f << FS);
+  };
+  if (chunked) prefetch(s0);
   // this block's trees: nodes into LDS, histogram cleared
   for (uint32_t e = threadIdx.x; e < tg * SB; e += WT_THREADS) {
-    const uint32_t g = e / SB, t = e % SB;
-    uint32_t f = a.feat[(size_t)(r0 + g) * SB + t];
-    f = f <= a.F ? f : 0u;
-    const uint32_t th = f ? a.tau[(size_t)(r0 + g) * SB + t] : 0u;
-    const uint32_t col = f ? f - 1u : 0u;
-    nodes[e] = ((uint64_t)th << 32) | (STAGED ? col * T * 4u : col);
+    const uint32_t f = a.feat[(size_t)r0 * SB + e], t = a.tau[(size_t)r0 * SB + e];
+    const bool split = f != 0 && f <= F;
+    const uint32_t th = split ? t : 0u, col = split ? f - 1u : 0u;
+    if constexpr (WIDE)
+      reinterpret_cast<uint64_t *>(nodes)[e] = ((uint64_t)th << 32) | (col << 8);
+    else
+      nodes[e] = (min(th, WT_RANK_MAX) << 8) | (col << FS);
   }
   if (a.hist_in_lds)
     for (uint32_t e = threadIdx.x; e < tg * SL * K; e += WT_THREADS) hist[e] = 0;
-  // the block's sample range, in tiles (a whole number of tiles, so that
-  // every tile starts at a multiple of 4 samples for the 16-byte loads)
-  const uint32_t per = ((a.n_sub + a.ranges - 1) / a.ranges + T - 1) / T * T;
-  const uint32_t s0 = blockIdx.x * per, s1 = min(a.n_sub, s0 + per);
   for (uint32_t base = s0; base < s1; base += T) {
     const uint32_t cnt = min(T, s1 - base);
     __syncthreads();  // the previous tile (and the node set-up) is done
-    for (uint32_t i = threadIdx.x; i < T; i += WT_THREADS) {
-      uint32_t y = 0xFFu;
-      if (i < cnt) {
-        const uint32_t smp = a.idx ? a.idx[base + i] : base + i;
-        if (smp < a.n && a.labels[smp] < K) y = a.labels[smp];  // invalid samples are left out
-      }
-      ylab[i] = (uint8_t)y;
+    if (threadIdx.x < T) {
+      // a sample that is left out counts 0 times, in class 0
+      uint32_t y = 0xFFu, w = 0, smp;
+      if (threadIdx.x < cnt) y = walk_label(a, base + threadIdx.x, smp, w);
+      ylab[threadIdx.x] = y == 0xFFu ? (uint8_t)0 : (uint8_t)y;
+      wgt[threadIdx.x] = y == 0xFFu ? 0u : w;
     }
-    // the tile's ranks, SG loads in flight per thread before their stores
-    constexpr uint32_t SG = 8;
-    if (!STAGED) {
-    } else if (a.idx) {
-      for (uint32_t e0 = threadIdx.x; e0 < a.F * T; e0 += SG * WT_THREADS) {
+    const uint32_t tid = thread();
+    if (chunked) {
+      uint4 *tile4 = reinterpret_cast<uint4 *>(tile);
+#pragma unroll
+      for (uint32_t k = 0; k < WT_NPF; ++k) {
+        const uint32_t c = k * WT_THREADS + tid, f = c / T4, q = c % T4;
+        if (c >= nch) continue;
+        if (const uint32_t j = base + 4u * q; j < s1 && j > j_last) {
+          const uint32_t *p = a.ranks + (size_t)f * a.ld + j;
+          pf[k] = make_uint4(p[0], j + 1u < s1 ? p[1] : 0u, j + 2u < s1 ? p[2] : 0u, 0u);
+        }
+        tile4[((q / 16u) * F + f) * 16u + q % 16u] =
+            make_uint4(word(pf[k].x, f), word(pf[k].y, f), word(pf[k].z, f), word(pf[k].w, f));
+      }
+    } else {
+      // SG loads in flight per thread before their stores
+      constexpr uint32_t SG = 8;
+      for (uint32_t e0 = tid; e0 < F * T; e0 += SG * WT_THREADS) {
         uint32_t v[SG];
 #pragma unroll
         for (uint32_t u = 0; u < SG; ++u) {
-          const uint32_t e = e0 + u * WT_THREADS, f = e / T, i = e % T;
+          const uint32_t e = e0 + u * WT_THREADS, f = e / T, q = e % T;
           v[u] = 0;
-          if (e < a.F * T && i < cnt) {
-            const uint32_t smp = a.idx[base + i];
+          if (e < F * T && q < cnt) {
+            const uint32_t smp = a.idx ? a.idx[base + q] : base + q;
             if (smp < a.n) v[u] = a.ranks[(size_t)f * a.ld + smp];
           }
         }
 #pragma unroll
-        for (uint32_t u = 0; u < SG; ++u)
-          if (e0 + u * WT_THREADS < a.F * T) tile[e0 + u * WT_THREADS] = v[u];
-      }
-    } else if (a.vec4 && cnt == T) {
-      // whole tile, 16-byte chunks: chunk c is ranks 4i..4i+3 of column f
-      const uint32_t T4 = T / 4, nch = a.F * T4;
-      uint4 *tile4 = reinterpret_cast<uint4 *>(tile);
-      for (uint32_t c0 = threadIdx.x; c0 < nch; c0 += SG * WT_THREADS) {
-        uint4 v[SG];
-#pragma unroll
         for (uint32_t u = 0; u < SG; ++u) {
-          const uint32_t c = c0 + u * WT_THREADS;
-          v[u] = make_uint4(0u, 0u, 0u, 0u);
-          if (c < nch)
-            v[u] = *reinterpret_cast<const uint4 *>(a.ranks + (size_t)(c / T4) * a.ld + base +
-                                                    4u * (c % T4));
+          const uint32_t e = e0 + u * WT_THREADS, f = e / T, q = e % T;
+          if (e < F * T) tile[((q / 64u) * F + f) * 64u + q % 64u] = word(v[u], f);
         }
-#pragma unroll
-        for (uint32_t u = 0; u < SG; ++u)
-          if (c0 + u * WT_THREADS < nch) tile4[c0 + u * WT_THREADS] = v[u];
-      }
-    } else {
-      for (uint32_t e0 = threadIdx.x; e0 < a.F * T; e0 += SG * WT_THREADS) {
-        uint32_t v[SG];
-#pragma unroll
-        for (uint32_t u = 0; u < SG; ++u) {
-          const uint32_t e = e0 + u * WT_THREADS, f = e / T, i = e % T;
-          v[u] = (e < a.F * T && i < cnt) ? a.ranks[(size_t)f * a.ld + base + i] : 0u;
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < SG; ++u)
-          if (e0 + u * WT_THREADS < a.F * T) tile[e0 + u * WT_THREADS] = v[u];
       }
     }
     __syncthreads();
-    uint32_t yk[IT], sk[IT], lane_off[IT];
-#pragma unroll
-    for (int k = 0; k < IT; ++k) {
-      const uint32_t i = threadIdx.x + k * WT_THREADS;
-      yk[k] = ylab[i];
-      lane_off[k] = lds0 + 4u * i;  // the sample's rank in column 0
-      // (unstaged ranks: the sample itself; in range whenever its label is valid)
-      sk[k] = (!STAGED && yk[k] != 0xFFu) ? (a.idx ? a.idx[base + i] : base + i) : 0u;
-    }
-    // GI trees at a time; a group past the last tree repeats the last one
-    // and leaves its count out
-    for (uint32_t g0 = 0; g0 < tg; g0 += GI) {
-      uint32_t nb[GI], na[GI][IT];
+    if (chunked && base + T < s1) prefetch(base + T);
+    const uint32_t y = ylab[i], w = wgt[i];
+    if (__ballot(w != 0u) == 0ull) continue;  // (uniform over the wave; no barrier inside)
+    const uint32_t y4 = hist0 + 4u * y;
+    // GI trees at a time; a batch past the last tree repeats the last one and
+    // leaves its count out
+    for (uint32_t g0 = set * GI; g0 < tg; g0 += NG * GI) {
+      uint32_t na[GI], cl[GI], cr[GI];
 #pragma unroll
       for (int gg = 0; gg < GI; ++gg) {
-        nb[gg] = node0 + 8u * SB * min(g0 + gg, tg - 1);
-#pragma unroll
-        for (int k = 0; k < IT; ++k) na[gg][k] = nb[gg];
+        na[gg] = node0 + NW * SB * min(g0 + gg, tg - 1);
+        // child of address x: 2 x + cl or cr
+        cl[gg] = NW - na[gg];
+        cr[gg] = 2u * NW - na[gg];
+        // (in vector registers: a select takes one scalar operand at most)
+        asm volatile("" : "+v"(cl[gg]), "+v"(cr[gg]));
       }
       for (uint32_t lv = 0; lv < a.D; ++lv) {
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int gg = 0; gg < GI; ++gg) {
-#pragma unroll
-          for (int k = 0; k < IT; ++k) {
-            const uint64_t w = lds_rd64(na[gg][k]);
-            const uint32_t lo = (uint32_t)w, th = (uint32_t)(w >> 32);
-            const uint32_t rk =
-                STAGED ? lds_rd32(lo + lane_off[k]) : a.ranks[(size_t)lo * a.ld + sk[k]];
-            na[gg][k] = 2u * na[gg][k] - nb[gg] + (rk < th ? 8u : 16u);
+          for (int gg = 0; gg < GI; ++gg) {
+            const uint64_t x = lds_rd64(na[gg]);
+            const uint32_t rk = lds_rd32((uint32_t)x + lane_off);
+            na[gg] = 2u * na[gg] + (rk < (uint32_t)(x >> 32) ? cl[gg] : cr[gg]);
           }
+        } else {
+          uint32_t x[GI], rk[GI];
+#pragma unroll
+          for (int gg = 0; gg < GI; ++gg) x[gg] = lds_rd32(na[gg]);
+#pragma unroll
+          for (int gg = 0; gg < GI; ++gg) {
+            // the word's low byte times 128 or 256, plus the lane's offset
+            const uint32_t at = FS ? __builtin_amdgcn_udot4(x[gg], 128u, lane_off, false)
+                                   : ((x[gg] & 0xFFu) << 8) + lane_off;
+            rk[gg] = lds_rd32(at);
+          }
+#pragma unroll
+          for (int gg = 0; gg < GI; ++gg)
+            na[gg] = 2u * na[gg] + (rk[gg] < x[gg] ? cl[gg] : cr[gg]);
         }
       }
 #pragma unroll
       for (int gg = 0; gg < GI; ++gg) {
         const uint32_t g = g0 + gg;
         if (g >= tg) continue;
-#pragma unroll
-        for (int k = 0; k < IT; ++k) {
-          if (yk[k] == 0xFFu) continue;
-          const uint32_t leaf = (na[gg][k] - nb[gg]) / 8u + 1u - SL;
-          const uint32_t e = leaf * K + yk[k];
-          if (a.hist_in_lds)
-            atomicAdd(&hist[(size_t)g * SL * K + e], 1u);
-          else
-            atomicAdd(&a.leafcnt[(size_t)(r0 + g) * SL * K + e], 1u);
+        // the leaf's word of class 0, in bytes from the tree's histogram
+        const uint32_t leaf0 = node0 + NW * SB * g + NW * (SL - 1u);
+        if (a.hist_in_lds) {
+          // (both factors below 2^24)
+          const uint32_t at = __umul24(na[gg] - leaf0, K) / (NW / 4u) + 4u * g * SL * K + y4;
+          __hip_atomic_fetch_add((__attribute__((address_space(3))) uint32_t *)at, w,
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else if (w) {
+          atomicAdd(&a.leafcnt[((size_t)(r0 + g) * SL + (na[gg] - leaf0) / NW) * K + y], w);
         }
       }
     }
   }
   if (a.hist_in_lds) {
     __syncthreads();
-    for (uint32_t e = threadIdx.x; e < tg * SL * K; e += WT_THREADS)
-      if (hist[e]) atomicAdd(&a.leafcnt[(size_t)r0 * SL * K + e], hist[e]);
+    // two counters at a time (each stays below 2^32, so no carry passes from
+    // one to the other).  The ranges start at different words, so that the
+    // blocks of a group, which end together, do not add to the same ones at
+    // the same time.
+    const uint32_t pairs = tg * (SL / 2) * K, rot = (uint64_t)pairs * blockIdx.x / gridDim.x;
+    const uint64_t *hist2 = reinterpret_cast<const uint64_t *>(hist);
+    unsigned long long *out =
+        reinterpret_cast<unsigned long long *>(a.leafcnt + (size_t)r0 * SL * K);
+#pragma unroll 4
+    for (uint32_t e = threadIdx.x; e < pairs; e += WT_THREADS) {
+      const uint32_t at = e + rot < pairs ? e + rot : e + rot - pairs;
+      const uint64_t v = hist2[at];
+      if (v) atomicAdd(&out[at], (unsigned long long)v);
+    }
   }
+}
+
+// How often each sample is named by idx (entries past n are invalid input).
+__global__ __launch_bounds__(256) void k_walk_weight(const uint32_t *__restrict__ idx,
+                                                     uint32_t n_sub, uint32_t n,
+                                                     uint32_t *__restrict__ weight) {
+  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j < n_sub && idx[j] < n) atomicAdd(&weight[idx[j]], 1u);
 }
 
 // Epilogue from leaf counts (walk path), any depth.  Block per tree: the
@@ -655,7 +764,6 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
                               uint32_t n_min, double alpha, const FitnessOut &out,
                               uint32_t *leafcnt) {
   const uint32_t SB = (1u << D) - 1u, SL = 1u << D, K = ds->K, F = ds->F;
-  const size_t cells = (size_t)P * SL * K;
   // only the context's own buffer is known to stay clear between calls (a
   // caller's scratch may have held anything since)
   const size_t bytes = walk_scratch_bytes(P, D, K);
@@ -672,6 +780,8 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     a.ld = ds->ld;
     a.labels = ds->labels;
     a.idx = idx;
+    a.weight = nullptr;
+    a.n_unique = ds->n_unique;
     a.n_sub = n_sub;
     a.n = ds->n;
     a.feat = feat;
@@ -681,72 +791,103 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     a.F = F;
     a.K = K;
     a.leafcnt = leafcnt;
-    a.vec4 = (ds->ld % 4 == 0 && ((uintptr_t)ds->ranks & 15u) == 0) ? 1u : 0u;
-    // LDS: the tile ([F][T] ranks and T labels), TG trees' nodes and, when
-    // it fits, their histograms, within a budget that leaves three blocks per
-    // CU; samples per thread: tiles of at most 16 KiB where the features allow
-    size_t budget = std::max<size_t>(48 * 1024, (ctx->max_lds - 4096) / 3);
-    if (ctx->walk_lds) budget = ctx->walk_lds;
-    const bool staged = (size_t)F * WT_THREADS * 4 <= 48 * 1024;
-    uint32_t IT = 4;
-    while (IT > 1 && (size_t)F * WT_THREADS * IT * 4 > 16 * 1024) IT /= 2;
-    if (ctx->walk_it == 1 || ctx->walk_it == 2 || ctx->walk_it == 4) IT = ctx->walk_it;
-    a.T = WT_THREADS * IT;
-    const size_t tile_bytes = (staged ? (size_t)F * a.T * 4 : 0) + a.T;
-    const size_t tree_nodes = (size_t)SB * 8, tree_hist = (size_t)SL * K * 4;
+    a.vec4 = (ds->n >= 4 && ds->ld % 4 == 0 && ((uintptr_t)ds->ranks & 15u) == 0) ? 1u : 0u;
+    if (idx && own && n_sub >= ds->n / 4) {
+      // A subset of a good part of the samples: all samples in order, each
+      // counted as often as the subset names it.  The columns then stream in,
+      // where a gather reads a line of 64 bytes or more per rank: at a quarter
+      // of the samples both move about as much.
+      uint32_t *w = (uint32_t *)arena_get(ctx, "walk_weight", (size_t)ds->n * 4);
+      if (!w) return MH_ENOMEM;
+      if (mh_status zs = launch_zero(ctx, {{w, (size_t)ds->n * 4}})) return zs;
+      k_walk_weight<<<(n_sub + 255) / 256, 256, 0, st>>>(idx, n_sub, ds->n, w);
+      MH_LAUNCHED(ctx, "k_walk_weight");
+      a.idx = nullptr;
+      a.weight = w;
+      a.n_sub = ds->n;
+    }
+    // LDS, one block per CU: a tile of T samples with its labels and weights,
+    // TG trees' nodes and, when it fits, their histograms.  The largest tile
+    // that leaves the trees at least 60 KiB: its waves then share nothing but
+    // the trees, and a tile's barriers are paid for by more walks.
+    const bool wide = ds->n >= WT_RANK_MAX;
+    uint32_t T = F <= 24 ? 1024u : F <= 48 ? 512u : F <= 128 ? 256u : 128u;
+    const uint32_t NG = WT_THREADS / T;
+    const size_t budget = ctx->max_lds - 4096;
+    const size_t tile_bytes = (size_t)F * T * 4 + T * 4 + T;
+    const size_t tree_nodes = (size_t)SB * (wide ? 8 : 4), tree_hist = (size_t)SL * K * 4;
+    if (tile_bytes + tree_nodes + 16 > budget)
+      return fail(ctx, MH_EDEVICE, "the device's LDS is too small for the walk kernel");
     a.hist_in_lds = 1;
-    size_t TG = budget > tile_bytes ? (budget - tile_bytes) / (tree_nodes + tree_hist) : 0;
+    size_t TG = (budget - tile_bytes - 16) / (tree_nodes + tree_hist);
     if (TG == 0) {
       // histograms in memory: the nodes alone decide the trees per block
       a.hist_in_lds = 0;
-      TG = budget > tile_bytes ? (budget - tile_bytes) / tree_nodes : 1;
+      TG = (budget - tile_bytes - 16) / tree_nodes;
     }
-    TG = std::max<size_t>(1, std::min<size_t>({TG, 32, P}));
-    // trees walked together per thread: 8, or 4 for small groups; a group
-    // is a whole number of them where it can be
-    const uint32_t GI = TG >= 8 ? 8u : 4u;
-    if (TG > GI) TG -= TG % GI;
-    a.TG = (uint32_t)TG;
-    const uint32_t groups = (P + a.TG - 1) / a.TG;
-    const size_t lds =
-        tile_bytes + TG * tree_nodes + (a.hist_in_lds ? TG * tree_hist : 0);
+    // Groups of trees times ranges of samples, at most one block per CU: the
+    // choice with the least work for a block, counted in CU cycles (measured):
+    // 8.4 per 64 samples, tree (in batches of four) and level, 12 per 64
+    // samples and column staged, 2,000 per tile for its barriers and the
+    // chains' latency, and 1.5 per histogram word cleared and added to memory.
+    // With a multiple of 8 ranges every block of one range is on the same XCD
+    // (blocks go round-robin over the 8 XCDs in launch order), whose L2 then
+    // serves the range's ranks to all groups but one; that saves 4 per column.
+    const uint32_t cus = (uint32_t)ctx->num_cu, units = (a.n_sub + 63) / 64;
+    const uint32_t g_min = (uint32_t)((P + TG - 1) / TG);
+    uint32_t groups = g_min, ranges = 1;
+    double best = 0;
+    for (uint32_t g = g_min; g <= std::max(g_min, std::min(P, cus)); ++g) {
+      const uint32_t tg = (P + g - 1) / g;
+      if (g > g_min && tg == (P + g - 2) / (g - 1)) continue;
+      uint32_t rg = std::max(1u, std::min(units, cus / g));
+      const uint32_t chains = tg > 2 * NG ? (tg + 3) / 4 * 4 : tg;
+      for (uint32_t r = rg;; r &= ~7u) {
+        const uint32_t per = (units + r - 1) / r;
+        const double c =
+            per * (8.4 * chains * D + (r % 8 ? 12.0 : 8.0) * F + 2000.0 * 64 / T) +
+            1.5 * tg * SL * K;
+        if (best == 0 || c < best) {
+          best = c;
+          groups = g;
+          ranges = r;
+        }
+        if (r < 8 || r % 8 == 0) break;
+      }
+    }
+    a.TG = (P + groups - 1) / groups;
+    groups = (P + a.TG - 1) / a.TG;
+    const size_t lds = tile_bytes + ((a.TG * tree_nodes + 7) & ~(size_t)7) +
+                       (a.hist_in_lds ? a.TG * tree_hist : 0);
     const size_t lds_al = (lds + 15) & ~(size_t)15;
-    // sample ranges: one round of resident blocks in all, at least one tile
-    // each
-    const uint32_t per_cu = std::max<uint32_t>(
-        1u, std::min<uint32_t>(8u, (uint32_t)(ctx->max_lds / std::max<size_t>(lds_al, 1))));
-    const uint32_t want = per_cu * (uint32_t)ctx->num_cu;
-    const uint32_t tiles = (n_sub + a.T - 1) / a.T;
-    a.ranges = std::max(1u, std::min(tiles, want / groups));
-    // a multiple of 8 ranges puts every block of one range on the same XCD
-    // (blocks go round-robin over the 8 XCDs in launch order), so each XCD's
-    // L2 holds only its ranges' ranks
-    if (a.ranges >= 8) a.ranges &= ~7u;
+    a.per = (units + ranges - 1) / ranges * 64;
+    ranges = (a.n_sub + a.per - 1) / a.per;
+    // trees a lane walks at once
+    const uint32_t gi = (a.TG + NG - 1) / NG;
     hipEvent_t e0, e1;
     const bool timed = prof_pair(ctx, &e0, &e1);
-    const dim3 grid(a.ranges, groups);
-#define MH_WALK2(ITV, GIV)                                                                  \
-  if (staged)                                                                               \
-    hipExtLaunchKernelGGL(k_walk_tiles<ITV, GIV, true>, grid, dim3(WT_THREADS), lds_al, st,  \
-                          e0, e1, 0, a);                                                    \
-  else                                                                                      \
-    hipExtLaunchKernelGGL(k_walk_tiles<ITV, GIV, false>, grid, dim3(WT_THREADS), lds_al, st, \
-                          e0, e1, 0, a);
-#define MH_WALK(ITV)    \
-  if (GI == 8) {        \
-    MH_WALK2(ITV, 8)    \
-  } else {              \
-    MH_WALK2(ITV, 4)    \
+    const dim3 grid(ranges, groups);
+#define MH_WALK(TV, GIV, WV)                                                                \
+  hipExtLaunchKernelGGL((k_walk_tiles<TV, GIV, WV>), grid, dim3(WT_THREADS), lds_al, st, e0, e1, \
+                        0, a)
+#define MH_WALK_T(GIV, WV)    \
+  switch (T) {                \
+    case 1024: MH_WALK(1024, GIV, WV); break; \
+    case 512: MH_WALK(512, GIV, WV); break;   \
+    case 256: MH_WALK(256, GIV, WV); break;   \
+    default: MH_WALK(128, GIV, WV); break;    \
   }
-    if (IT == 4) {
-      MH_WALK(4)
-    } else if (IT == 2) {
-      MH_WALK(2)
+    if (wide) {
+      MH_WALK_T(4, true);
+    } else if (gi <= 1) {
+      MH_WALK_T(1, false);
+    } else if (gi <= 2) {
+      MH_WALK_T(2, false);
     } else {
-      MH_WALK(1)
+      MH_WALK_T(4, false);
     }
+#undef MH_WALK_T
 #undef MH_WALK
-#undef MH_WALK2
     MH_LAUNCHED(ctx, "k_walk_tiles");
     if (timed) ctx->prof_launches += 1;
     ctx->prof_evals += (uint64_t)n_sub * P;

@@ -1,0 +1,97 @@
+"""The walk kernel at its edges against the oracle, element by element: every
+tile width (by the number of features), one sample and sizes around a tile and
+a block's range, subsets read through the index and as multiplicities (with
+repeated samples), one tree to many groups, columns whose threshold count
+passes what the packed words hold, and unaligned rank columns."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import dev, np_, random_trees, u32
+from paper_2311_06952_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(mh, ds, ods, feat, tau, D, idx=None):
+    want = oracle.fitness(ods, feat, tau, D, idx=idx, n_min=2, alpha=0.5)
+    for static in (False, True):
+        got = mh.fitness_eval(ds, dev(feat), dev(tau), D, idx=None if idx is None else dev(idx),
+                              n_min=2, alpha=0.5, static=static)
+        for k in range(2):
+            np.testing.assert_array_equal(u32(got[k]), want[k])
+        for k in (2, 3):
+            np.testing.assert_array_equal(np_(got[k]), want[k])
+
+
+# (n, F, K, D, P): tiles of 1,024, 512, 256 and 128 samples
+@pytest.mark.parametrize("n,F,K,D,P", [
+    (1, 24, 2, 6, 3), (63, 24, 3, 6, 65), (1023, 24, 2, 7, 5), (1025, 24, 4, 6, 33),
+    (513, 25, 3, 6, 17), (1537, 48, 2, 8, 4), (255, 49, 3, 6, 41), (1281, 128, 2, 6, 19),
+    (127, 129, 3, 6, 70), (641, 255, 2, 10, 3), (70_003, 5, 2, 6, 300)])
+def test_walk_tile_edges(mh_mod, n, F, K, D, P):
+    X, y = synth.random_small(n + F, n, F, K, levels=None if n % 2 else 30)
+    ods = oracle.dataset_from_X(X, y, K)
+    ds = mh_mod.dataset(X, y, K)
+    rng = np.random.default_rng(n)
+    feat, tau = random_trees(rng, P, D, F, ods.n_unique)
+    _check(mh_mod, ds, ods, feat, tau, D)
+
+
+@pytest.mark.parametrize("share", [0.1, 0.249, 0.25, 0.9, 3.0])
+def test_walk_subsets(mh_mod, share):
+    """Below a quarter of the samples the subset is gathered; from there on it
+    is counted, repeated samples as often as they are named."""
+    n, F, K, D = 4001, 9, 3, 7
+    X, y = synth.random_small(7, n, F, K)
+    ods = oracle.dataset_from_X(X, y, K)
+    ds = mh_mod.dataset(X, y, K)
+    rng = np.random.default_rng(3)
+    feat, tau = random_trees(rng, 21, D, F, ods.n_unique)
+    idx = rng.integers(0, n, size=int(n * share)).astype(np.uint32)
+    _check(mh_mod, ds, ods, feat, tau, D, idx=idx)
+
+
+@pytest.mark.parametrize("ld", [1301, 1304])
+def test_walk_many_thresholds(mh_mod, ld):
+    """Columns cut out of an encoding of more values than the packed words
+    hold, with rank columns that are and are not multiples of 16 bytes."""
+    import torch
+    n, F, K, D, P = 1300, 6, 3, 6, 11
+    rng = np.random.default_rng(ld)
+    nu = np.array([2**24, 700, 2**25, 2**24 - 1, 5, 2**24 - 2], np.uint32)
+    ranks = np.stack([rng.integers(0, v, size=n) for v in nu]).astype(np.uint32)
+    y = rng.integers(0, K, size=n).astype(np.uint8)
+    ods = oracle.Dataset(ranks, nu, y, K)
+    padded = torch.zeros((F, ld), dtype=torch.int32, device="cuda")
+    padded[:, :n] = dev(ranks)
+    feat, tau = random_trees(rng, P, D, F, nu)
+    for few in (False, True):  # with and without the wide columns
+        if few:
+            nu = np.minimum(nu, 2**24 - 2).astype(np.uint32)
+            ranks = np.minimum(ranks, nu[:, None] - 1).astype(np.uint32)
+            padded[:, :n] = dev(ranks)
+            ods = oracle.Dataset(ranks, nu, y, K)
+        ds = mh_mod.Dataset(padded, dev(y), dev(nu), n, F, K)
+        _check(mh_mod, ds, ods, feat, tau, D)
+
+
+def test_walk_wide_ranks(mh_mod):
+    """2^24 samples: thresholds of 32 bits, over a subset and over all."""
+    n, F, K, D, P = 2**24, 2, 2, 6, 9
+    rng = np.random.default_rng(5)
+    ranks = np.stack([rng.permutation(n), rng.integers(0, 1000, size=n)]).astype(np.uint32)
+    nu = np.array([n, 1000], np.uint32)
+    y = (ranks[0] % 3 == 0).astype(np.uint8)
+    ods = oracle.Dataset(ranks, nu, y, K)
+    ds = mh_mod.Dataset(dev(ranks), dev(y), dev(nu), n, F, K)
+    feat, tau = random_trees(rng, P, D, F, nu)
+    idx = rng.integers(0, n, size=3001).astype(np.uint32)
+    _check(mh_mod, ds, ods, feat, tau, D, idx=idx)
+    _check(mh_mod, ds, ods, feat[:1], tau[:1], D)
+
+
+@pytest.fixture(scope="module")
+def mh_mod():
+    import paper_2311_06952_amd as m
+    return m
