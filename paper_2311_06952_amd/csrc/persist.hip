@@ -781,20 +781,33 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
   a.tph = 0;
   uint32_t per_block = (max_tiles + grid - 1) / grid;  // tiles of one block, at most
   if (gr.tiles) {
-    // blocks in proportion to each problem's tiles, at least one each
+    // The fewest tiles per block, x, with which the problems' blocks (tiles / x
+    // each, rounded up, at least one) are no more than the grid: the problems
+    // do not wait for each other, so the launch lasts as long as its fullest
+    // block.  (In proportion to the tiles, rounded down, a problem just short
+    // of two blocks gets one with twice the others' tiles: the launch for
+    // the 32 problems of a level-6 horizon, n = 10^6, F = 20, 6.6 -> 4.7 ms.)
     const std::vector<uint32_t> &tl = *gr.tiles;
     const uint32_t np = (uint32_t)tl.size();
-    uint64_t total = 0;
-    for (uint32_t t : tl) total += t;
+    auto blocks_at = [&](uint32_t x) {
+      uint64_t nb = 0;
+      for (uint32_t t : tl) nb += t ? (t + x - 1) / x : 1u;
+      return nb;
+    };
+    uint32_t x_lo = 1, x_hi = 1;
+    for (uint32_t t : tl) x_hi = std::max(x_hi, t);
+    while (x_lo < x_hi) {
+      const uint32_t x = x_lo + (x_hi - x_lo) / 2;
+      if (blocks_at(x) <= grid) x_hi = x;
+      else x_lo = x + 1;
+    }
     std::vector<uint4> rg(np);
     std::vector<uint16_t> pob;
     uint32_t t0 = 0;
     for (uint32_t i = 0; i < np; ++i) {
-      uint64_t nbk = total ? (uint64_t)grid * tl[i] / total : 1;
-      nbk = nbk < 1 ? 1 : nbk;
-      nbk = tl[i] && nbk > tl[i] ? tl[i] : nbk;
-      rg[i] = make_uint4(t0, t0 + tl[i], (uint32_t)pob.size(), (uint32_t)nbk);
-      pob.insert(pob.end(), (size_t)nbk, (uint16_t)i);
+      const uint32_t nbk = tl[i] ? (tl[i] + x_lo - 1) / x_lo : 1u;
+      rg[i] = make_uint4(t0, t0 + tl[i], (uint32_t)pob.size(), nbk);
+      pob.insert(pob.end(), nbk, (uint16_t)i);
       t0 += tl[i];
     }
     if (pob.size() > (size_t)per_cu * (size_t)ctx->num_cu || pob.size() > (size_t)ctx->num_cu * 8u)
