@@ -151,7 +151,7 @@ __device__ __forceinline__ void stage_positions(uint8_t *__restrict__ lds, uint3
 // CMP (staged tiles only): the tiles come in the compact form (sorted ranks
 // and positions, the masks rebuilt in LDS) rather than as whole records.
 template <int D, int WAVES, int H, bool RES, bool CMP = false>
-__global__ __launch_bounds__(H * WAVES * 64) void k_deoct_persist(PersistArgs pa) {
+__global__ __launch_bounds__(H * WAVES * 64, H == 4 && !RES ? 4 : 1) void k_deoct_persist(PersistArgs pa) {
   constexpr int SB = (1 << D) - 1, SL = 1 << D, m = 2 * SB;
   constexpr uint32_t NTH = WAVES * 64, NT = H * NTH;
   constexpr int NA = (SB + H - 1) / H;  // nodes per group (the last may have fewer)
@@ -736,8 +736,9 @@ struct Groups {
   uint4 *ranges;
 };
 
-// Four wave groups exist only with resident tiles (staging every generation
-// needs registers that four groups per block do not have).
+// Four wave groups with tiles staged every generation exist up to depth 3:
+// 128 registers per lane hold a tree of seven nodes and the prefetch.  They are
+// the default where no resident form can be (four_staged).
 template <int D, int WAVES, int H>
 mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_tiles,
                    const Groups &gr, bool *used) {
@@ -747,7 +748,7 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
   // F = 20, n = 10^6, a level's launch 6.0 -> 4.9 ms; F = 8, n = 10^7, the
   // launches of a moving-horizon run 186 -> 237 ms)
   const void *kstage = nullptr;
-  if constexpr (H < 4)
+  if constexpr (H < 4 || D <= 3)
     kstage = pa.F >= PERSIST_COMPACT_MIN_F
                  ? reinterpret_cast<const void *>(k_deoct_persist<D, WAVES, H, false, true>)
                  : reinterpret_cast<const void *>(k_deoct_persist<D, WAVES, H, false, false>);
@@ -756,6 +757,16 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
   if (per_cu < 1)
     return MH_OK;  // not co-resident: the caller tries fewer groups, then the
                    // per-generation kernels
+  // four groups by the rule of four_staged (fewer were asked for): staged, and
+  // only where they put more waves on a CU than two groups per block
+  const bool auto4 = H == 4 && ctx->persist_halves < 4;
+  if constexpr (H == 4 && D <= 3) {
+    const void *two = pa.F >= PERSIST_COMPACT_MIN_F
+                          ? reinterpret_cast<const void *>(k_deoct_persist<D, WAVES, 2, false, true>)
+                          : reinterpret_cast<const void *>(k_deoct_persist<D, WAVES, 2, false, false>);
+    const uint32_t lds2 = persist_lds_bytes(pa.F, pa.P, (1u << D) - 1u, 2);
+    if (auto4 && per_cu * 4 <= coop_per_cu(ctx, two, 2 * WAVES * 64, lds2) * 2) return MH_OK;
+  }
   const uint32_t want = persist_bpc(max_tiles, (uint32_t)ctx->num_cu, H * WAVES);
   // with many tiles per CU the tile work dominates, and the per-generation
   // kernels win where they keep more waves per CU busy than the whole-run
@@ -828,7 +839,7 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
   }
   // resident tiles when every block's tiles fit the LDS next to the DE rows
   uint32_t lds_use = lds;
-  if (ctx->persist_resident) {
+  if (ctx->persist_resident && !auto4) {
     const uint32_t SB = (1u << D) - 1u;
     const uint32_t tph = (per_block + H - 1) / H;
     const uint32_t tile = align16u(mask_region(pa.F) + pa.F * MCOL);
@@ -842,7 +853,7 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
       kern = kres;
     }
   }
-  if (!a.tph && !kstage) return MH_OK;  // four groups need resident tiles
+  if (!a.tph && !kstage) return MH_OK;  // no staged form
   if (!a.tph) kern = kstage;
   if (coop_is_bad(ctx, kern, grid)) return MH_OK;
   if (ctx->debug)
@@ -865,6 +876,24 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
   ctx->last_coop_grid = grid;
   *used = true;
   return MH_OK;
+}
+
+// Whether a run's tiles are tried with four staged groups per block: depth up
+// to 3, and more tiles than the LDS of all CUs holds, so that every
+// generation stages them.  A generation then waits for its tiles' loads and
+// staging, and 16 waves per CU hide more of it than 8.  Measured per
+// generation, two groups against four, K = 3: n = 10^6, F = 20, depth 3, P = 64
+// 52.5 and 46.9 us, P = 128 51.7 and 45.0, P = 256 74.9 and 58.6; n = 4 10^6, F
+// = 8, P = 128 138 and 110; n = 2 10^5, F = 20, P = 128 19.5 and 17.4; n = 10^6,
+// F = 20, P = 128, depth 2 42.6 and 36.8, depth 1 37.6 and 33.9.  With wide rows
+// only one block fits a CU, and the same number of waves in one block waits
+// more for its barriers: F = 30 65.4 and 67.7, F = 40 80.2 and 86.5.
+bool four_staged(const Ctx *ctx, uint32_t D, uint32_t waves, uint32_t F, uint32_t P,
+                 uint32_t max_tiles) {
+  const uint64_t tile = align16u(mask_region(F) + F * MCOL);
+  return D <= 3 && waves <= 4 && ctx->persist_halves == 2 &&
+         persist_lds_bytes(F, P, (1u << D) - 1u, 4) <= ctx->max_lds &&
+         max_tiles * tile > (uint64_t)ctx->num_cu * ctx->max_lds;
 }
 
 template <int D, int H>
@@ -1068,6 +1097,7 @@ mh_status persist_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint3
   if (timed) MH_HIP(ctx, hipEventRecord(e0, st));
   mh_status s = MH_OK;
   const uint32_t max_tiles = tile_layout(n_sub, F, K, n_problems).max_tiles;
+  if (four_staged(ctx, D, waves, F, P, max_tiles)) H = 4;
   // the most wave groups that launch, down to one
   for (uint32_t hh = H; hh >= 1 && !*used; hh /= 2) {
     const uint32_t lds_h = persist_lds_bytes(F, P, SB, hh);

@@ -1,0 +1,74 @@
+"""GPU parity of the whole-run kernel with tiles staged every generation by four
+groups per block against the oracle: best tree, cost and the final population
+bit for bit; and several problems of very different sizes in one launch."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2311_06952_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mh():
+    import paper_2311_06952_amd as m
+    return m
+
+
+def _check(mh, ctx, X, y, K, D, prm):
+    want = oracle.deoct(oracle.dataset_from_X(X, y, K), D, oracle.de_params(*prm), with_pop=True)
+    got = mh.subtree_solve(mh.dataset(X, y, K, ctx=ctx), D, mh.de_params(*prm), ctx=ctx,
+                           with_pop=True)
+    for key in ("feat", "tau", "label", "pop", "pop_cost"):
+        np.testing.assert_array_equal(got[key], want[key])
+    assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
+
+
+# whole records below 16 features, the compact form from there on; blocks
+# without a tile, with one group busy, with a ragged last round
+@pytest.mark.parametrize("D,P,K,n,F", [
+    (1, 3, 2, 5, 2), (1, 65, 3, 9000, 17), (2, 64, 4, 3000, 15), (2, 200, 2, 20_000, 16),
+    (3, 5, 3, 64, 16), (3, 64, 5, 17_000, 3), (3, 128, 3, 40_000, 20), (3, 256, 2, 33_000, 9),
+    (3, 129, 7, 6_000, 18), (3, 100, 2, 2_000, 39)])
+def test_four_staged_groups(mh, monkeypatch, D, P, K, n, F):
+    from paper_2311_06952_amd import capi
+    monkeypatch.setenv("MHDEOCT_PERSIST", "1")
+    monkeypatch.setenv("MHDEOCT_PERSIST_RESIDENT", "0")
+    monkeypatch.setenv("MHDEOCT_PERSIST_HALVES", "4")
+    X, y = synth.random_small(D * 1000 + P, n, F, K, levels=50 if K == 5 else None)
+    ctx = capi.Context(0)
+    _check(mh, ctx, X, y, K, D, (P, 7, -1.0 if K > 3 else 0.5, 0.7, 77 + D, 2, 0.5))
+    ctx.close()
+
+
+def test_four_staged_groups_by_size(mh):
+    """More tiles than the LDS of the chip holds: taken without being asked for."""
+    from paper_2311_06952_amd import capi
+    X, y = synth.random_small(5, 175_000, 20, 3)
+    ctx = capi.Context(0)
+    _check(mh, ctx, X, y, 3, 3, (9, 3, 0.5, 0.9, 3, 1, 0.0))
+    ctx.close()
+
+
+@pytest.mark.parametrize("share", [0.004, 0.31, 0.97])
+def test_problems_of_unequal_size(mh, monkeypatch, share):
+    """The blocks of a launch follow the problems' tiles: the left child of the
+    first split holds about this share of the samples."""
+    from paper_2311_06952_amd import capi
+    monkeypatch.setenv("MHDEOCT_PERSIST", "1")
+    monkeypatch.setenv("MHDEOCT_PERSIST_RESIDENT", "0")
+    n, F, K, D = 16_000, 5, 3, 4
+    rng = np.random.default_rng(int(share * 1000))
+    X = rng.normal(size=(n, F)).astype(np.float32)
+    cut = np.quantile(X[:, 0], share)
+    y = np.where(X[:, 0] < cut, 2, (X[:, 1] > 0.3).astype(int)).astype(np.uint8)
+    y[rng.random(n) < 0.05] = 1
+    prm = (40, 12, 0.5, 0.8, 11, 1, 0.0)
+    want = oracle.mh_train(oracle.dataset_from_X(X, y, K), D, 1, oracle.de_params(*prm))
+    ctx = capi.Context(0)
+    got = mh.mh_train(mh.dataset(X, y, K, ctx=ctx), D, 1, mh.de_params(*prm), batched=True, ctx=ctx)
+    ctx.close()
+    for key in ("feat", "tau", "label"):
+        np.testing.assert_array_equal(got[key], want[key])
+    assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
