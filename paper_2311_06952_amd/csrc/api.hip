@@ -553,10 +553,6 @@ mh_status mh_ctx_create(int device, void *hip_stream, mh_ctx **out) {
     c->c.resident_blocks = (uint32_t)std::max(0, atoi(v));
   if (const char *v = std::getenv("MHDEOCT_RANK_COOP")) c->c.rank_coop = atoi(v) != 0;
   if (const char *v = std::getenv("MHDEOCT_DEBUG")) c->c.debug = atoi(v) != 0;
-  if (const char *v = std::getenv("MHDEOCT_SELECT_TPI")) {
-    const int t = atoi(v);
-    c->c.de_select_tpi = (t == 1 || t == 2 || t == 4 || t == 8) ? (uint32_t)t : 0u;
-  }
   if (const char *v = std::getenv("MHDEOCT_WAIT_TICKS"))
     c->c.wait_ticks = std::min<uint64_t>(strtoull(v, nullptr, 10), 200000000ull);
   if (const char *v = std::getenv("MHDEOCT_RANK_R")) {

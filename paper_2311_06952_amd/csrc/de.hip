@@ -97,52 +97,110 @@ __global__ __launch_bounds__(LB) void k_de_gen(StepArgs a, GenArgs e) {
 // of de_gen_body would make every individual's draws and float64 work one
 // after another on a single CU).  Same arithmetic and results.
 //
-// Part 1, individual r of problem blockIdx.y on e.tpi adjacent lanes (lane j
-// of the group takes classes j, j + tpi, ... of the epilogue and genes j,
-// j + tpi, ... of the copy): the epilogue of the evaluated population's node
-// counts (its cost), then selection (eq. selection, ties to the trial) or, in
-// generation 0, the initial cost; the consumed counters go back to zero.
+// Part 1, SEL_NI individuals of problem blockIdx.y: the epilogue of the
+// evaluated population's node counts (their costs), then selection (eq.
+// selection, ties to the trial) or, in generation 0, the initial cost; the
+// consumed counters go back to zero.  It waits for memory, so every thread's
+// loads are few and go out together: the counts of the block's individuals
+// into LDS (classes in chunks when they are many; consecutive threads load
+// consecutive individuals of one counter) and the trial genes, before the
+// selection is known, into registers.  A thread per individual and last-level
+// node then scores its two leaves over all classes.  (A few lanes per
+// individual with all of a tree's nodes in registers spill from depth 5 on:
+// P = 512, K = 4, depth 4 9.7 -> 4.8 us; P = 256, K = 3, depth 5 48.8 -> 4.9.)
 constexpr uint32_t SPLIT_THREADS = 256;
+constexpr uint32_t SEL_NI = 8;
+constexpr uint32_t SEL_WORDS = 8192;  // LDS words of a chunk's counts
 
-template <int D, int TPI>
+template <int D>
 __global__ __launch_bounds__(SPLIT_THREADS) void k_de_select(StepArgs a, GenArgs e) {
-  constexpr int SB = (1 << D) - 1, m = 2 * SB;
-  constexpr uint32_t tpi = TPI;
+  constexpr uint32_t SB = (1u << D) - 1u, m = 2 * SB, LN = 1u << (D - 1);
+  constexpr uint32_t KC = SEL_WORDS / (SB * SEL_NI);  // classes of a chunk
+  constexpr uint32_t QM = (m * SEL_NI + SPLIT_THREADS - 1) / SPLIT_THREADS;  // genes per thread
+  __shared__ uint32_t s_cnt[SB * KC * SEL_NI];
+  __shared__ uint32_t s_sum[3 * SEL_NI];  // correct, violations, splits
+  __shared__ uint32_t s_take[SEL_NI];
   const uint32_t sub = blockIdx.y, P = a.P, Ppad = pad64(P), K = e.K;
-  const uint32_t r = (blockIdx.x * SPLIT_THREADS + threadIdx.x) / tpi, j = threadIdx.x % tpi;
-  if (r >= P) return;  // whole groups leave together
+  const uint32_t r0 = blockIdx.x * SEL_NI, own = min(SEL_NI, P - r0);
+  const uint32_t i = threadIdx.x % SEL_NI, u = threadIdx.x / SEL_NI, step = SPLIT_THREADS / SEL_NI;
+  const uint32_t r = r0 + min(i, own - 1u);
+  const bool live = i < own;
   double *cost = a.cost + (size_t)sub * P;
-  // the parent's cost and this lane's share of the trial genes are loaded
-  // with the counts, before the selection is known, so that the step waits
-  // for memory once
-  constexpr int QM = (m + TPI - 1) / TPI;  // genes per lane
-  double v[QM];
-  double pc = 0.0;
+  double v[QM], pc = 0.0;
   if (!e.init) {
     pc = cost[r];
     const double *tr = a.trial + (size_t)sub * P * m + (size_t)r * a.rs;
 #pragma unroll
-    for (int i = 0; i < QM; ++i) {
-      const uint32_t q = j + (uint32_t)i * tpi;
-      if (q < (uint32_t)m) v[i] = tr[(size_t)q * a.qs];
+    for (uint32_t k = 0; k < QM; ++k) v[k] = tr[(size_t)min(u + k * step, m - 1u) * a.qs];
+  }
+  uint32_t *cnt = e.cnt + (size_t)sub * SB * K * Ppad;
+  const uint32_t *ctot = e.ctot + (size_t)sub * K;
+  if (threadIdx.x < 3 * SEL_NI) s_sum[threadIdx.x] = 0;
+  uint32_t n_sub = 0, nl0 = 0, nl1 = 0, b0 = 0, b1 = 0;
+  for (uint32_t k0 = 0; k0 < K; k0 += KC) {
+    const uint32_t kc = min(KC, K - k0), inv = 0xFFFFFFFFu / kc + 1u;  // y / kc: exact, y kc < 2^32
+    if (k0) __syncthreads();  // the last chunk is scored
+#pragma unroll 4
+    for (uint32_t y = u; y < SB * kc; y += step) {
+      const uint32_t t = kc == 1 ? y : __umulhi(y, inv), c = y - t * kc;
+      uint32_t *at = cnt + ((size_t)t * K + k0 + c) * Ppad + r;
+      uint32_t w = 0;
+#pragma unroll
+      for (uint32_t q = 0; q < CNT_REP; ++q)
+        w += at[q * cnt_copy_elems(e.n_problems, SB, K, P)];
+      s_cnt[y * SEL_NI + i] = w;
+    }
+    __syncthreads();
+    if (live)
+      for (uint32_t y = u; y < SB * kc; y += step) {
+        const uint32_t t = kc == 1 ? y : __umulhi(y, inv), c = y - t * kc;
+        uint32_t *at = cnt + ((size_t)t * K + k0 + c) * Ppad + r;
+#pragma unroll
+        for (uint32_t q = 0; q < CNT_REP; ++q) at[q * cnt_copy_elems(e.n_problems, SB, K, P)] = 0;
+      }
+    for (uint32_t c = 0; c < kc; ++c) {
+      const uint32_t tot = ctot[k0 + c];
+      n_sub += tot;
+      if (u >= LN) continue;
+      uint32_t w = tot, node = 1;
+#pragma unroll
+      for (int d = D - 2; d >= 0; --d) {
+        const uint32_t left = s_cnt[((node - 1) * kc + c) * SEL_NI + i], bit = (u >> d) & 1u;
+        w = bit ? w - left : left;
+        node = 2 * node + bit;
+      }
+      const uint32_t l = s_cnt[((node - 1) * kc + c) * SEL_NI + i], z = w - l;
+      nl0 += l;
+      nl1 += z;
+      b0 = l > b0 ? l : b0;
+      b1 = z > b1 ? z : b1;
     }
   }
-  const size_t rep = cnt_copy_elems(e.n_problems, SB, K, P);
-  const TreeScore sc = epilogue_node_counts<D, CNT_REP>(
-      e.cnt + (size_t)sub * SB * K * Ppad, e.ctot + (size_t)sub * K, K, Ppad, r,
-      a.feat + ((size_t)sub * P + r) * SB, e.n_min, e.alpha, nullptr, nullptr, rep, tpi);
-  if (e.init) {
-    if (j == 0) cost[r] = sc.cost;
-    return;
+  if (u < LN) {
+    atomicAdd(&s_sum[i], b0 + b1);
+    const uint32_t vio = (nl0 > 0 && nl0 < e.n_min ? 1u : 0u) + (nl1 > 0 && nl1 < e.n_min ? 1u : 0u);
+    if (vio) atomicAdd(&s_sum[SEL_NI + i], vio);
   }
-  if (!(sc.cost <= pc)) return;
+  const uint8_t *feat = a.feat + ((size_t)sub * P + r) * SB;
+  uint32_t splits = 0;
+  for (uint32_t t = u; t < SB; t += step) splits += feat[t] != 0;
+  if (splits) atomicAdd(&s_sum[2 * SEL_NI + i], splits);
+  __syncthreads();
+  if (u == 0) {
+    double w = (double)(n_sub - s_sum[i]);
+    w = __dadd_rn(w, __dmul_rn(e.alpha, (double)s_sum[2 * SEL_NI + i]));
+    w = __dadd_rn(w, (double)s_sum[SEL_NI + i]);
+    const bool take = live && (e.init || w <= pc);
+    if (take) cost[r] = w;
+    s_take[i] = take ? 1u : 0u;
+  }
+  if (e.init) return;
+  __syncthreads();
+  if (!s_take[i]) return;
   double *pr = a.pop + (size_t)sub * P * m + (size_t)r * a.rs;
 #pragma unroll
-  for (int i = 0; i < QM; ++i) {
-    const uint32_t q = j + (uint32_t)i * tpi;
-    if (q < (uint32_t)m) pr[(size_t)q * a.qs] = v[i];
-  }
-  if (j == 0) cost[r] = sc.cost;
+  for (uint32_t k = 0; k < QM; ++k)
+    if (u + k * step < m) pr[(size_t)(u + k * step) * a.qs] = v[k];
 }
 
 // Part 2, one thread per (node t, individual r) of problem blockIdx.y, r
@@ -460,22 +518,13 @@ mh_status launch_de_gen(Ctx *ctx, const DeDev &de, const uint64_t *prob_ids, uin
   const uint32_t tpi = 1;  // more threads per individual measured slower
   GenArgs e{cnt, ctot, K, n_min, alpha, init ? 1 : 0, tpi, n_problems};
   if (de.P >= DE_SPLIT_MIN_P) {
-    // large populations: the generation as two launches spread over the chip;
-    // the epilogue and selection of an individual on up to 4 lanes (one per
-    // class), so that its count loads and gene copies are spread out
+    // large populations: the generation as two launches spread over the chip
     hipStream_t st = ctx->stream;
     const uint32_t SB = (1u << de.D) - 1u;
-    uint32_t stpi = 1;
-    while (stpi < K && stpi < 4) stpi <<= 1;
-    if (ctx->de_select_tpi) stpi = ctx->de_select_tpi;
-    e.tpi = stpi;
-    const dim3 g1((de.P * stpi + SPLIT_THREADS - 1) / SPLIT_THREADS, n_problems);
+    const dim3 g1((de.P + SEL_NI - 1) / SEL_NI, n_problems);
     const dim3 g2((de.P * SB + SPLIT_THREADS - 1) / SPLIT_THREADS, n_problems);
-#define MH_SPLIT(DD)                                                          \
-  if (stpi == 1) k_de_select<DD, 1><<<g1, SPLIT_THREADS, 0, st>>>(a, e);      \
-  else if (stpi == 2) k_de_select<DD, 2><<<g1, SPLIT_THREADS, 0, st>>>(a, e); \
-  else if (stpi == 4) k_de_select<DD, 4><<<g1, SPLIT_THREADS, 0, st>>>(a, e); \
-  else k_de_select<DD, 8><<<g1, SPLIT_THREADS, 0, st>>>(a, e);                \
+#define MH_SPLIT(DD)                               \
+  k_de_select<DD><<<g1, SPLIT_THREADS, 0, st>>>(a, e); \
   k_de_mutate<<<g2, SPLIT_THREADS, 0, st>>>(a);
     switch (de.D) {
       case 1: MH_SPLIT(1) break;

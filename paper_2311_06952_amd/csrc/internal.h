@@ -80,9 +80,6 @@ struct Ctx {
   // grid-barrier time limit in device wall-clock ticks (MHDEOCT_WAIT_TICKS;
   // tests set a tiny one to exercise the recovery from a barrier that gives up)
   uint64_t wait_ticks = 200000000ull;
-  // lanes per individual of the split DE step's selection (MHDEOCT_SELECT_TPI,
-  // 1, 2, 4 or 8; 0: one per class up to 4)
-  uint32_t de_select_tpi = 0;
   // remembered occupancy queries
   struct Occ {
     const void *kern;
