@@ -497,9 +497,11 @@ static StepArgs make_args(const DeDev &de, const uint64_t *prob_ids, uint64_t pr
   return a;
 }
 
-// From this population size on a generation's DE work runs as two launches
-// spread over the chip instead of one block per problem.
-constexpr uint32_t DE_SPLIT_MIN_P = 256;
+// From this population size on, and from depth 4 on, a generation's DE work
+// runs as two launches spread over the chip instead of one block per problem
+// (n = 10^5, one block against the two: depth 5, P = 128 and 200 28.9 us and
+// 9.8; depth 4, P = 200 16.4 and 9.7; depth 3, P = 128 8.7 and 9.6).
+constexpr uint32_t DE_SPLIT_MIN_P = 256, DE_SPLIT_MIN_D = 4;
 
 static uint32_t step_threads(uint32_t P) {
   uint32_t threads = 64;
@@ -517,7 +519,7 @@ mh_status launch_de_gen(Ctx *ctx, const DeDev &de, const uint64_t *prob_ids, uin
   const uint32_t rp = step_threads(de.P);
   const uint32_t tpi = 1;  // more threads per individual measured slower
   GenArgs e{cnt, ctot, K, n_min, alpha, init ? 1 : 0, tpi, n_problems};
-  if (de.P >= DE_SPLIT_MIN_P) {
+  if (de.P >= DE_SPLIT_MIN_P || de.D >= DE_SPLIT_MIN_D) {
     // large populations: the generation as two launches spread over the chip
     hipStream_t st = ctx->stream;
     const uint32_t SB = (1u << de.D) - 1u;

@@ -780,6 +780,13 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
     if (!ctx->persist_blocks_per_cu && max_tiles > 16u * (uint32_t)ctx->num_cu &&
         ctx->fit_blocks_per_cu * fw > have)
       return MH_OK;
+    // (at depth 4 and four waves of individuals the DE work adds to that from
+    // about 32 tiles per CU on: n = 10^6, F = 20, P = 256 110 us here and 98
+    // there, P = 130 105 and 88; n = 4 10^6, F = 6 341 and 286; but n = 3 10^5,
+    // F = 8 36 and 41)
+    if (!ctx->persist_blocks_per_cu && D == 4 && WAVES == 4 &&
+        max_tiles > 32u * (uint32_t)ctx->num_cu)
+      return MH_OK;
   }
   uint32_t bpc = ctx->persist_blocks_per_cu ? ctx->persist_blocks_per_cu : want;
   bpc = bpc < (uint32_t)per_cu ? bpc : (uint32_t)per_cu;
@@ -899,12 +906,18 @@ bool four_staged(const Ctx *ctx, uint32_t D, uint32_t waves, uint32_t F, uint32_
 template <int D, int H>
 mh_status launch_d(Ctx *ctx, uint32_t waves, const PersistArgs &pa, uint32_t lds,
                    uint32_t max_tiles, const Groups &gr, bool *used) {
-  switch (waves) {
-    case 1: return launch_w<D, 1, H>(ctx, pa, lds, max_tiles, gr, used);
-    case 2: return launch_w<D, 2, H>(ctx, pa, lds, max_tiles, gr, used);
+  if (waves == 1) return launch_w<D, 1, H>(ctx, pa, lds, max_tiles, gr, used);
+  if (waves == 2) return launch_w<D, 2, H>(ctx, pa, lds, max_tiles, gr, used);
+  // Depth 5 beyond two waves of individuals is left to the per-generation
+  // kernels: every block would repeat the DE work of a large population on 31
+  // nodes for few tiles (per generation, here and there: n = 10^4, F = 10, P =
+  // 200 59.5 and 29.2 us; n = 10^5 71 and 44; n = 5 10^5 120 and 94; n = 3 10^4,
+  // F = 20, P = 130 42 and 34).
+  if constexpr (D < 5) switch (waves) {
     case 4: return launch_w<D, 4, H>(ctx, pa, lds, max_tiles, gr, used);
     default: return launch_w<D, (H == 1 ? 8 : 4), H>(ctx, pa, lds, max_tiles, gr, used);
   }
+  return MH_OK;
 }
 
 template <int D>

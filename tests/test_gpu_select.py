@@ -30,3 +30,22 @@ def test_large_population_selection(monkeypatch, D, P, K, n, M, n_min):
     for key in ("feat", "tau", "label", "pop", "pop_cost"):
         np.testing.assert_array_equal(got[key], want[key])
     assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
+
+
+@pytest.mark.parametrize("D,D_MH,P", [(5, 4, 9), (5, 5, 64), (6, 4, 130)])
+def test_selection_of_several_problems(monkeypatch, D, D_MH, P):
+    """From depth 4 on the two launches also serve small populations, and the
+    levels of a batched horizon run all their problems in one grid."""
+    import paper_2311_06952_amd as mh
+    from paper_2311_06952_amd import capi
+    monkeypatch.setenv("MHDEOCT_PERSIST", "0")
+    X, y = synth.random_small(D * 10 + P, 1500, 5, 4)
+    prm = (P, 3, -1.0, 0.6, 5, 2, 0.5)
+    want = oracle.mh_train(oracle.dataset_from_X(X, y, 4), D, D_MH, oracle.de_params(*prm))
+    ctx = capi.Context(0)
+    got = mh.mh_train(mh.dataset(X, y, 4, ctx=ctx), D, D_MH, mh.de_params(*prm), batched=True,
+                      ctx=ctx)
+    ctx.close()
+    for key in ("feat", "tau", "label"):
+        np.testing.assert_array_equal(got[key], want[key])
+    assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
