@@ -327,7 +327,8 @@ __device__ __forceinline__ void leaf_epilogue_tree(uint32_t *__restrict__ leafcn
 // Measured per launch, against 256-thread blocks of up to 32 64-bit-node trees
 // without prefetch: depth 8, n = 10^5, F = 16, P = 100: 40.9 -> 37.2 us;
 // depth 6, n = 2 10^5, F = 100, P = 64 (ranks read from memory at every step
-// before): 810 -> 55 us.
+// before): 810 -> 55 us.  A call for four depth-2 trees on three quarters of
+// n = 2 10^5, F = 120: 52 us with every column staged, 43 with SEL.
 // ---------------------------------------------------------------------------
 constexpr uint32_t WT_THREADS = 1024;
 constexpr uint32_t WT_NPF = 8;  // 16-byte chunks of the next tile per thread
@@ -386,14 +387,49 @@ __device__ __forceinline__ void walk_plain(const WalkArgs &a, uint32_t r0, uint3
   }
 }
 
-template <uint32_t T, int GI, bool WIDE>
+// SEL: only the columns that the block's trees split on are staged (few trees
+// of a wide data set), numbered by their order.
+template <uint32_t T, int GI, bool WIDE, bool SEL>
 __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
   extern __shared__ __align__(16) uint32_t wl[];
-  __shared__ uint32_t s_wide;
   constexpr uint32_t NG = WT_THREADS / T, NW = WIDE ? 8u : 4u;  // bytes of a node
   // the column is held shifted left by FS
   constexpr uint32_t FS = T > 128 ? 1 : 0;
-  const uint32_t SB = (1u << a.D) - 1u, SL = 1u << a.D, K = a.K, F = a.F;
+  __shared__ uint8_t s_num[256], s_col[256];  // SEL: column to number and back
+  __shared__ uint32_t s_cols;
+  const uint32_t SB = (1u << a.D) - 1u, SL = 1u << a.D, K = a.K;
+  const uint32_t r0 = blockIdx.y * a.TG;
+  const uint32_t tg = min(a.TG, a.P - r0);
+  uint32_t F = a.F;  // columns staged
+  if constexpr (SEL) {
+    if (threadIdx.x < 256) s_num[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint32_t e = threadIdx.x; e < tg * SB; e += WT_THREADS) {
+      const uint32_t f = a.feat[(size_t)r0 * SB + e];
+      if (f != 0 && f <= a.F) s_num[f - 1u] = 1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      uint32_t run = 0;
+      for (uint32_t f = threadIdx.x; f < 256; f += 64) {
+        const bool on = s_num[f] != 0;
+        const uint64_t all = __ballot(on);
+        const uint32_t at = run + (uint32_t)__popcll(all & ((1ull << threadIdx.x) - 1ull));
+        if (on) {
+          s_col[at] = (uint8_t)f;
+          s_num[f] = (uint8_t)at;
+        }
+        run += (uint32_t)__popcll(all);
+      }
+      if (threadIdx.x == 0) {
+        if (run == 0) s_col[0] = 0;  // no split at all: nodes name column 0
+        s_cols = run ? run : 1u;
+      }
+    }
+    __syncthreads();
+    F = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_cols);
+  }
+  auto source = [&](uint32_t f) { return SEL ? (uint32_t)s_col[f] : f; };
   uint32_t *tile = wl;                                           // [T / 64][F][64]
   uint32_t *wgt = wl + F * T;                                    // [T] weights
   uint8_t *ylab = reinterpret_cast<uint8_t *>(wgt + T);          // [T]
@@ -403,18 +439,14 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint32_t *)wl);
   const uint32_t node0 = lds0 + 4u * (F * T + T + T / 4);
   const uint32_t hist0 = lds0 + 4u * (uint32_t)(hist - wl);
-  const uint32_t r0 = blockIdx.y * a.TG;
-  const uint32_t tg = min(a.TG, a.P - r0);
   // the block's sample range (a multiple of 64, so that every tile starts at
   // a multiple of 4 samples for the 16-byte loads)
   const uint32_t s0 = min(a.n_sub, blockIdx.x * a.per), s1 = min(a.n_sub, s0 + a.per);
   if (!WIDE) {
-    if (threadIdx.x == 0) s_wide = 0;
-    __syncthreads();
-    for (uint32_t f = threadIdx.x; f < F; f += WT_THREADS)
-      if (a.n_unique[f] >= WT_RANK_MAX) s_wide = 1;
-    __syncthreads();
-    if (s_wide) {
+    // (every wave finds the same, so the block leaves together)
+    bool big = false;
+    for (uint32_t f = threadIdx.x & 63u; f < a.F; f += 64) big |= a.n_unique[f] >= WT_RANK_MAX;
+    if (__ballot(big) != 0ull) {
       walk_plain(a, r0, tg, s0, s1);
       return;
     }
@@ -444,7 +476,7 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
     for (uint32_t k = 0; k < WT_NPF; ++k) {
       if (k * WT_THREADS >= nch) break;
       const uint32_t c = min(k * WT_THREADS + tid, nch - 1u), j = min(base + 4u * (c % T4), j_last);
-      pf[k] = *reinterpret_cast<const uint4 *>(a.ranks + (size_t)(c / T4) * a.ld + j);
+      pf[k] = *reinterpret_cast<const uint4 *>(a.ranks + (size_t)source(c / T4) * a.ld + j);
     }
   };
   auto word = [&](uint32_t rank, uint32_t f) {
@@ -454,8 +486,8 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
   // this block's trees: nodes into LDS, histogram cleared
   for (uint32_t e = threadIdx.x; e < tg * SB; e += WT_THREADS) {
     const uint32_t f = a.feat[(size_t)r0 * SB + e], t = a.tau[(size_t)r0 * SB + e];
-    const bool split = f != 0 && f <= F;
-    const uint32_t th = split ? t : 0u, col = split ? f - 1u : 0u;
+    const bool split = f != 0 && f <= a.F;
+    const uint32_t th = split ? t : 0u, col = split ? (SEL ? s_num[f - 1u] : f - 1u) : 0u;
     if constexpr (WIDE)
       reinterpret_cast<uint64_t *>(nodes)[e] = ((uint64_t)th << 32) | (col << 8);
     else
@@ -481,7 +513,7 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
         const uint32_t c = k * WT_THREADS + tid, f = c / T4, q = c % T4;
         if (c >= nch) continue;
         if (const uint32_t j = base + 4u * q; j < s1 && j > j_last) {
-          const uint32_t *p = a.ranks + (size_t)f * a.ld + j;
+          const uint32_t *p = a.ranks + (size_t)source(f) * a.ld + j;
           pf[k] = make_uint4(p[0], j + 1u < s1 ? p[1] : 0u, j + 2u < s1 ? p[2] : 0u, 0u);
         }
         tile4[((q / 16u) * F + f) * 16u + q % 16u] =
@@ -498,7 +530,7 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
           v[u] = 0;
           if (e < F * T && q < cnt) {
             const uint32_t smp = a.idx ? a.idx[base + q] : base + q;
-            if (smp < a.n) v[u] = a.ranks[(size_t)f * a.ld + smp];
+            if (smp < a.n) v[u] = a.ranks[(size_t)source(f) * a.ld + smp];
           }
         }
 #pragma unroll
@@ -792,11 +824,16 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     a.K = K;
     a.leafcnt = leafcnt;
     a.vec4 = (ds->n >= 4 && ds->ld % 4 == 0 && ((uintptr_t)ds->ranks & 15u) == 0) ? 1u : 0u;
-    if (idx && own && n_sub >= ds->n / 4) {
+    // few trees on a wide data set stage only the columns they split on, at
+    // most one per node (Fs: the columns a block stages, at most)
+    const bool sel = (uint64_t)P * SB <= F && ds->n < WT_RANK_MAX;
+    const uint32_t Fs = sel ? P * SB : F;
+    if (idx && own && n_sub >= ds->n / 4 && (uint64_t)n_sub * Fs >= (1u << 20)) {
       // A subset of a good part of the samples: all samples in order, each
       // counted as often as the subset names it.  The columns then stream in,
       // where a gather reads a line of 64 bytes or more per rank: at a quarter
-      // of the samples both move about as much.
+      // of the samples both move about as much.  (Two more launches, about 5
+      // us: a gather of 2^20 ranks takes 64 MB of lines.)
       uint32_t *w = (uint32_t *)arena_get(ctx, "walk_weight", (size_t)ds->n * 4);
       if (!w) return MH_ENOMEM;
       if (mh_status zs = launch_zero(ctx, {{w, (size_t)ds->n * 4}})) return zs;
@@ -811,10 +848,10 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     // that leaves the trees at least 60 KiB: its waves then share nothing but
     // the trees, and a tile's barriers are paid for by more walks.
     const bool wide = ds->n >= WT_RANK_MAX;
-    uint32_t T = F <= 24 ? 1024u : F <= 48 ? 512u : F <= 128 ? 256u : 128u;
+    const uint32_t T = Fs <= 24 ? 1024u : Fs <= 48 ? 512u : Fs <= 128 ? 256u : 128u;
     const uint32_t NG = WT_THREADS / T;
     const size_t budget = ctx->max_lds - 4096;
-    const size_t tile_bytes = (size_t)F * T * 4 + T * 4 + T;
+    const size_t tile_bytes = (size_t)Fs * T * 4 + T * 4 + T;
     const size_t tree_nodes = (size_t)SB * (wide ? 8 : 4), tree_hist = (size_t)SL * K * 4;
     if (tile_bytes + tree_nodes + 16 > budget)
       return fail(ctx, MH_EDEVICE, "the device's LDS is too small for the walk kernel");
@@ -845,7 +882,7 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
       for (uint32_t r = rg;; r &= ~7u) {
         const uint32_t per = (units + r - 1) / r;
         const double c =
-            per * (8.4 * chains * D + (r % 8 ? 12.0 : 8.0) * F + 2000.0 * 64 / T) +
+            per * (8.4 * chains * D + (r % 8 ? 12.0 : 8.0) * Fs + 2000.0 * 64 / T) +
             1.5 * tg * SL * K;
         if (best == 0 || c < best) {
           best = c;
@@ -867,24 +904,28 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     hipEvent_t e0, e1;
     const bool timed = prof_pair(ctx, &e0, &e1);
     const dim3 grid(ranges, groups);
-#define MH_WALK(TV, GIV, WV)                                                                \
-  hipExtLaunchKernelGGL((k_walk_tiles<TV, GIV, WV>), grid, dim3(WT_THREADS), lds_al, st, e0, e1, \
-                        0, a)
-#define MH_WALK_T(GIV, WV)    \
-  switch (T) {                \
-    case 1024: MH_WALK(1024, GIV, WV); break; \
-    case 512: MH_WALK(512, GIV, WV); break;   \
-    case 256: MH_WALK(256, GIV, WV); break;   \
-    default: MH_WALK(128, GIV, WV); break;    \
+#define MH_WALK(TV, GIV, WV, SV)                                                             \
+  hipExtLaunchKernelGGL((k_walk_tiles<TV, GIV, WV, SV>), grid, dim3(WT_THREADS), lds_al, st, e0, \
+                        e1, 0, a)
+#define MH_WALK_T(GIV, WV, SV)                    \
+  switch (T) {                                    \
+    case 1024: MH_WALK(1024, GIV, WV, SV); break; \
+    case 512: MH_WALK(512, GIV, WV, SV); break;   \
+    case 256: MH_WALK(256, GIV, WV, SV); break;   \
+    default: MH_WALK(128, GIV, WV, SV); break;    \
   }
     if (wide) {
-      MH_WALK_T(4, true);
+      MH_WALK_T(4, true, false);
+    } else if (sel && gi <= 2) {
+      MH_WALK_T(1, false, true);
+    } else if (sel) {
+      MH_WALK_T(4, false, true);
     } else if (gi <= 1) {
-      MH_WALK_T(1, false);
+      MH_WALK_T(1, false, false);
     } else if (gi <= 2) {
-      MH_WALK_T(2, false);
+      MH_WALK_T(2, false, false);
     } else {
-      MH_WALK_T(4, false);
+      MH_WALK_T(4, false, false);
     }
 #undef MH_WALK_T
 #undef MH_WALK

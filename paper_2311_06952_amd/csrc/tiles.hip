@@ -221,8 +221,17 @@ __global__ __launch_bounds__(256) void k_tile_sort(const uint32_t *__restrict__ 
 
 }  // namespace
 
+// One block plans the tiles and lists the samples, class by class, and its
+// time grows with samples times classes (and the few blocks of the tile sort
+// with the features), where the six launches take a call about 10 us whatever
+// the size.  Measured, a fitness call of 64 depth-2 trees in us, separate
+// launches and this form: K = 2, F = 4: n = 4000 55 and 44, 22,000 58 and 51;
+// K = 2, F = 60: 6000 54 and 45, 8000 49 and 48, 12,000 51 and 56; K = 9, F = 4:
+// 4000 50 and 44, 6000 49 and 48, 8000 50 and 54; K = 9, F = 22: 4000 49 and 46,
+// 6000 50 and 53; K = 9, F = 60: 3000 56 and 52, 6000 54 and 63.
 bool tiles_small(const mh_dataset *ds, uint32_t n_sub) {
-  return n_sub <= SMALL_MAX_N && ds->n < (1u << 26);
+  return n_sub <= SMALL_MAX_N && ds->n < (1u << 26) &&
+         (uint64_t)n_sub * (12u * ds->K + ds->F) <= 12u * 48000u;
 }
 
 mh_status launch_tile_build(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx,

@@ -52,6 +52,36 @@ def test_walk_subsets(mh_mod, share):
     _check(mh_mod, ds, ods, feat, tau, D, idx=idx)
 
 
+@pytest.mark.parametrize("share", [0.25, 0.95, 3.0])
+def test_walk_large_subsets(mh_mod, share):
+    """From 2^20 gathered ranks on the subset is counted into multiplicities."""
+    n, F, K, D = 130_000, 9, 3, 6
+    X, y = synth.random_small(8, n, F, K)
+    ods = oracle.dataset_from_X(X, y, K)
+    ds = mh_mod.dataset(X, y, K)
+    rng = np.random.default_rng(4)
+    feat, tau = random_trees(rng, 5, D, F, ods.n_unique)
+    idx = rng.integers(0, n, size=int(n * share)).astype(np.uint32)
+    _check(mh_mod, ds, ods, feat, tau, D, idx=idx)
+
+
+# at most as many nodes as columns: only the columns split on are staged (tiles
+# of every width; one tree; trees without a split)
+@pytest.mark.parametrize("n,F,K,D,P,nosplit", [
+    (5000, 120, 3, 2, 40, 0.15), (1999, 255, 2, 1, 255, 0.15), (130, 90, 3, 4, 6, 0.1),
+    (3001, 100, 4, 5, 1, 0.15), (70_001, 85, 2, 3, 2, 0.3), (900, 81, 3, 2, 5, 1.0),
+    (2500, 200, 3, 1, 47, 0.0)])
+def test_walk_selected_columns(mh_mod, n, F, K, D, P, nosplit):
+    X, y = synth.random_small(n + F, n, F, K, levels=None if n % 2 else 30)
+    ods = oracle.dataset_from_X(X, y, K)
+    ds = mh_mod.dataset(X, y, K)
+    rng = np.random.default_rng(n)
+    feat, tau = random_trees(rng, P, D, F, ods.n_unique, p_nosplit=nosplit)
+    _check(mh_mod, ds, ods, feat, tau, D)
+    idx = rng.integers(0, n, size=n // 2).astype(np.uint32)
+    _check(mh_mod, ds, ods, feat, tau, D, idx=idx)
+
+
 @pytest.mark.parametrize("ld", [1301, 1304])
 def test_walk_many_thresholds(mh_mod, ld):
     """Columns cut out of an encoding of more values than the packed words
