@@ -35,7 +35,7 @@ KERNELS = {
                  "internal.h"),
         counters="k_fitness_bits_plain_large_counters.txt"),
     "persistent": dict(
-        sources=("persist.hip", "fitness_core.h", "epilogue.h", "device_common.h", "grid_sync.h",
+        sources=("persist.hip", "persist.h", "fitness_core.h", "epilogue.h", "device_common.h", "grid_sync.h",
                  "internal.h"),
         counters=None),
 }

@@ -398,7 +398,7 @@ typedef struct {
  * memory are allocated once, here, as the pool that holds the resident
  * state of admitted requests (tile layout, population, counters); the
  * context's arena additionally holds the rank-encoding scratch of the
- * largest request.  At most max_slots (1..256) requests are resident at a
+ * largest request, or of a group of small ones (up to 256 MiB).  At most max_slots (1..256) requests are resident at a
  * time.  The context must not be used for other calls while the server
  * exists (they would share its stream and arena). */
 mh_status mh_server_create(mh_ctx *ctx, uint64_t hbm_budget, uint32_t max_slots,
@@ -446,7 +446,11 @@ mh_status mh_server_footprint(uint32_t n, uint32_t F, uint32_t K, uint32_t D,
  * generation.  A request whose tile layout has at least two tiles per CU
  * (about 32,000 samples on 256 CUs; MHDEOCT_SERVE_SOLO_TILES sets the tile
  * count, 0 never) fills the device by itself: it runs whole at admission as
- * one cooperative launch, the plain form's kernel.  Requests that ran their
+ * one cooperative launch, the plain form's kernel.  Small requests (P <= 128,
+ * at most 22,528 samples) run whole as well, in groups: the ones at the head
+ * of the queue are admitted together (pool, slots and four times the CUs'
+ * blocks bound a group), prepared by a launch for all of them, and one launch
+ * takes their runs' blocks from a queue.  Requests that ran their
  * G generations get their best tree evaluated and copied to pinned host
  * memory.  At most a few rounds are in
  * flight on the device; a round waits for older ones as needed.  Stops
