@@ -553,9 +553,7 @@ mh_status launch_de_gen(Ctx *ctx, const DeDev &de, const uint64_t *prob_ids, uin
     case 1: MH_GEN(1) break;
     case 2: MH_GEN(2) break;
     case 3: MH_GEN(3) break;
-    case 4: MH_GEN(4) break;
-    case 5: MH_GEN(5) break;
-    default: return fail(ctx, MH_EINVAL, "fused DE step supports depth 1..5");
+    default: return fail(ctx, MH_EINVAL, "one-block DE step supports depth 1..3");
   }
 #undef MH_GEN
   MH_LAUNCHED(ctx, "k_de_gen");

@@ -835,13 +835,16 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
       // of the samples both move about as much.  (Two more launches, about 5
       // us: a gather of 2^20 ranks takes 64 MB of lines.)
       uint32_t *w = (uint32_t *)arena_get(ctx, "walk_weight", (size_t)ds->n * 4);
-      if (!w) return MH_ENOMEM;
-      if (mh_status zs = launch_zero(ctx, {{w, (size_t)ds->n * 4}})) return zs;
-      k_walk_weight<<<(n_sub + 255) / 256, 256, 0, st>>>(idx, n_sub, ds->n, w);
-      MH_LAUNCHED(ctx, "k_walk_weight");
-      a.idx = nullptr;
-      a.weight = w;
-      a.n_sub = ds->n;
+      if (w) {
+        if (mh_status zs = launch_zero(ctx, {{w, (size_t)ds->n * 4}})) return zs;
+        k_walk_weight<<<(n_sub + 255) / 256, 256, 0, st>>>(idx, n_sub, ds->n, w);
+        MH_LAUNCHED(ctx, "k_walk_weight");
+        a.idx = nullptr;
+        a.weight = w;
+        a.n_sub = ds->n;
+      } else {
+        (void)hipGetLastError();  // no room for it: the subset is gathered
+      }
     }
     // LDS, one block per CU: a tile of T samples with its labels and weights,
     // TG trees' nodes and, when it fits, their histograms.  The largest tile
