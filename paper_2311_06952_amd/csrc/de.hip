@@ -215,11 +215,11 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_de_mutate(StepArgs a) {
   __shared__ uint32_t s_i[SPLIT_THREADS / 64];
   const uint32_t sub = blockIdx.y, P = a.P;
   const double *cost = a.cost + (size_t)sub * P;
-  double bc = DBL_MAX;
+  double bc = ARGMIN_NONE;
   uint32_t bi = 0xFFFFFFFFu;
   for (uint32_t i = threadIdx.x; i < P; i += SPLIT_THREADS) {
-    const double c = cost[i];
-    if (c < bc) {  // ascending i in this thread: ties keep the lower index
+    const double c = argmin_key(cost[i], i);
+    if (c < bc || i < bi) {  // ascending i in this thread: ties keep the lower index
       bc = c;
       bi = i;
     }
@@ -316,11 +316,11 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_de_select_mutate(StepArgs a) 
     const double t = ct[j];
     return t <= c ? t : c;
   };
-  double bc = DBL_MAX;
+  double bc = ARGMIN_NONE;
   uint32_t bi = 0xFFFFFFFFu;
   for (uint32_t i = threadIdx.x; i < P; i += SPLIT_THREADS) {
-    const double c = post_cost(i);
-    if (c < bc) {  // ascending i in this thread: ties keep the lower index
+    const double c = argmin_key(post_cost(i), i);
+    if (c < bc || i < bi) {  // ascending i in this thread: ties keep the lower index
       bc = c;
       bi = i;
     }

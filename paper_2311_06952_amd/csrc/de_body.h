@@ -3,8 +3,6 @@
 // stand-alone DE kernels and the fused fitness + DE kernel.
 #pragma once
 
-#include <cfloat>
-
 #include "device_common.h"
 #include "epilogue.h"
 #include "internal.h"
@@ -86,7 +84,7 @@ __device__ __forceinline__ void de_step_body(const StepArgs &a, uint32_t sub, ui
   }
   const uint32_t nr = blockDim.x / tpi;  // a power of two >= P
   if (j == 0) {
-    s_cost[r] = r < P ? my_cost : DBL_MAX;
+    s_cost[r] = r < P ? argmin_key(my_cost, r) : ARGMIN_NONE;
     s_idx[r] = r;
   }
   __syncthreads();
@@ -296,10 +294,11 @@ __device__ __forceinline__ void de_gen_body(const StepArgs &a, const GenArgs &e,
 #pragma unroll
         for (int t = 0; t < SB; ++t) cnt[q * rep + ((size_t)t * K + k) * Ppad] = 0;
   }
-  double my_cost = DBL_MAX;
+  double bc = ARGMIN_NONE;
   if (live) {
     const bool take = !init && tc <= c_old;
-    my_cost = (init || take) ? tc : c_old;
+    const double my_cost = (init || take) ? tc : c_old;
+    bc = argmin_key(my_cost, r);
     if (init || take) cost[r] = my_cost;
     if constexpr (GENES_EARLY) {
 #pragma unroll
@@ -331,7 +330,6 @@ __device__ __forceinline__ void de_gen_body(const StepArgs &a, const GenArgs &e,
   }
 
   // ---- best: lowest index of the minimum cost
-  double bc = my_cost;
   uint32_t bi = r;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {

@@ -66,6 +66,22 @@ __device__ __forceinline__ void decode_node(double a, double b, uint32_t F,
   tau = th;
 }
 
+// The best individual is the one a scan in index order ends with that starts
+// from individual 0 and moves on when a cost is smaller: the lowest index of
+// the smallest cost, also where costs overflow to infinity (a large alpha times
+// its splits); a NaN (an infinite alpha times no split) is never smaller, and
+// nothing is smaller than a NaN it starts from.  argmin_key maps a cost to a
+// number that orders so; a place without an individual holds ARGMIN_NONE and an
+// index past the individuals, which loses every tie.
+constexpr double ARGMIN_NONE = __builtin_huge_val();
+__device__ __forceinline__ double argmin_key(double cost, uint32_t r) {
+  return cost == cost ? cost : (r == 0 ? -ARGMIN_NONE : ARGMIN_NONE);
+}
+// The cost behind the best individual's key.
+__device__ __forceinline__ double argmin_cost(double key) {
+  return key == -ARGMIN_NONE ? __builtin_nan("") : key;
+}
+
 // wave64 helpers
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 

@@ -18,15 +18,15 @@ __host__ __device__ __forceinline__ uint32_t align16u(uint32_t x) { return (x + 
 // (cost, index) of the wave's smallest cost, ties to the lower index: DPP
 // row shifts (1, 2, 4, 8) reduce each row of 16 lanes into its last lane,
 // two row broadcasts fold the four rows into lane 63, which is read back.
-// A lane with no source in a step sees the (largest cost, largest index)
-// sentinel, which never wins.
+// A lane with no source in a step sees (infinity, the largest index), which
+// never wins: an infinite cost has a lower index.
 __device__ __forceinline__ void wave_argmin(double &c, uint32_t &i) {
   auto step = [&](auto ctrl_tag, auto mask_tag) {
     constexpr int ctrl = decltype(ctrl_tag)::value, rmask = decltype(mask_tag)::value;
     const uint32_t lo = (uint32_t)__double2loint(c), hi = (uint32_t)__double2hiint(c);
-    const uint32_t nlo = (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFFu, (int)lo, ctrl,
+    const uint32_t nlo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, ctrl,
                                                                rmask, 0xF, false);
-    const uint32_t nhi = (uint32_t)__builtin_amdgcn_update_dpp((int)0x7FEFFFFFu, (int)hi, ctrl,
+    const uint32_t nhi = (uint32_t)__builtin_amdgcn_update_dpp((int)0x7FF00000u, (int)hi, ctrl,
                                                                rmask, 0xF, false);
     const uint32_t ni = (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFFu, (int)i, ctrl,
                                                               rmask, 0xF, false);

@@ -27,7 +27,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cfloat>
 #include <cstdio>
 #include <type_traits>
 #include <vector>
@@ -636,7 +635,7 @@ __global__ __launch_bounds__(H * WAVES * 64, H == 4 && !RES ? 4 : 1) void k_deoc
 
     // ---- best: lowest index of the minimum cost (both halves hold every
     // individual's cost; duplicates do not change the result)
-    double bc = live ? cost_r : DBL_MAX;
+    double bc = live ? argmin_key(cost_r, r) : ARGMIN_NONE;
     uint32_t bi = r;
     // (every group holds the same costs: the first group's waves reduce them)
     if (h == 0) {
@@ -674,7 +673,7 @@ __global__ __launch_bounds__(H * WAVES * 64, H == 4 && !RES ? 4 : 1) void k_deoc
       if (!pa.out_label) break;
       // one more pass counts the best tree alone (every lane holds it)
       bst_fin = bst;
-      cost_fin = bc;
+      cost_fin = argmin_cost(bc);
 #pragma unroll
       for (int j = 0; j < NA; ++j) {
         const int t = n_lo + j;

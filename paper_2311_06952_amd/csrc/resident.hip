@@ -30,7 +30,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cfloat>
 #include <cstdio>
 #include <type_traits>
 #include <vector>
@@ -555,7 +554,7 @@ __device__ __forceinline__ void resident_body(const ArgPtr pa, uint32_t bx, uint
     // costs: the first group's waves reduce them); the counters are cleared
     // for the next generation meanwhile
     if (h == 0) {
-      double bc = live ? cost_r : DBL_MAX;
+      double bc = live ? argmin_key(cost_r, r) : ARGMIN_NONE;
       uint32_t bi = r;
       wave_argmin(bc, bi);
       if ((threadIdx.x & 63u) == 0) {
@@ -592,7 +591,7 @@ __device__ __forceinline__ void resident_body(const ArgPtr pa, uint32_t bx, uint
       if (!pa->out_label) break;
       // one more pass counts the best tree alone (every lane holds it)
       bst_fin = bst;
-      cost_fin = bc;
+      cost_fin = argmin_cost(bc);
 #pragma unroll
       for (int j = 0; j < NA; ++j) {
         const int t = n_lo + j;
