@@ -346,7 +346,7 @@ struct WalkArgs {
   const uint32_t *tau;
   uint32_t P, D, F, K;
   uint32_t TG;      // trees per block
-  uint32_t per;     // samples per block (gridDim.x ranges), a multiple of 64
+  uint32_t per;     // samples per block (gridDim.x ranges), in units of 64
   uint32_t hist_in_lds;
   uint32_t vec4;  // rank columns readable as 16-byte chunks (aligned, ld % 4 == 0)
   uint32_t *leafcnt;  // [P][2^D][K]
@@ -370,9 +370,9 @@ __device__ __forceinline__ uint32_t walk_label(const WalkArgs &a, uint32_t j, ui
 __device__ __forceinline__ void walk_plain(const WalkArgs &a, uint32_t r0, uint32_t tg, uint32_t s0,
                                         uint32_t s1) {
   const uint32_t SB = (1u << a.D) - 1u, SL = 1u << a.D;
-  for (uint32_t j = s0 + threadIdx.x; j < s1; j += WT_THREADS) {
+  for (uint64_t j = (uint64_t)s0 + threadIdx.x; j < s1; j += WT_THREADS) {
     uint32_t i, w;
-    const uint32_t y = walk_label(a, j, i, w);
+    const uint32_t y = walk_label(a, (uint32_t)j, i, w);
     if (y == 0xFFu) continue;
     for (uint32_t g = 0; g < tg; ++g) {
       const size_t tr = (size_t)(r0 + g) * SB;
@@ -441,7 +441,9 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
   const uint32_t hist0 = lds0 + 4u * (uint32_t)(hist - wl);
   // the block's sample range (a multiple of 64, so that every tile starts at
   // a multiple of 4 samples for the 16-byte loads)
-  const uint32_t s0 = min(a.n_sub, blockIdx.x * a.per), s1 = min(a.n_sub, s0 + a.per);
+  const uint64_t per = 64ull * a.per;  // (64-bit: no wrap for counts near 2^32)
+  const uint32_t s0 = (uint32_t)min((uint64_t)a.n_sub, blockIdx.x * per);
+  const uint32_t s1 = (uint32_t)min((uint64_t)a.n_sub, s0 + per);
   if (!WIDE) {
     // (every wave finds the same, so the block leaves together)
     bool big = false;
@@ -495,8 +497,9 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
   }
   if (a.hist_in_lds)
     for (uint32_t e = threadIdx.x; e < tg * SL * K; e += WT_THREADS) hist[e] = 0;
-  for (uint32_t base = s0; base < s1; base += T) {
+  for (uint32_t base = s0, next; base < s1; base = next) {
     const uint32_t cnt = min(T, s1 - base);
+    next = base + cnt;
     __syncthreads();  // the previous tile (and the node set-up) is done
     if (threadIdx.x < T) {
       // a sample that is left out counts 0 times, in class 0
@@ -541,7 +544,7 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
       }
     }
     __syncthreads();
-    if (chunked && base + T < s1) prefetch(base + T);
+    if (chunked && next < s1) prefetch(next);
     const uint32_t y = ylab[i], w = wgt[i];
     if (__ballot(w != 0u) == 0ull) continue;  // (uniform over the wave; no barrier inside)
     const uint32_t y4 = hist0 + 4u * y;
@@ -619,11 +622,12 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
 }
 
 // How often each sample is named by idx (entries past n are invalid input).
+// (A launch takes fewer than 2^32 threads, a subset as many entries.)
 __global__ __launch_bounds__(256) void k_walk_weight(const uint32_t *__restrict__ idx,
                                                      uint32_t n_sub, uint32_t n,
                                                      uint32_t *__restrict__ weight) {
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n_sub && idx[j] < n) atomicAdd(&weight[idx[j]], 1u);
+  for (uint64_t j = blockIdx.x * 256ull + threadIdx.x; j < n_sub; j += gridDim.x * 256ull)
+    if (idx[j] < n) atomicAdd(&weight[idx[j]], 1u);
 }
 
 // Epilogue from leaf counts (walk path), any depth.  Block per tree: the
@@ -837,7 +841,8 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
       uint32_t *w = (uint32_t *)arena_get(ctx, "walk_weight", (size_t)ds->n * 4);
       if (w) {
         if (mh_status zs = launch_zero(ctx, {{w, (size_t)ds->n * 4}})) return zs;
-        k_walk_weight<<<(n_sub + 255) / 256, 256, 0, st>>>(idx, n_sub, ds->n, w);
+        const uint32_t blocks = (uint32_t)std::min<uint64_t>(((uint64_t)n_sub + 255) / 256, 1u << 16);
+        k_walk_weight<<<blocks, 256, 0, st>>>(idx, n_sub, ds->n, w);
         MH_LAUNCHED(ctx, "k_walk_weight");
         a.idx = nullptr;
         a.weight = w;
@@ -873,7 +878,7 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     // With a multiple of 8 ranges every block of one range is on the same XCD
     // (blocks go round-robin over the 8 XCDs in launch order), whose L2 then
     // serves the range's ranks to all groups but one; that saves 4 per column.
-    const uint32_t cus = (uint32_t)ctx->num_cu, units = (a.n_sub + 63) / 64;
+    const uint32_t cus = (uint32_t)ctx->num_cu, units = (uint32_t)(((uint64_t)a.n_sub + 63) / 64);
     const uint32_t g_min = (uint32_t)((P + TG - 1) / TG);
     uint32_t groups = g_min, ranges = 1;
     double best = 0;
@@ -900,8 +905,8 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     const size_t lds = tile_bytes + ((a.TG * tree_nodes + 7) & ~(size_t)7) +
                        (a.hist_in_lds ? a.TG * tree_hist : 0);
     const size_t lds_al = (lds + 15) & ~(size_t)15;
-    a.per = (units + ranges - 1) / ranges * 64;
-    ranges = (a.n_sub + a.per - 1) / a.per;
+    a.per = (units + ranges - 1) / ranges;
+    ranges = (units + a.per - 1) / a.per;
     // trees a lane walks at once
     const uint32_t gi = (a.TG + NG - 1) / NG;
     hipEvent_t e0, e1;

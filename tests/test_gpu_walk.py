@@ -125,3 +125,62 @@ def test_walk_wide_ranks(mh_mod):
 def mh_mod():
     import paper_2311_06952_amd as m
     return m
+
+
+def _near_limit_counts(n, tau, K=3):
+    """Leaf counts of a depth-6 tree over samples i < n with rank i % 64 and
+    label (i // 64) % 3."""
+    rows, tail = divmod(n, 64)
+    per_class = np.array([len(range(k, rows, K)) for k in range(K)], dtype=np.int64)
+    counts = np.zeros((64, K), dtype=np.int64)
+    for r in range(64):
+        t = 1
+        for _ in range(6):
+            t = 2 * t if r < tau[t - 1] else 2 * t + 1
+        counts[t - 64] += per_class
+        if r < tail:
+            counts[t - 64, rows % K] += 1
+    return counts
+
+
+@pytest.mark.parametrize("n", [2**32 - 4, 2**32 - 1021])
+def test_walk_sample_counts_near_the_32_bit_limit(n):
+    """The last ranges and tiles end within a tile of 2^32 samples (rows of
+    whole 16-byte chunks, and an odd row)."""
+    import torch
+
+    import paper_2311_06952_amd as mh
+    ranks = torch.arange(64, dtype=torch.int32, device="cuda").repeat(1 << 26)[:n].view(1, n)
+    labels = torch.arange(3, dtype=torch.uint8, device="cuda").repeat_interleave(64)
+    labels = labels.repeat((1 << 32) // 192 + 1)[:n]
+    ds = mh.Dataset(ranks, labels, torch.tensor([64], dtype=torch.int32, device="cuda"), n, 1, 3)
+    tau = np.random.default_rng(3).integers(0, 65, 63).astype(np.int32)
+    feat = torch.ones((1, 63), dtype=torch.uint8, device="cuda")
+    counts, correct, _, _ = mh.fitness_eval(ds, feat, torch.as_tensor(tau).cuda(), 6)
+    got = counts.cpu().numpy().view(np.uint32).astype(np.int64)[0]
+    del ranks, labels, ds
+    torch.cuda.empty_cache()
+    np.testing.assert_array_equal(got, _near_limit_counts(n, tau))
+    assert int(correct.cpu().numpy().view(np.uint32)[0]) == got.max(axis=1).sum()
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_walk_subset_near_the_32_bit_limit(static):
+    """A subset that names 2^20 samples 4,096 times, but for the last five."""
+    import torch
+
+    import paper_2311_06952_amd as mh
+    n, n_sub = 1 << 20, 2**32 - 5
+    ranks = (torch.arange(n, dtype=torch.int32, device="cuda") % 64).view(1, n).contiguous()
+    labels = (torch.arange(n, dtype=torch.int32, device="cuda") // 64 % 3).to(torch.uint8)
+    ds = mh.Dataset(ranks, labels, torch.tensor([64], dtype=torch.int32, device="cuda"), n, 1, 3)
+    idx = torch.arange(n, dtype=torch.int32, device="cuda").repeat(4096)[:n_sub]
+    tau = np.random.default_rng(4).integers(0, 65, 63).astype(np.int32)
+    feat = torch.ones((1, 63), dtype=torch.uint8, device="cuda")
+    counts, _, _, _ = mh.fitness_eval(ds, feat, torch.as_tensor(tau).cuda(), 6, idx=idx,
+                                      static=static)
+    got = counts.cpu().numpy().view(np.uint32).astype(np.int64)[0]
+    del idx
+    torch.cuda.empty_cache()
+    want = 4095 * _near_limit_counts(n, tau) + _near_limit_counts(n - 5, tau)
+    np.testing.assert_array_equal(got, want)
