@@ -384,7 +384,7 @@ typedef struct mh_server mh_server;
 typedef struct {
   uint64_t req_id;
   mh_status status;      /* MH_OK, MH_EINVAL when the request's X held a NaN, MH_EDEVICE
-                            when its cooperative launch gave up at a grid barrier,
+                            when the encoding of its data failed on the device,
                             MH_ECANCELED when it was cancelled (mh_server_cancel or the
                             time limit of mh_server_set_limits; tree then unset) */
   uint32_t n, F, K;
@@ -452,7 +452,8 @@ mh_status mh_server_footprint(uint32_t n, uint32_t F, uint32_t K, uint32_t D,
  * blocks bound a group), prepared by a launch for all of them, and one launch
  * takes their runs' blocks from a queue.  Requests that ran their
  * G generations get their best tree evaluated and copied to pinned host
- * memory.  At most a few rounds are in
+ * memory.  A request whose launch gave up at a grid barrier (its blocks did
+ * not all run at once) is queued again, first, and stepped.  At most a few rounds are in
  * flight on the device; a round waits for older ones as needed.  Stops
  * early when nothing is resident or queued.  *n_active / *n_queued (may be
  * NULL) receive the counts after the last round. */

@@ -100,9 +100,12 @@ bool coop_is_bad(const Ctx *ctx, const void *kern, uint32_t grid) {
   return false;
 }
 
+void coop_note_bad(Ctx *ctx, const void *kern, uint32_t grid) {
+  if (kern && !coop_is_bad(ctx, kern, grid)) ctx->coop_bad.push_back({kern, grid});
+}
+
 void coop_note_failure(Ctx *ctx) {
-  if (ctx->last_coop_kern && !coop_is_bad(ctx, ctx->last_coop_kern, ctx->last_coop_grid))
-    ctx->coop_bad.push_back({ctx->last_coop_kern, ctx->last_coop_grid});
+  coop_note_bad(ctx, ctx->last_coop_kern, ctx->last_coop_grid);
 }
 
 mh_status wait_stream(Ctx *ctx) {

@@ -127,7 +127,8 @@ hipError_t launch_grid_sync(Ctx *ctx, const void *kern, dim3 grid, dim3 block, v
                             size_t lds);
 // Whether (kern, grid) gave up at a grid barrier before in this context.
 bool coop_is_bad(const Ctx *ctx, const void *kern, uint32_t grid);
-// Records the last cooperative launch as one whose barrier gave up.
+// Records a launch, or the last one, as one whose barrier gave up.
+void coop_note_bad(Ctx *ctx, const void *kern, uint32_t grid);
 void coop_note_failure(Ctx *ctx);
 // Shape key bucket of a tile count: floor(log2(tiles per CU)) + 1 (0 for none).
 uint32_t tiles_bucket(uint32_t max_tiles, uint32_t num_cu);

@@ -152,6 +152,11 @@ struct Req {
   int ev_slot = -1;       // the slot whose event marks the packed result
   uint32_t nb_group = 0;  // blocks of its part of a group run (0: none)
   bool solo = false;  // solved whole by one cooperative launch at admission
+  // the launch that ran it whole, and whether a launch with grid barriers gave
+  // up on it: it is then solved again without any
+  const void *coop_kern = nullptr;
+  uint32_t coop_grid = 0;
+  bool redo = false;
   bool cancelled = false;  // by mh_server_cancel or the time limit
 
   template <typename T>
@@ -210,6 +215,8 @@ struct mh_server {
   // requests with at least this many tiles run whole as one cooperative
   // launch (0: never); MHDEOCT_SERVE_SOLO_TILES, default two per CU
   uint32_t solo_tiles = 0;
+  // a group's launch gave up at a grid barrier: no more groups
+  bool no_groups = false;
   // mh_server_set_limits: queued requests at most (0: no limit) and the
   // time from submission after which a request is cancelled (0: none)
   uint32_t max_queued = 0;
@@ -236,7 +243,7 @@ size_t desc_capacity(uint32_t max_slots, uint32_t num_cu) {
 // class counts in chunks; resident_shape) is the least; 0 where it does not
 // fit, or steps too long for a group.
 uint32_t group_blocks(const Ctx *c, const Req &q) {
-  if (!c->persist || !c->persist_resident || q.n == 0 || q.n > SMALL_MAX_N || q.prm.P > 128 ||
+  if (q.redo || !c->persist || !c->persist_resident || q.n == 0 || q.n > SMALL_MAX_N || q.prm.P > 128 ||
       q.prm.G > GROUP_MAX_G)
     return 0;
   const uint32_t SB = (1u << q.D) - 1u, waves = waves_for(q.prm.P);
@@ -255,6 +262,11 @@ uint32_t group_blocks(const Ctx *c, const Req &q) {
   return best;
 }
 
+// Whether a request runs whole at admission, by itself.
+bool runs_solo(const mh_server *s, const Req &q) {
+  return !q.redo && s->c->persist && s->solo_tiles && q.cv.max_tiles >= s->solo_tiles;
+}
+
 mh_status admit(mh_server *s, Req &q) {
   Ctx *c = s->c;
   hipStream_t st = c->stream;
@@ -262,7 +274,10 @@ mh_status admit(mh_server *s, Req &q) {
   uint32_t *ranks = (uint32_t *)arena_get(c, "srv_ranks", (size_t)q.F * ld * 4);
   if (!ranks) return MH_ENOMEM;
   uint32_t *nu = q.at<uint32_t>(q.cv.nu);
+  const bool rank_coop = c->rank_coop;
+  c->rank_coop = rank_coop && !q.redo;
   mh_status r = launch_rank_encode(c, q.X, q.n, q.F, ld, ranks, nu, q.at<uint32_t>(q.cv.nan));
+  c->rank_coop = rank_coop;
   if (r) return r;
   mh_dataset ds{q.n, q.F, q.K, ld, ranks, q.y, nu};
   r = launch_tile_build(c, &ds, nullptr, nullptr, q.n, 1, q.base + q.cv.tiles, q.cv.tile_bytes);
@@ -271,7 +286,7 @@ mh_status admit(mh_server *s, Req &q) {
   r = launch_de_init(c, q.prm.P, q.D, q.F, q.prm.seed, nullptr, 0, 1, nullptr, 0,
                      q.at<double>(q.cv.pop), true);
   if (r) return r;
-  if (c->persist && s->solo_tiles && q.cv.max_tiles >= s->solo_tiles) {
+  if (runs_solo(s, q)) {
     // a request that fills the device by itself: its whole run as one
     // cooperative launch (the plain form's kernel), finished at admission
     const PersistFinal fin{q.at<uint8_t>(q.cv.f1), q.at<uint32_t>(q.cv.t1),
@@ -283,6 +298,8 @@ mh_status admit(mh_server *s, Req &q) {
                              q.at<uint32_t>(q.cv.best), q.at<uint32_t>(q.cv.err), &fin, &used);
     if (r) return r;
     if (used) {
+      q.coop_kern = c->last_coop_kern;
+      q.coop_grid = c->last_coop_grid;
       q.solo = true;
       q.g = q.prm.G + 1;
       return MH_OK;
@@ -330,12 +347,16 @@ mh_status retire(mh_server *s, Req &q) {
 }
 
 // Moves requests whose packed result has landed to the done list.  With
-// `wait`, blocks on the oldest one first.
+// `wait`, blocks on the oldest one first.  A request whose blocks did not all
+// run at once (its run, or the encoding of its data, gave up at a grid barrier)
+// goes back to the head of the queue, to be stepped by launches without
+// barriers: its result does not depend on the launch form.
 mh_status collect(mh_server *s, bool wait) {
   Ctx *c = s->c;
   if (wait && !s->retiring.empty())
     MH_HIP(c, hipEventSynchronize(s->slot_ev[s->retiring.front().ev_slot]));
   size_t kept = 0;
+  std::vector<Req> again;
   for (size_t i = 0; i < s->retiring.size(); ++i) {
     Req &q = s->retiring[i];
     const hipError_t e = hipEventQuery(s->slot_ev[q.ev_slot]);
@@ -346,6 +367,18 @@ mh_status collect(mh_server *s, bool wait) {
     }
     if (e != hipSuccess) return hip_fail(c, e, "hipEventQuery");
     const ResultOut &o = s->pinned[q.slot];
+    if (o.flag && !(o.flag & 2u) && !q.cancelled && !q.redo) {
+      if (o.flag & 1u) {
+        coop_note_bad(c, q.coop_kern, q.coop_grid);
+        s->no_groups = s->no_groups || q.nb_group;
+      }
+      s->free_slots.push_back(q.slot);
+      q.redo = true;
+      q.solo = false;
+      q.nb_group = 0;
+      again.push_back(q);
+      continue;
+    }
     mh_result res;
     std::memset(&res, 0, sizeof(res));
     res.req_id = q.id;
@@ -368,6 +401,7 @@ mh_status collect(mh_server *s, bool wait) {
     s->free_slots.push_back(q.slot);
   }
   s->retiring.resize(kept);
+  s->queue.insert(s->queue.begin(), again.begin(), again.end());
   return MH_OK;
 }
 
@@ -501,6 +535,8 @@ mh_status group_run(mh_server *s, std::vector<Req> &g, bool *used) {
   if (r) return r;
   MH_HIP(c, hipEventRecord(s->slot_ev[g[0].slot], st));
   for (Req &q : g) {
+    q.coop_kern = c->last_coop_kern;
+    q.coop_grid = c->last_coop_grid;
     q.solo = true;
     q.g = q.prm.G + 1;
     q.ev_slot = g[0].slot;
@@ -650,11 +686,6 @@ void drop_cancelled(mh_server *s) {
   s->active.resize(kept);
 }
 
-// Whether a queued request will run whole at admission.
-bool c_solo(const mh_server *s, const Req &q) {
-  return s->c->persist && s->solo_tiles && q.cv.max_tiles >= s->solo_tiles;
-}
-
 mh_status round_once(mh_server *s) {
   drop_cancelled(s);
   mh_status r = collect(s, s->active.empty() && s->queue.empty());
@@ -668,9 +699,9 @@ mh_status round_once(mh_server *s) {
   size_t group_ranks = 0;
   while (!s->queue.empty() && !s->free_slots.empty()) {
     Req &q = s->queue.front();
-    const bool solo = c_solo(s, q);
+    const bool solo = runs_solo(s, q);
     if (solo && (solo_run || !group.empty())) break;
-    if (!solo && !solo_run && s->solo_tiles) {
+    if (!solo && !solo_run && s->solo_tiles && !s->no_groups) {
       const uint32_t nb = group_blocks(s->c, q);
       if (nb) {
         const size_t rb = (size_t)q.F * std::max(256u, (q.n + 255u) & ~255u) * 4;

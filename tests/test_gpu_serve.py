@@ -223,3 +223,34 @@ def test_server_cancel_and_time_limit(mh, monkeypatch):
     _same(res[31]["tree"], oracle_tree(31, 2000, 4, 2, 2, 16, 6))
     srv.close()
     ctx.close()
+
+
+def test_server_barrier_give_up_recovery(mh, monkeypatch):
+    """Grid barriers that give up (forced from the host with a zero time limit,
+    so that waits end at once) fail no request: runs in a group, a
+    whole-request run and a request whose rank encoding has a barrier are
+    solved again without one; and so are requests that come later."""
+    from paper_2311_06952_amd import capi
+    reqs = [(40, 20_000, 4, 2, 5, 128, 6, 0.5),    # several blocks in a group
+            (41, 18_000, 6, 3, 4, 100, 6, -1.0),
+            (42, 700, 4, 2, 2, 32, 6, 0.5),        # one block: no barrier
+            (43, 40_000, 6, 3, 3, 64, 5, 0.5),     # a whole-request run
+            (44, 20_000, 5, 3, 3, 300, 5, 0.5)]    # stepped from the start
+    late = [(45, 20_000, 5, 4, 5, 100, 6, 0.5), (46, 50_000, 5, 3, 3, 40, 5, 0.5)]
+    monkeypatch.setenv("MHDEOCT_WAIT_TICKS", "0")
+    ctx = capi.Context(0)
+    srv = mh.Server(1 << 30, 4, ctx=ctx)
+    for r in reqs:
+        _submit(mh, srv, r)
+    res = {r["req_id"]: r for r in srv.drain()}
+    for r in late:
+        _submit(mh, srv, r)
+    res.update({r["req_id"]: r for r in srv.drain()})
+    srv.close()
+    ctx.close()
+    for rid, n, F, K, D, P, G, M in reqs + late:
+        assert res[rid]["status"] == 0
+        X, y = _data(rid, n, F, K)
+        want = oracle.deoct(oracle.dataset_from_X(X, y, K), D,
+                            oracle.de_params(P, G, M, 0.9, 7000 + rid))
+        _same(res[rid]["tree"], want)
