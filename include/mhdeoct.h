@@ -398,9 +398,10 @@ typedef struct {
  * memory are allocated once, here, as the pool that holds the resident
  * state of admitted requests (tile layout, population, counters); the
  * context's arena additionally holds the rank-encoding scratch of the
- * largest request, or of a group of small ones (up to 256 MiB).  At most max_slots (1..256) requests are resident at a
- * time.  The context must not be used for other calls while the server
- * exists (they would share its stream and arena). */
+ * largest request, or the ranks and counters of a group of small ones (up to
+ * 256 MiB).  At most max_slots (1..256) requests are resident at a time.  The
+ * context must not be used for other calls while the server exists (they
+ * would share its stream and arena). */
 mh_status mh_server_create(mh_ctx *ctx, uint64_t hbm_budget, uint32_t max_slots,
                            mh_server **out);
 /* Waits for the server's queued work and frees its pool. */

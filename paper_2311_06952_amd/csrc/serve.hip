@@ -180,7 +180,9 @@ constexpr uint32_t GROUP_MAX_G = 2000;
 // Blocks of a group's runs, at most, per CU: a resident request that is stepped
 // waits for a group between two of its generations.
 constexpr uint32_t GROUP_ROUNDS = 4;
-constexpr size_t GROUP_MAX_RANK_BYTES = size_t(256) << 20;
+// Arena bytes of a group, at most: the ranks of its requests and the counters
+// of those that run on several blocks (one block counts in its LDS).
+constexpr size_t GROUP_MAX_BYTES = size_t(256) << 20;
 
 uint32_t waves_for(uint32_t P) {
   uint32_t w = pad64(P) / 64;
@@ -238,6 +240,15 @@ size_t desc_capacity(uint32_t max_slots, uint32_t num_cu) {
   return std::max(5 * per, group);
 }
 
+uint32_t rank_ld(uint32_t n) { return std::max(256u, (n + 255u) & ~255u); }
+// Words of a request's counters in a group run of nb blocks.
+size_t group_cnt_words(const Req &q, uint32_t nb) {
+  return nb > 1 ? 3 * (size_t)((1u << q.D) - 1u) * q.K * pad64(q.prm.P) : 0;
+}
+size_t group_bytes(const Req &q, uint32_t nb) {
+  return ((size_t)q.F * rank_ld(q.n) + group_cnt_words(q, nb)) * 4;
+}
+
 // Blocks of a request in a group run: the number for which blocks times the
 // generation's cycles (its searches, the exchange between its blocks, the
 // class counts in chunks; resident_shape) is the least; 0 where it does not
@@ -270,7 +281,7 @@ bool runs_solo(const mh_server *s, const Req &q) {
 mh_status admit(mh_server *s, Req &q) {
   Ctx *c = s->c;
   hipStream_t st = c->stream;
-  const uint32_t ld = std::max(256u, (q.n + 255u) & ~255u);
+  const uint32_t ld = rank_ld(q.n);
   uint32_t *ranks = (uint32_t *)arena_get(c, "srv_ranks", (size_t)q.F * ld * 4);
   if (!ranks) return MH_ENOMEM;
   uint32_t *nu = q.at<uint32_t>(q.cv.nu);
@@ -424,16 +435,19 @@ mh_status group_run(mh_server *s, std::vector<Req> &g, bool *used) {
     blocks += sh[i].nblk;
     lds = std::max(lds, sh[i].lds);
     P_max = std::max(P_max, q.prm.P);
-    rank_words += (size_t)q.F * std::max(256u, (q.n + 255u) & ~255u);
-    cnt_words += 3 * (size_t)((1u << q.D) - 1u) * q.K * pad64(q.prm.P);
-    bar_words += barrier_words(sh[i].nblk);
+    rank_words += (size_t)q.F * rank_ld(q.n);
+    cnt_words += group_cnt_words(q, sh[i].nblk);
+    bar_words += sh[i].nblk > 1 ? barrier_words(sh[i].nblk) : 0u;
   }
   uint32_t *ranks = (uint32_t *)arena_get(c, "srv_ranks", rank_words * 4);
   uint32_t *cnt = (uint32_t *)arena_get(c, "srv_cnt", cnt_words * 4);
   uint32_t *bar = (uint32_t *)arena_get(c, "srv_bar", (size_t)bar_words * 4);
   uint32_t *flags = (uint32_t *)arena_get(c, "srv_flags", (size_t)s->max_slots * 8 + 4);
   double *xcost = (double *)arena_get(c, "srv_xcost", (size_t)s->max_slots * 128 * 8);
-  if (!ranks || !cnt || !bar || !flags || !xcost) return MH_ENOMEM;
+  if (!ranks || !cnt || !bar || !flags || !xcost) {
+    (void)hipGetLastError();  // no room for a group: its requests are stepped
+    return MH_OK;
+  }
   std::vector<SmallJob> jobs(cnt_n);
   std::vector<RunArgs> runs(cnt_n);
   const size_t o_runs = align256(cnt_n * sizeof(SmallJob)),
@@ -462,7 +476,7 @@ mh_status group_run(mh_server *s, std::vector<Req> &g, bool *used) {
     j.n = j.n_sub = q.n;
     j.F = q.F;
     j.K = q.K;
-    j.ld = std::max(256u, (q.n + 255u) & ~255u);
+    j.ld = rank_ld(q.n);
     j.P = q.prm.P;
     j.SB = SB;
     RunArgs &a = runs[i];
@@ -510,8 +524,8 @@ mh_status group_run(mh_server *s, std::vector<Req> &g, bool *used) {
     for (uint32_t b = 0; b < a.nblk; ++b) map[blk + b] = i;
     blk += a.nblk;
     ro += (size_t)q.F * j.ld;
-    co += 3 * (size_t)SB * q.K * pad64(q.prm.P);
-    bo += barrier_words(a.nblk);
+    co += group_cnt_words(q, a.nblk);
+    bo += a.nblk > 1 ? barrier_words(a.nblk) : 0u;
   }
   std::memcpy(host, jobs.data(), cnt_n * sizeof(SmallJob));
   std::memcpy(host + o_runs, runs.data(), cnt_n * sizeof(RunArgs));
@@ -696,7 +710,7 @@ mh_status round_once(mh_server *s) {
   bool solo_run = false;
   std::vector<Req> group;
   uint32_t group_blk = 0;
-  size_t group_ranks = 0;
+  size_t group_mem = 0;
   while (!s->queue.empty() && !s->free_slots.empty()) {
     Req &q = s->queue.front();
     const bool solo = runs_solo(s, q);
@@ -704,9 +718,10 @@ mh_status round_once(mh_server *s) {
     if (!solo && !solo_run && s->solo_tiles && !s->no_groups) {
       const uint32_t nb = group_blocks(s->c, q);
       if (nb) {
-        const size_t rb = (size_t)q.F * std::max(256u, (q.n + 255u) & ~255u) * 4;
-        if ((!group.empty() && group_blk + nb > GROUP_ROUNDS * (uint32_t)s->c->num_cu) ||
-             group_ranks + rb > GROUP_MAX_RANK_BYTES) break;
+        const size_t mem = group_bytes(q, nb);
+        if (!group.empty() && (group_blk + nb > GROUP_ROUNDS * (uint32_t)s->c->num_cu ||
+                               group_mem + mem > GROUP_MAX_BYTES))
+          break;
         size_t off = 0;
         if (!s->pool.alloc(q.cv.total, &off)) break;
         q.off = off;
@@ -717,7 +732,7 @@ mh_status round_once(mh_server *s) {
         q.g = 0;
         q.nb_group = nb;
         group_blk += nb;
-        group_ranks += rb;
+        group_mem += mem;
         group.push_back(q);
         s->queue.pop_front();
         continue;

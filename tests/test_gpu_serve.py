@@ -254,3 +254,31 @@ def test_server_barrier_give_up_recovery(mh, monkeypatch):
         want = oracle.deoct(oracle.dataset_from_X(X, y, K), D,
                             oracle.de_params(P, G, M, 0.9, 7000 + rid))
         _same(res[rid]["tree"], want)
+
+
+def test_server_group_scratch_is_bounded(mh):
+    """A group's scratch outside the server's budget stays within the stated
+    256 MiB whatever its requests' classes and depth: 256 requests on a few
+    blocks each, whose counters take 5.8 MB each."""
+    import torch
+    from paper_2311_06952_amd import capi
+    n, F, K, D, P = 100, 1, 254, 5, 3
+    X, y = synth.random_small(1, n, F, K)
+    Xd, yd = torch.as_tensor(X).cuda(), torch.as_tensor(y).cuda()
+    foot = mh.server_footprint(n, F, K, D, P)
+    ctx = capi.Context(0)
+    srv = mh.Server(256 * foot, 256, ctx=ctx)
+    before = torch.cuda.mem_get_info()[0]
+    for i in range(256):
+        srv.submit(i, Xd, yd, K, D, mh.de_params(P, 2, 0.5, 0.9, i % 3))
+    res = {r["req_id"]: r for r in srv.drain()}
+    used = before - torch.cuda.mem_get_info()[0]
+    srv.close()
+    ctx.close()
+    assert used <= (256 + 32) << 20  # (and allocation granularity)
+    ods = oracle.dataset_from_X(X, y, K)
+    for s in range(3):
+        want = oracle.deoct(ods, D, oracle.de_params(P, 2, 0.5, 0.9, s))
+        for i in range(s, 256, 3):
+            assert res[i]["status"] == 0
+            _same(res[i]["tree"], want)
