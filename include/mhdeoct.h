@@ -447,7 +447,8 @@ mh_status mh_server_footprint(uint32_t n, uint32_t F, uint32_t K, uint32_t D,
  * generation.  A request whose tile layout has at least two tiles per CU
  * (about 32,000 samples on 256 CUs; MHDEOCT_SERVE_SOLO_TILES sets the tile
  * count, 0 never) fills the device by itself: it runs whole at admission as
- * one cooperative launch, the plain form's kernel.  Small requests (P <= 128,
+ * one cooperative launch, the plain form's kernel, or, where the plain form
+ * runs kernels per generation, a few dozen generations a round by those.  Small requests (P <= 128,
  * at most 22,528 samples) run whole as well, in groups: the ones at the head
  * of the queue are admitted together (pool, slots and four times the CUs'
  * blocks bound a group), prepared by a launch for all of them, and one launch

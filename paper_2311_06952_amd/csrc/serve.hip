@@ -21,7 +21,8 @@
 //    individual and pack the result into pinned host memory, followed by an
 //    event.
 // Two kinds of requests are not stepped.  One that fills the device by itself
-// runs whole at admission as one launch.  Small ones (up to SMALL_MAX_N
+// runs whole at admission as one launch (or, where its shape is left to the
+// per-generation kernels, WHOLE_BURST generations a round).  Small ones (up to SMALL_MAX_N
 // samples, 128 individuals) are admitted in groups: as many from the head of
 // the queue as a few rounds of the CUs hold are prepared in one launch, run
 // whole in another, each on its own blocks with its tiles resident in LDS, the
@@ -157,6 +158,7 @@ struct Req {
   const void *coop_kern = nullptr;
   uint32_t coop_grid = 0;
   bool redo = false;
+  bool bursts = false;  // steps WHOLE_BURST generations a round
   bool cancelled = false;  // by mh_server_cancel or the time limit
 
   template <typename T>
@@ -175,6 +177,13 @@ struct Req {
 constexpr int RING = 4;           // rounds whose descriptors may be in flight
 constexpr uint32_t MAX_SLOTS = 256;
 
+// A request that fills the device but whose shape the whole-run kernels leave to
+// the per-generation ones (launch_deoct_persist) steps this many generations a
+// round by itself: one generation a round, in the launches of all requests with
+// their descriptor upload and one-block DE step, took n = 63,000, F = 4, depth 5,
+// P = 184, G = 46 4.3 ms, this form 2.3; n = 973,000, F = 8, depth 5, P = 198,
+// G = 29 8.6 and 5.3.
+constexpr uint32_t WHOLE_BURST = 32;
 // A group run holds the stream until its longest request is done.
 constexpr uint32_t GROUP_MAX_G = 2000;
 // Blocks of a group's runs, at most, per CU: a resident request that is stepped
@@ -315,6 +324,7 @@ mh_status admit(mh_server *s, Req &q) {
       q.g = q.prm.G + 1;
       return MH_OK;
     }
+    q.bursts = true;
   }
   return launch_decode(c, q.at<double>(q.cv.pop), q.prm.P, q.D, q.F, nu, q.at<uint8_t>(q.cv.feat),
                        q.at<uint32_t>(q.cv.tau), 1, nullptr, true);
@@ -561,6 +571,30 @@ mh_status group_run(mh_server *s, std::vector<Req> &g, bool *used) {
   return MH_OK;
 }
 
+// The next generations of a request that fills the device by itself.
+mh_status burst(mh_server *s, Req &q) {
+  Ctx *c = s->c;
+  const int k = (int)(s->rounds % RING);
+  if (s->ring_used[k]) MH_HIP(c, hipEventSynchronize(s->ring_ev[k]));
+  const uint32_t g1 = std::min(q.prm.G + 1, q.g + WHOLE_BURST);
+  for (; q.g < g1; ++q.g) {
+    mh_status r = launch_fitness_count(c, q.base + q.cv.tiles, q.F, q.K, q.n, 1, q.cv.max_tiles,
+                                       q.at<uint8_t>(q.cv.feat), q.at<uint32_t>(q.cv.tau),
+                                       q.prm.P, q.D, q.at<uint32_t>(q.cv.cnt), nullptr);
+    if (r) return r;
+    r = launch_de_gen(c, q.de(), nullptr, 0, 1, q.g + 1, q.g == 0, q.at<double>(q.cv.pop),
+                      q.at<double>(q.cv.cost), q.at<double>(q.cv.trial), q.at<uint32_t>(q.cv.best),
+                      q.g < q.prm.G ? q.at<double>(q.cv.trial) : nullptr, q.at<uint8_t>(q.cv.feat),
+                      q.at<uint32_t>(q.cv.tau), q.at<uint32_t>(q.cv.cnt), q.ctot(), q.K,
+                      q.prm.n_min, q.prm.alpha);
+    if (r) return r;
+  }
+  MH_HIP(c, hipEventRecord(s->ring_ev[k], c->stream));
+  s->ring_used[k] = true;
+  s->rounds += 1;
+  return MH_OK;
+}
+
 // One generation of every active request: per depth, a fitness launch over
 // all of them and a DE launch with a block per request.
 mh_status generation(mh_server *s) {
@@ -578,7 +612,7 @@ mh_status generation(mh_server *s) {
   for (uint32_t D = 1; D <= 5; ++D) {
     std::vector<Req *> js;
     for (Req &q : s->active)
-      if (q.D == D && q.g <= q.prm.G) js.push_back(&q);
+      if (q.D == D && q.g <= q.prm.G && !q.bursts) js.push_back(&q);
     if (js.empty()) continue;
     Launch L{D, 0, 0, 0, (uint32_t)js.size(), 0, 0, 0, 0};
     uint64_t tiles = 0;
@@ -644,7 +678,7 @@ mh_status generation(mh_server *s) {
     if (r) return r;
   }
   for (Req &q : s->active)
-    if (q.g <= q.prm.G) q.g += 1;
+    if (q.g <= q.prm.G && !q.bursts) q.g += 1;
   return MH_OK;
 }
 
@@ -765,6 +799,9 @@ mh_status round_once(mh_server *s) {
   }
   r = generation(s);
   if (r) return r;
+  for (Req &q : s->active)
+    if (q.bursts && q.g <= q.prm.G)
+      if ((r = burst(s, q))) return r;
   // requests past their last generation: pack the result, free the pool block
   // (later work on the stream may reuse it; the result copy is queued first)
   size_t kept = 0;

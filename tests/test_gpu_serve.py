@@ -282,3 +282,30 @@ def test_server_group_scratch_is_bounded(mh):
         for i in range(s, 256, 3):
             assert res[i]["status"] == 0
             _same(res[i]["tree"], want)
+
+
+def test_served_large_requests_left_to_the_per_generation_kernels(mh):
+    """Requests that fill the device and whose shape no whole-run kernel takes
+    (depth 5 with more than 128 individuals, depth 4 with many tiles): bursts
+    of generations around their length, beside a stepped one and one that is
+    cancelled between two bursts."""
+    from paper_2311_06952_amd import capi
+    reqs = [(70, 36_000, 3, 2, 5, 130, 31, 0.5), (71, 33_000, 4, 3, 5, 200, 32, -1.0),
+            (72, 40_000, 3, 3, 5, 256, 3, 0.5), (73, 550_000, 4, 3, 4, 130, 5, 0.5),
+            (74, 3000, 5, 3, 3, 300, 20, 0.5), (75, 36_000, 3, 2, 5, 300, 4000, 0.5)]
+    ctx = capi.Context(0)
+    srv = mh.Server(1 << 30, 8, ctx=ctx)
+    for r in reversed(reqs):
+        _submit(mh, srv, r)
+    srv.pump(3)
+    srv.cancel(75)
+    res = {r["req_id"]: r for r in srv.drain()}
+    srv.close()
+    ctx.close()
+    assert res[75]["status"] == capi.MH_ECANCELED and res[75]["t_admit_ns"] > 0
+    for rid, n, F, K, D, P, G, M in reqs[:-1]:
+        assert res[rid]["status"] == 0
+        X, y = _data(rid, n, F, K)
+        want = oracle.deoct(oracle.dataset_from_X(X, y, K), D,
+                            oracle.de_params(P, G, M, 0.9, 7000 + rid))
+        _same(res[rid]["tree"], want)
