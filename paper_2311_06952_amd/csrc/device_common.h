@@ -77,9 +77,14 @@ constexpr double ARGMIN_NONE = __builtin_huge_val();
 __device__ __forceinline__ double argmin_key(double cost, uint32_t r) {
   return cost == cost ? cost : (r == 0 ? -ARGMIN_NONE : ARGMIN_NONE);
 }
-// The cost behind the best individual's key.
-__device__ __forceinline__ double argmin_cost(double key) {
-  return key == -ARGMIN_NONE ? __builtin_nan("") : key;
+// Inside a run a NaN comes from an infinite alpha alone, and every cost is then
+// infinite or NaN: as infinities the lowest index wins.  (One instruction; the
+// test for index 0 in the whole-run kernels slowed a generation by 6 %.)
+__device__ __forceinline__ double run_key(double cost) { return __builtin_fmin(cost, ARGMIN_NONE); }
+// The cost behind the best individual's run_key.
+__device__ __forceinline__ double run_cost(double key, double alpha, uint32_t splits) {
+  const double penalty = __dmul_rn(alpha, (double)splits);
+  return penalty == penalty ? key : penalty;
 }
 
 // wave64 helpers

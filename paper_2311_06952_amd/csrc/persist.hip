@@ -566,7 +566,7 @@ __global__ __launch_bounds__(H * WAVES * 64, H == 4 && !RES ? 4 : 1) void k_deoc
           pa.out_tau[t] = th;
         }
         *pa.out_correct = correct;
-        *pa.out_cost = cost_fin;
+        *pa.out_cost = run_cost(cost_fin, pa.alpha, nsplit);
       }
       break;
     }
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(H * WAVES * 64, H == 4 && !RES ? 4 : 1) void k_deoc
 
     // ---- best: lowest index of the minimum cost (both halves hold every
     // individual's cost; duplicates do not change the result)
-    double bc = live ? argmin_key(cost_r, r) : ARGMIN_NONE;
+    double bc = live ? run_key(cost_r) : ARGMIN_NONE;
     uint32_t bi = r;
     // (every group holds the same costs: the first group's waves reduce them)
     if (h == 0) {
@@ -673,7 +673,7 @@ __global__ __launch_bounds__(H * WAVES * 64, H == 4 && !RES ? 4 : 1) void k_deoc
       if (!pa.out_label) break;
       // one more pass counts the best tree alone (every lane holds it)
       bst_fin = bst;
-      cost_fin = argmin_cost(bc);
+      cost_fin = bc;
 #pragma unroll
       for (int j = 0; j < NA; ++j) {
         const int t = n_lo + j;

@@ -396,7 +396,7 @@ __device__ __forceinline__ void resident_body(const ArgPtr pa, uint32_t bx, uint
         __syncthreads();
         if (threadIdx.x == 0) {
           *pa->out_correct = s_cor[0];
-          *pa->out_cost = cost_fin;
+          *pa->out_cost = run_cost(cost_fin, pa->alpha, s_spl[0]);
         }
       }
       break;
@@ -554,7 +554,7 @@ __device__ __forceinline__ void resident_body(const ArgPtr pa, uint32_t bx, uint
     // costs: the first group's waves reduce them); the counters are cleared
     // for the next generation meanwhile
     if (h == 0) {
-      double bc = live ? argmin_key(cost_r, r) : ARGMIN_NONE;
+      double bc = live ? run_key(cost_r) : ARGMIN_NONE;
       uint32_t bi = r;
       wave_argmin(bc, bi);
       if ((threadIdx.x & 63u) == 0) {
@@ -591,7 +591,7 @@ __device__ __forceinline__ void resident_body(const ArgPtr pa, uint32_t bx, uint
       if (!pa->out_label) break;
       // one more pass counts the best tree alone (every lane holds it)
       bst_fin = bst;
-      cost_fin = argmin_cost(bc);
+      cost_fin = bc;
 #pragma unroll
       for (int j = 0; j < NA; ++j) {
         const int t = n_lo + j;
