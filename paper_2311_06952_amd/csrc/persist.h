@@ -86,9 +86,12 @@ struct RunShape {
   bool split = false;  // costs shared out over the blocks (needs RunArgs::xcost)
 };
 // resident_shape: the number of blocks (up to max_blocks) expected to be the
-// fastest; resident_fit: nb blocks, if the run fits them.
+// fastest, none where another form is, for at most `tiles` tiles, likely
+// tiles_likely; resident_fit: nb blocks, if the run fits them; resident_cycles:
+// the expected cycles of a generation.
 RunShape resident_shape(const Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K,
-                        uint32_t tiles, uint32_t max_blocks);
+                        uint32_t tiles, uint32_t tiles_likely, uint32_t max_blocks);
+double resident_cycles(uint32_t D, uint32_t P, uint32_t K, const RunShape &r, uint32_t tiles);
 RunShape resident_fit(const Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K,
                       uint32_t tiles, uint32_t nb);
 // Launches runs of one depth and one population width (P padded to a power of

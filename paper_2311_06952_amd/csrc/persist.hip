@@ -943,9 +943,14 @@ mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint
   const uint32_t max_tiles = tile_layout(n_sub, F, K, n_problems).max_tiles;
   std::vector<RunShape> sh(n_problems);
   auto tiles_of = [&](uint32_t i) { return ptiles ? (*ptiles)[i] : max_tiles; };
+  // (the bound counts a ragged tile for every class: half of a tile each,
+  // likely, and a tile at least)
+  auto likely = [&](uint32_t i) {
+    return ptiles ? (*ptiles)[i] : std::max(std::min(K, n_sub), max_tiles - K / 2);
+  };
   uint64_t total = 0, all_tiles = 0;
   for (uint32_t i = 0; i < n_problems; ++i) {
-    sh[i] = resident_shape(ctx, D, P, F, K, tiles_of(i), cus);
+    sh[i] = resident_shape(ctx, D, P, F, K, tiles_of(i), likely(i), cus);
     if (!sh[i].nblk) return MH_OK;
     total += sh[i].nblk;
     all_tiles += tiles_of(i);
@@ -954,7 +959,7 @@ mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint
     for (uint32_t i = 0; i < n_problems; ++i) {
       const uint64_t room = cus - n_problems;
       const uint32_t nb = 1u + (uint32_t)(all_tiles ? room * tiles_of(i) / all_tiles : 0);
-      sh[i] = resident_shape(ctx, D, P, F, K, tiles_of(i), nb);
+      sh[i] = resident_shape(ctx, D, P, F, K, tiles_of(i), likely(i), nb);
       if (!sh[i].nblk) return MH_OK;
     }
   }

@@ -18,7 +18,7 @@
 //  - costs: a group scores its share of the last-level nodes' leaf pairs;
 //  - mutation, crossover and decode: group h makes the nodes h NA ...
 // With one block there is no exchange at all: the LDS counters are the counts.
-// The number of blocks follows the tiles (resident_blocks).
+// The number of blocks follows the tiles (resident_shape).
 //
 // Against the form of two groups per block with all of a tree's nodes unrolled
 // in each thread (a generation's cycles at n = 3 10^4, F = 13, K = 5, depth 5,
@@ -730,35 +730,62 @@ RunShape resident_fit(const Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32
   return r;
 }
 
+// Cycles of a generation of a run of the given shape (2.4 GHz) over `tiles`
+// tiles, by the parts that a block works through one after another: its
+// group's nodes (mutation, crossover, decode), its searches (33 cycles of a CU's
+// LDS each), its leaf scores, and with several blocks the exchange.  Against
+// 7,900 measured runs (n = 300 to 16,000, F = 2 to 20, K = 2 to 40, depth 1 to 5,
+// P = 8 to 512, 1 to 256 blocks): 4 % too long on average, standard deviation 12 %.
+double resident_cycles(uint32_t D, uint32_t P, uint32_t K, const RunShape &r, uint32_t tiles) {
+  const uint32_t SB = (1u << D) - 1u, LN = 1u << (D - 1), w = waves_of(P), H = 16 / w;
+  const uint32_t per = std::max(1u, (tiles + r.nblk - 1) / r.nblk);
+  const double searches = D < 4 ? SB : (D == 4 ? 16 : (H >= 4 ? 36 : 32));  // of a tile and wave
+  double t = 900.0 + 770.0 * D + 500.0 * w + 3700.0 * ((SB + H - 1) / H) + 33.0 * per * w * searches;
+  if (!r.split) t += 100.0 * K * ((LN + H - 1) / H) * D;
+  if (r.split) t += 16600.0 - 47.0 * std::min(r.nblk, 128u);  // (a block scores P / nblk)
+  else if (r.nblk > 1) t += (r.slots < K ? 14000.0 : w == 1 && D > 3 ? 7500.0 : 6000.0) + 12.0 * r.nblk;
+  return t;
+}
+
+// The same of the form with all of a tree's nodes in a thread's registers and
+// few tiles per block (persist.hip): standard deviation 10 % over 590 runs.
+static double unrolled_cycles(uint32_t D, uint32_t P, uint32_t K) {
+  const uint32_t SB = (1u << D) - 1u, w = waves_of(P), H = w <= 4 ? 2 : 1;
+  return 8100.0 - 1220.0 * D + 130.0 * w + 280.0 * SB + 2430.0 * ((SB + H - 1) / H) + 80.0 * SB * K;
+}
+
 RunShape resident_shape(const Ctx *ctx, uint32_t D, uint32_t P, uint32_t F, uint32_t K,
-                        uint32_t tiles, uint32_t max_blocks) {
+                        uint32_t tiles, uint32_t tiles_likely, uint32_t max_blocks) {
+  // Several blocks only where the groups are many: up to 128 individuals (eight
+  // groups), from depth 3 on.  Elsewhere two groups per block with all of a
+  // tree's nodes in registers (persist.hip) are as fast or faster.  Per
+  // generation, there against here: n = 5 10^4, F = 21, P = 100, depth 3: 9.5
+  // and 8.6 us; n = 5000, F = 10, P = 128, depth 3: 7.5 and 7.2; n = 2000, F =
+  // 20, P = 100, depth 1: 4.0 and 4.9; n = 4000, F = 4, P = 128, depth 2: 5.0 and
+  // 5.4; n = 10^5, F = 16, P = 256, depth 3: 10.4 and 10.8; n = 2 10^4, F = 8, P =
+  // 512, depth 3: 11.5 and 13.3.  At depth 1 its several blocks per CU get in
+  // each other's way when they add to few classes' counters: n = 6.4 10^4, F =
+  // 4, K = 2, P = 128 6.1 and 5.3, n = 3.2 10^4, F = 12, K = 3, P = 64 6.6 and 4.7,
+  // but n = 10^4, K = 3 4.4 and 4.5, n = 6.4 10^4, F = 5, K = 10, P = 8 4.7 and 5.5.
+  const bool contended = D == 1 && K <= (P <= 64 ? 4u : 2u) &&
+                         (P > 32 ? 3u : 2u) * tiles_likely >= (uint32_t)ctx->num_cu * K;
+  const bool several = (P <= 128 && D >= 3) || (P <= 128 && contended) || ctx->resident_blocks;
   RunShape best;
-  const uint32_t waves = waves_of(P), H = RES_THREADS / (waves * 64), SB = (1u << D) - 1u;
   double best_t = 1e300;
-  auto consider = [&](uint32_t nb) {
+  for (uint32_t nb = 1; nb <= (several ? max_blocks : 1u); ++nb) {
     const RunShape r = resident_fit(ctx, D, P, F, K, tiles, nb);
-    if (!r.nblk) return;
-    // cycles of a generation that depend on nb: the block's searches (a CU's
-    // LDS serves a wave's search in about 33 cycles), and the exchange
-    const double nodes = D < 4 ? SB : (D == 4 ? 16 : (H >= 4 ? 36 : 32));
-    const double t = r.tiles_max * waves * nodes * 33.0 + (nb > 1 ? 9000.0 + 12.0 * nb : 0.0) +
-                     (!r.split && r.slots < K ? 8000.0 : 0.0);
+    if (!r.nblk) continue;
+    const double t = resident_cycles(D, P, K, r, tiles_likely);
+    // One block alone against that form: it needs no exchange but has all the
+    // searches.  n = 300, F = 4, K = 2, P = 512, depth 2 (7 tiles) 5.8 us there
+    // and 7.2 here; n = 2000, P = 200, depth 3 (33 tiles) 7.4 and 16.2, n = 1000,
+    // F = 4, P = 32, depth 2 (17 tiles) 4.9 and 3.5.
+    if (!several && t > unrolled_cycles(D, P, K)) continue;
     if (ctx->resident_blocks ? nb == ctx->resident_blocks : t < best_t) {
       best_t = t;
       best = r;
     }
-  };
-  // Several blocks only where the groups are many: up to 128 individuals (eight
-  // groups), except at depth 2.  Elsewhere two groups per block with all of a
-  // tree's nodes in registers (persist.hip) are as fast or faster.  Per
-  // generation, there against here: n = 5 10^4, F = 21, P = 100, depth 3: 9.5
-  // and 8.6 us; n = 5000, F = 10, P = 128, depth 3: 7.5 and 7.2; n = 5 10^4, F
-  // = 12, P = 64, depth 1: 6.3 and 5.5; the same with P = 128, depth 2: 6.5 and
-  // 6.7; n = 10^5, F = 16, P = 256, depth 3: 10.4 and 10.8; n = 5 10^4, F = 12,
-  // P = 256, depth 4: 15.9 and 18.2; n = 2 10^4, F = 8, P = 512, depth 3: 11.5
-  // and 13.3.
-  const bool several = (P <= 128 && D != 2) || ctx->resident_blocks;
-  for (uint32_t nb = 1; nb <= (several ? max_blocks : 1u); ++nb) consider(nb);
+  }
   return best;
 }
 

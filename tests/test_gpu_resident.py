@@ -49,3 +49,38 @@ def test_resident_run_matches_oracle(mh, monkeypatch, blocks, D, P, K, n, F, M, 
 def _oracle(X, y, K, D, prm):
     r = oracle.deoct(oracle.dataset_from_X(X, y, K), D, oracle.de_params(*prm), with_pop=True)
     return r, r["pop"], r["pop_cost"]
+
+
+# the kernel each shape runs in: one resident block only where its searches cost
+# less than the other form's exchange, several from depth 3 on and up to 128
+# individuals, or at depth 1 where few classes and many tiles meet
+@pytest.mark.parametrize("D,P,K,n,F,kernel", [
+    (2, 32, 2, 1000, 4, "k_deoct_resident<2,1>: 1 runs, grid 1,"),
+    (2, 512, 2, 300, 4, "k_deoct_persist<2,"),
+    (3, 262, 2, 2000, 3, "k_deoct_persist<3,"),
+    (3, 100, 2, 2000, 4, "k_deoct_resident<3,2>: 1 runs, grid "),
+    (1, 64, 5, 4000, 10, "k_deoct_persist<1,"),
+    (1, 64, 2, 30_000, 4, "k_deoct_resident<1,1>: 1 runs, grid "),
+    (1, 300, 2, 30_000, 4, "k_deoct_persist<1,"),
+    (2, 100, 3, 8000, 20, "k_deoct_persist<2,"),
+])
+def test_whole_run_form_by_shape(mh, monkeypatch, capfd, D, P, K, n, F, kernel):
+    from paper_2311_06952_amd import capi
+    X, y = synth.random_small(D * 1000 + P, n, F, K)
+    prm = (P, 5, 0.5, 0.7, 7, 1, 0.0)
+    want, pop, cost = _oracle(X, y, K, D, prm)
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")
+    ctx = capi.Context(0)
+    capfd.readouterr()
+    got = mh.subtree_solve(mh.dataset(X, y, K, ctx=ctx), D, mh.de_params(*prm), ctx=ctx,
+                           with_pop=True)
+    err = capfd.readouterr().err
+    ctx.close()
+    assert kernel in err
+    if "grid 1," not in kernel:
+        assert "grid 1," not in err
+    for key in ("feat", "tau", "label"):
+        np.testing.assert_array_equal(got[key], want[key])
+    assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
+    np.testing.assert_array_equal(got["pop"], pop)
+    np.testing.assert_array_equal(got["pop_cost"], cost)
