@@ -309,3 +309,31 @@ def test_served_large_requests_left_to_the_per_generation_kernels(mh):
         want = oracle.deoct(oracle.dataset_from_X(X, y, K), D,
                             oracle.de_params(P, G, M, 0.9, 7000 + rid))
         _same(res[rid]["tree"], want)
+
+
+def test_served_small_groups_use_idle_units(mh, monkeypatch, capfd):
+    """A small request alone, and a few together, are spread over more blocks
+    than a full group would give them; their results stay the oracle's."""
+    import re
+    from paper_2311_06952_amd import capi
+    reqs = [(80, 12_918, 1, 3, 5, 8, 9, 0.5), (81, 9000, 12, 40, 4, 100, 6, -1.0),
+            (82, 22_000, 3, 2, 2, 128, 6, 0.5), (83, 70, 2, 2, 1, 3, 6, 0.5)]
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")
+    ctx = capi.Context(0)
+    srv = mh.Server(1 << 30, 4, ctx=ctx)
+    res, blocks = {}, []
+    for batch in [reqs[:1], reqs[1:2], reqs[2:3], reqs[3:], reqs]:
+        capfd.readouterr()
+        for r in batch:
+            _submit(mh, srv, r)
+        res.update({r["req_id"]: r for r in srv.drain()})
+        blocks.append(int(re.search(r"queue<\d>: (\d+) blocks", capfd.readouterr().err)[1]))
+        for rid, n, F, K, D, P, G, M in batch:
+            assert res[rid]["status"] == 0
+            X, y = _data(rid, n, F, K)
+            want = oracle.deoct(oracle.dataset_from_X(X, y, K), D,
+                                oracle.de_params(P, G, M, 0.9, 7000 + rid))
+            _same(res[rid]["tree"], want)
+    srv.close()
+    ctx.close()
+    assert blocks[0] > 32 and blocks[1] > 32 and blocks[3] <= 4 and max(blocks) <= 256
