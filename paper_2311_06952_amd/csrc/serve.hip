@@ -184,10 +184,16 @@ constexpr uint32_t MAX_SLOTS = 256;
 // P = 184, G = 46 4.3 ms, this form 2.3; n = 973,000, F = 8, depth 5, P = 198,
 // G = 29 8.6 and 5.3.
 constexpr uint32_t WHOLE_BURST = 32;
-// A group run holds the stream until its longest request is done.
+// A group run holds the stream until its longest request is done, and a run
+// whose blocks have not all started waits for earlier ones at its first barrier,
+// which gives up after 2 s: 2,000 generations of the largest runs (depth 5, P =
+// 128, about 50 us each) are 0.1 s.
 constexpr uint32_t GROUP_MAX_G = 2000;
-// Blocks of a group's runs, at most, per CU: a resident request that is stepped
-// waits for a group between two of its generations.
+// Blocks of a group's runs, at most, per CU: enough that long runs at its end
+// leave few CUs idle, while a request that is stepped waits for a group between
+// two of its generations.  A burst of 64 and of 192 small requests: 7.5 and 21.5
+// ms with one block per CU, 6.4 and 18.3 with two, 5.9 and 16.4 with four, 5.8
+// and 15.6 with eight.
 constexpr uint32_t GROUP_ROUNDS = 4;
 // Arena bytes of a group, at most: the ranks of its requests and the counters
 // of those that run on several blocks (one block counts in its LDS).
@@ -258,21 +264,28 @@ size_t group_bytes(const Req &q, uint32_t nb) {
   return ((size_t)q.F * rank_ld(q.n) + group_cnt_words(q, nb)) * 4;
 }
 
-// Blocks of a request in a group run, up to max_blocks: the number for which
-// blocks times the cycles of a generation are the least, so that a full group
-// takes the least time; with `alone`, the cycles themselves; 0 where it does not
-// fit, or runs too long for a group.
+// Blocks of a request in a group run, up to max_blocks; 0 where it does not fit,
+// or runs too long for a group.  With `alone` the number for which a generation
+// takes the fewest cycles.  Else the one that keeps a full chip the least: the
+// least blocks times cycles, these by weights that favour more blocks than the
+// cycles of a run alone (resident_cycles) would, since a long run that starts
+// last holds up the group: bursts of 64 and 192 requests of 10^3 to 2 10^4
+// samples (P = 128, G = 100) 5.85 and 16.4 ms, 6.07 and 17.0 by resident_cycles.
 uint32_t group_blocks(const Ctx *c, const Req &q, uint32_t max_blocks, bool alone) {
   if (q.redo || !c->persist || !c->persist_resident || q.n == 0 || q.n > SMALL_MAX_N || q.prm.P > 128 ||
       q.prm.G > GROUP_MAX_G)
     return 0;
+  const uint32_t SB = (1u << q.D) - 1u, waves = waves_for(q.prm.P);
   const uint32_t likely = std::max(std::min(q.K, q.n), q.cv.max_tiles - q.K / 2);
   uint32_t best = 0;
   double best_c = 1e300;
   for (uint32_t nb = 1; nb <= max_blocks && nb <= q.cv.max_tiles; ++nb) {
     const RunShape r = resident_fit(c, q.D, q.prm.P, q.F, q.K, q.cv.max_tiles, nb);
     if (!r.nblk) continue;
-    const double t = (alone ? 1.0 : nb) * resident_cycles(q.D, q.prm.P, q.K, r, likely);
+    const double t =
+        alone ? resident_cycles(q.D, q.prm.P, q.K, r, likely)
+              : nb * (6000.0 + r.tiles_max * waves * (SB + 3.0) * 33.0 + (nb > 1 ? 9000.0 : 0.0) +
+                      (r.split ? 3500.0 : 3000.0 * ((q.K + r.slots - 1) / r.slots - 1)));
     if (t < best_c) {
       best_c = t;
       best = nb;
