@@ -234,6 +234,12 @@ struct mh_server {
   uint32_t solo_tiles = 0;
   // a group's launch gave up at a grid barrier: no more groups
   bool no_groups = false;
+  // the last group's start and end on the device, its length once it is known
+  // (group_open until then) and when the host saw its end: requests that are
+  // stepped get as long before the next group
+  hipEvent_t group_ev[2] = {};
+  bool group_open = false;
+  uint64_t group_ns = 0, group_end = 0;
   // mh_server_set_limits: queued requests at most (0: no limit) and the
   // time from submission after which a request is cancelled (0: none)
   uint32_t max_queued = 0;
@@ -477,6 +483,7 @@ mh_status group_run(mh_server *s, std::vector<Req> &g, bool *used) {
                o_map = o_pack + align256(cnt_n * sizeof(PackJob)),
                bytes = o_map + (size_t)blocks * 4;
   if (bytes > s->desc_bytes) return fail(c, MH_EINVAL, "server descriptor space exhausted");
+  MH_HIP(c, hipEventRecord(s->group_ev[0], st));
   PackJob *pk = reinterpret_cast<PackJob *>(host + o_pack);
   uint32_t *map = reinterpret_cast<uint32_t *>(host + o_map);
   uint32_t blk = 0;
@@ -570,6 +577,8 @@ mh_status group_run(mh_server *s, std::vector<Req> &g, bool *used) {
   r = launch_pack_jobs(c, reinterpret_cast<const PackJob *>(s->desc_dev + o_pack), cnt_n);
   if (r) return r;
   MH_HIP(c, hipEventRecord(s->slot_ev[g[0].slot], st));
+  MH_HIP(c, hipEventRecord(s->group_ev[1], st));
+  s->group_open = true;
   for (Req &q : g) {
     q.coop_kern = c->last_coop_kern;
     q.coop_grid = c->last_coop_grid;
@@ -746,10 +755,34 @@ void drop_cancelled(mh_server *s) {
   s->active.resize(kept);
 }
 
+// Whether a group may run now: at once while no request is stepped, else when
+// the stepped ones had the device since the last group for as long as it took.
+// (One group a round, a generation of the stepped ones between two: a request
+// of P = 200, G = 1000 on 3,000 samples, 26 ms alone, took 1,116 ms beside
+// a stream of a small request every 0.5 ms, and takes 50.)
+mh_status group_turn(mh_server *s, bool *turn) {
+  if (s->group_open) {
+    const hipError_t e = hipEventQuery(s->group_ev[1]);
+    if (e == hipSuccess) {
+      float ms = 0.f;
+      MH_HIP(s->c, hipEventElapsedTime(&ms, s->group_ev[0], s->group_ev[1]));
+      s->group_ns = (uint64_t)(ms * 1e6);
+      s->group_end = now_ns();
+      s->group_open = false;
+    } else if (e != hipErrorNotReady) {
+      return hip_fail(s->c, e, "hipEventQuery");
+    }
+  }
+  *turn = s->active.empty() || (!s->group_open && now_ns() - s->group_end >= s->group_ns);
+  return MH_OK;
+}
+
 mh_status round_once(mh_server *s) {
   drop_cancelled(s);
   mh_status r = collect(s, s->active.empty() && s->queue.empty());
   if (r) return r;
+  bool turn = false;
+  if ((r = group_turn(s, &turn))) return r;
   // admission, in submission order; at most one whole-request run or group run
   // per round, so that the resident requests get a generation between two of
   // them
@@ -764,6 +797,7 @@ mh_status round_once(mh_server *s) {
     if (!solo && !solo_run && s->solo_tiles && !s->no_groups) {
       const uint32_t nb = group_blocks(s->c, q, (uint32_t)s->c->num_cu, false);
       if (nb) {
+        if (!turn) break;
         const size_t mem = group_bytes(q, nb);
         if (!group.empty() && (group_blk + nb > GROUP_ROUNDS * (uint32_t)s->c->num_cu ||
                                group_mem + mem > GROUP_MAX_BYTES))
@@ -893,6 +927,7 @@ mh_status mh_server_create(mh_ctx *ctx, uint64_t hbm_budget, uint32_t max_slots,
     e = hipHostMalloc((void **)&s->ring[k], s->desc_bytes);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ring_ev[k], hipEventDisableTiming);
   }
+  for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreate(&s->group_ev[k]);
   s->slot_ev.assign(max_slots, nullptr);
   for (uint32_t i = 0; i < max_slots && e == hipSuccess; ++i)
     e = hipEventCreateWithFlags(&s->slot_ev[i], hipEventDisableTiming);
@@ -917,6 +952,8 @@ void mh_server_destroy(mh_server *s) {
     if (s->ring[k]) (void)hipHostFree(s->ring[k]);
     if (s->ring_ev[k]) (void)hipEventDestroy(s->ring_ev[k]);
   }
+  for (hipEvent_t ev : s->group_ev)
+    if (ev) (void)hipEventDestroy(ev);
   for (hipEvent_t ev : s->slot_ev)
     if (ev) (void)hipEventDestroy(ev);
   delete s;

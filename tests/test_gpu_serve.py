@@ -337,3 +337,43 @@ def test_served_small_groups_use_idle_units(mh, monkeypatch, capfd):
     srv.close()
     ctx.close()
     assert blocks[0] > 32 and blocks[1] > 32 and blocks[3] <= 4 and max(blocks) <= 256
+
+
+def test_stepped_request_advances_beside_a_stream_of_small_ones(mh):
+    """A request that is stepped has the device between two groups for as long as
+    a group took: few small requests, submitted one a round, run before it ends
+    (with a group every round it would be one for each of its generations)."""
+    import torch
+    from paper_2311_06952_amd import capi
+    G, small = 300, (91, 6000, 8, 3, 4, 100, 60, 0.5)
+    X, y = _data(*small[:4])
+    Xd, yd = torch.as_tensor(X).cuda(), torch.as_tensor(y).cuda()
+    ctx = capi.Context(0)
+    srv = mh.Server(1 << 30, 64, ctx=ctx)
+    _submit(mh, srv, (90, 3000, 6, 3, 3, 200, G, 0.5))
+    res, k, before = {}, 0, None
+    for _ in range(20 * G):
+        if before is None:
+            k += 1
+            srv.submit(1000 + k, Xd, yd, 3, 4, _prm(mh, 100, 60, 0.5, 91))
+        left = srv.pump(1)
+        for r in srv.poll():
+            res[r["req_id"]] = r
+            if r["req_id"] == 90:
+                before = len(res) - 1
+        if left == (0, 0):
+            break
+    srv.close()
+    ctx.close()
+    assert before is not None and len(res) == k + 1
+    assert all(r["status"] == 0 for r in res.values())
+    # a round admits what has queued up, so count the groups by their ends
+    groups = len({r["t_done_ns"] // 1000 for r in res.values() if r["t_done_ns"] <= res[90]["t_done_ns"]})
+    assert groups < G // 3
+    Xl, yl = _data(90, 3000, 6, 3)
+    want = oracle.deoct(oracle.dataset_from_X(Xl, yl, 3), 3, oracle.de_params(200, G, 0.5, 0.9, 7090))
+    _same(res[90]["tree"], want)
+    want = oracle.deoct(oracle.dataset_from_X(X, y, 3), 4, oracle.de_params(100, 60, 0.5, 0.9, 7091))
+    for r in res.values():
+        if r["req_id"] != 90:
+            _same(r["tree"], want)
