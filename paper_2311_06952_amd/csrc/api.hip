@@ -254,6 +254,7 @@ struct EvalSet {
   uint32_t max_tiles;
   uint32_t *cnt;
   uint32_t *leafcnt;  // walk path: caller scratch for the leaf counts (null: the arena's)
+  const uint32_t *weight;  // walk path: how often idx names each sample (null: not counted)
 };
 
 static mh_status eval_trees(Ctx *ctx, const EvalSet &es, const uint8_t *feat, const uint32_t *tau,
@@ -263,7 +264,7 @@ static mh_status eval_trees(Ctx *ctx, const EvalSet &es, const uint8_t *feat, co
     return launch_fitness_tiles(ctx, es.tiles, es.ds->F, es.ds->K, es.n_sub, 1, es.max_tiles, feat,
                                 tau, P, D, n_min, alpha, es.cnt, out);
   return launch_fitness_walk(ctx, es.ds, es.idx, es.n_sub, feat, tau, P, D, n_min, alpha, out,
-                             es.leafcnt);
+                             es.leafcnt, es.weight);
 }
 
 // Device bytes of the tile layout and counters (tile path) or the leaf
@@ -279,11 +280,14 @@ static size_t eval_scratch_bytes(const mh_dataset *ds, uint32_t n_sub, uint32_t 
 // static_base: caller-provided scratch of eval_scratch_bytes (null: the
 // context arena's buffers tile_name and cnt_name).  min_trees: the tile
 // layout is built only for at least this many trees (DEOCT builds it for its
-// population whatever the size: its kernels all read it).
+// population whatever the size: its kernels all read it).  evaluations: how
+// often the set is evaluated (the walk path counts a subset's samples once for
+// all of them).
 static mh_status prepare_eval(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub,
                               uint32_t D, uint32_t P, const char *tile_name, const char *cnt_name,
                               EvalSet &es, uint8_t *static_base = nullptr,
-                              uint32_t min_trees = 0, const SmallJob *init = nullptr) {
+                              uint32_t min_trees = 0, const SmallJob *init = nullptr,
+                              uint32_t evaluations = 1) {
   es.ds = ds;
   es.idx = idx;
   es.n_sub = n_sub;
@@ -292,7 +296,12 @@ static mh_status prepare_eval(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
   es.max_tiles = 0;
   const bool use_tiles = tile_path_ok(D, ds->F, ds->n) && P >= min_trees;
   es.leafcnt = use_tiles ? nullptr : reinterpret_cast<uint32_t *>(static_base);
-  if (!use_tiles) return MH_OK;
+  es.weight = nullptr;
+  if (!use_tiles) {
+    if (idx && !static_base && walk_weighs(ctx, ds, n_sub, P, D, evaluations))
+      es.weight = walk_weights(ctx, ds, idx, n_sub);
+    return MH_OK;
+  }
   TileHdr h = tile_layout(n_sub, ds->F, ds->K, 1);
   void *tiles = static_base ? static_base : arena_get(ctx, tile_name, h.total_bytes);
   uint32_t *cnt = static_base
@@ -326,7 +335,7 @@ static mh_status deoct(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint
   init.SB = SB;
   const bool init_done = W == 0 && tile_path_ok(D, ds->F, ds->n) && tiles_small(ds, n_sub);
   mh_status s = prepare_eval(ctx, ds, idx, n_sub, D, P, "ss_tiles", "ss_cnt", es, nullptr, 0,
-                             init_done ? &init : nullptr);
+                             init_done ? &init : nullptr, prm->G + 1);
   if (s) return s;
   double *trial = (double *)arena_get(ctx, "ss_trial", (size_t)P * m * 8);
   double *cost = (double *)arena_get(ctx, "ss_cost", (size_t)P * 8);

@@ -16,6 +16,8 @@
 // tree at a time with an LDS histogram per (leaf, class).
 #include <hip/hip_ext.h>
 
+#include <cstdio>
+
 #include "de_body.h"
 #include "device_common.h"
 #include "epilogue.h"
@@ -621,6 +623,74 @@ __global__ __launch_bounds__(WT_THREADS) void k_walk_tiles(WalkArgs a) {
   }
 }
 
+// The walk with every rank read from memory where its node asks for it: a lane
+// per sample, the block's trees in LDS as 64-bit nodes (tau, column), GI
+// independent chains per lane.  The memory system bounds it (a wave's read of 64
+// ranks is up to 64 lines), but it reads D ranks per tree where k_walk_tiles
+// stages F columns for every group of trees, and the columns leave it room for
+// few trees.  Measured per launch, there and here: n = 1.55 10^5, a sorted quarter
+// of it, F = 120, K = 20, depth 7, P = 178 500 and 105 us; 2,700 samples of 1.35
+// 10^5, F = 145, K = 5, depth 6, P = 5 33 and 12 us.
+constexpr uint32_t WD_THREADS = 256;
+
+template <int GI>
+__global__ __launch_bounds__(WD_THREADS) void k_walk_direct(WalkArgs a) {
+  extern __shared__ __align__(16) uint32_t wl[];
+  const uint32_t SB = (1u << a.D) - 1u, SL = 1u << a.D, K = a.K;
+  const uint32_t r0 = blockIdx.y * a.TG, tg = min(a.TG, a.P - r0);
+  uint64_t *nodes = reinterpret_cast<uint64_t *>(wl);                     // [TG][SB]
+  uint32_t *hist = reinterpret_cast<uint32_t *>(nodes + (size_t)a.TG * SB);  // [TG][SL][K]
+  const uint32_t node0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint32_t *)wl);
+  for (uint32_t e = threadIdx.x; e < tg * SB; e += WD_THREADS) {
+    const uint32_t f = a.feat[(size_t)r0 * SB + e], t = a.tau[(size_t)r0 * SB + e];
+    const bool split = f != 0 && f <= a.F;
+    nodes[e] = split ? ((uint64_t)t << 32) | (f - 1u) : 0ull;
+  }
+  if (a.hist_in_lds)
+    for (uint32_t e = threadIdx.x; e < tg * SL * K; e += WD_THREADS) hist[e] = 0;
+  __syncthreads();
+  const uint64_t per = 64ull * a.per;  // (64-bit: no wrap for counts near 2^32)
+  const uint32_t s0 = (uint32_t)min((uint64_t)a.n_sub, blockIdx.x * per);
+  const uint32_t s1 = (uint32_t)min((uint64_t)a.n_sub, s0 + per);
+  for (uint32_t base = s0, next; base < s1; base = next) {
+    const uint32_t cnt = min(WD_THREADS, s1 - base);
+    next = base + cnt;
+    uint32_t smp, w, y = 0xFFu;
+    if (threadIdx.x < cnt) y = walk_label(a, base + threadIdx.x, smp, w);
+    if (y == 0xFFu) continue;
+    const uint32_t *rank = a.ranks + smp;
+    for (uint32_t g0 = 0; g0 < tg; g0 += GI) {
+      uint32_t nb[GI], na[GI];
+#pragma unroll
+      for (int gg = 0; gg < GI; ++gg) na[gg] = nb[gg] = node0 + 8u * SB * min(g0 + gg, tg - 1);
+      for (uint32_t lv = 0; lv < a.D; ++lv) {
+        uint64_t x[GI];
+        uint32_t rk[GI];
+#pragma unroll
+        for (int gg = 0; gg < GI; ++gg) x[gg] = lds_rd64(na[gg]);
+#pragma unroll
+        for (int gg = 0; gg < GI; ++gg) rk[gg] = rank[(size_t)(uint32_t)x[gg] * a.ld];
+#pragma unroll
+        for (int gg = 0; gg < GI; ++gg)
+          na[gg] = 2u * na[gg] - nb[gg] + (rk[gg] < (uint32_t)(x[gg] >> 32) ? 8u : 16u);
+      }
+#pragma unroll
+      for (int gg = 0; gg < GI; ++gg) {
+        if (g0 + gg >= tg) continue;
+        const uint32_t leaf = (na[gg] - nb[gg]) / 8u + 1u - SL;
+        if (a.hist_in_lds)
+          atomicAdd(&hist[((g0 + gg) * SL + leaf) * K + y], w);
+        else
+          atomicAdd(&a.leafcnt[((size_t)(r0 + g0 + gg) * SL + leaf) * K + y], w);
+      }
+    }
+  }
+  if (!a.hist_in_lds) return;
+  __syncthreads();
+  for (uint32_t e = threadIdx.x; e < tg * SL * K; e += WD_THREADS)
+    if (hist[e]) atomicAdd(&a.leafcnt[(size_t)r0 * SL * K + e], hist[e]);
+}
+
 // How often each sample is named by idx (entries past n are invalid input).
 // (A launch takes fewer than 2^32 threads, a subset as many entries.)
 __global__ __launch_bounds__(256) void k_walk_weight(const uint32_t *__restrict__ idx,
@@ -795,11 +865,187 @@ mh_status launch_fitness_tiles(Ctx *ctx, const void *tiles, uint32_t F, uint32_t
                                  cnt, out);
 }
 
+// How a walk over n_sub samples shares out its trees and samples over the
+// blocks, and the cycles its fullest CU is expected to take.
+struct WalkPlan {
+  double cycles = 1e300;
+  bool direct = false, sel = false, wide = false, hist_in_lds = false;
+  uint32_t T = 0;  // samples per tile, or the trees a lane walks at once (direct)
+  uint32_t TG = 0, per = 0, ranges = 0, groups = 0;
+  size_t lds = 0;
+};
+
+// The 128-byte lines that 64 samples of one column lie on: two when they follow
+// each other; of a subset, whose order is not known here, between the sorted
+// case (2 n / n_sub) and the random one (64).
+static double walk_lines(const mh_dataset *ds, uint32_t n_sub, bool gather) {
+  return gather ? std::min(64.0, 8.0 * ds->n / n_sub) : 2.0;
+}
+
+// k_walk_tiles.  LDS, one block per CU: a tile of T samples with its labels and
+// weights, TG trees' nodes and, when it fits, their histograms.  The largest
+// tile that leaves the trees at least 60 KiB: its waves then share nothing but
+// the trees, and a tile's barriers are paid for by more walks.
+// Groups of trees times ranges of samples, at most one block per CU: the choice
+// with the least work for a block, counted in CU cycles (measured): 8.4 per 64
+// samples, tree (in batches of four) and level, 12 per 64 samples and column
+// staged, 2,000 per tile for its barriers and the chains' latency, and 1.5 per
+// histogram word cleared and added to memory.  With a multiple of 8 ranges every
+// block of one range is on the same XCD (blocks go round-robin over the 8 XCDs in
+// launch order), whose L2 then serves the range's ranks to all groups but one;
+// that saves 4 per column.  Through an index 64 ranks of a column cost a block
+// about 50 cycles and 1.2 per line, and the chip 30 and 4.2 per line (a CU's
+// share of the memory bandwidth).
+static WalkPlan plan_tiles(const Ctx *ctx, const mh_dataset *ds, uint32_t n_sub, bool gather,
+                           uint32_t P, uint32_t D) {
+  const uint32_t SB = (1u << D) - 1u, SL = 1u << D, K = ds->K, F = ds->F;
+  WalkPlan w;
+  w.wide = ds->n >= WT_RANK_MAX;
+  // few trees on a wide data set stage only the columns they split on, at most
+  // one per node (Fs: the columns a block stages, at most)
+  w.sel = (uint64_t)P * SB <= F && !w.wide;
+  const uint32_t Fs = w.sel ? P * SB : F;
+  const uint32_t T = Fs <= 24 ? 1024u : Fs <= 48 ? 512u : Fs <= 128 ? 256u : 128u;
+  const uint32_t NG = WT_THREADS / T;
+  const size_t budget = ctx->max_lds - 4096;
+  const size_t tile_bytes = (size_t)Fs * T * 4 + T * 4 + T;
+  const size_t tree_nodes = (size_t)SB * (w.wide ? 8 : 4), tree_hist = (size_t)SL * K * 4;
+  if (tile_bytes + tree_nodes + 16 > budget) return w;
+  w.T = T;
+  w.hist_in_lds = true;
+  size_t TG = (budget - tile_bytes - 16) / (tree_nodes + tree_hist);
+  if (TG == 0) {
+    // histograms in memory: the nodes alone decide the trees per block
+    w.hist_in_lds = false;
+    TG = (budget - tile_bytes - 16) / tree_nodes;
+  }
+  const uint32_t cus = (uint32_t)ctx->num_cu, units = (uint32_t)(((uint64_t)n_sub + 63) / 64);
+  const uint32_t g_min = (uint32_t)((P + TG - 1) / TG);
+  uint32_t best_units = 0;
+  for (uint32_t g = g_min; g <= std::max(g_min, std::min(P, cus)); ++g) {
+    const uint32_t tg = (P + g - 1) / g;
+    if (g > g_min && tg == (P + g - 2) / (g - 1)) continue;
+    const uint32_t rg = std::max(1u, std::min(units, cus / g));
+    const uint32_t chains = tg > 2 * NG ? (tg + 3) / 4 * 4 : tg;
+    for (uint32_t r = rg;; r &= ~7u) {
+      const uint32_t per = (units + r - 1) / r;
+      const uint32_t rounds = (g * r + cus - 1) / cus;  // (more groups than CUs)
+      const double unit = 8.4 * chains * D + (r % 8 ? 12.0 : 8.0) * Fs + 2000.0 * 64 / T;
+      const double c = rounds * (per * unit + 1.5 * tg * SL * K);
+      if (c < w.cycles) {
+        w.cycles = c;
+        w.groups = g;
+        w.ranges = r;
+        best_units = rounds * per;
+      }
+      if (r < 8 || r % 8 == 0) break;
+    }
+  }
+  w.cycles += 6000.0;  // (launch and set-up, against k_walk_direct's)
+  if (gather) {
+    const double lines = walk_lines(ds, n_sub, true);
+    w.cycles +=
+        Fs * (best_units * (40.0 + 1.2 * lines) + (double)units / cus * (30.0 + 4.2 * lines));
+  }
+  w.TG = (P + w.groups - 1) / w.groups;
+  w.groups = (P + w.TG - 1) / w.TG;
+  w.per = (units + w.ranges - 1) / w.ranges;
+  w.ranges = (units + w.per - 1) / w.per;
+  w.lds = tile_bytes + ((w.TG * tree_nodes + 7) & ~(size_t)7) +
+          (w.hist_in_lds ? w.TG * tree_hist : 0);
+  return w;
+}
+
+// k_walk_direct: about three blocks per CU, at most 32 trees each.  Its cycles,
+// fitted to measured launches (n = 3,000 to 2.5 10^6, F = 2 to 240, P = 1 to 512,
+// depth 1 to 10, all samples and subsets): 12 per wave, tree and level, 0.8 per
+// line that these touch and 5 per line that a block's trees touch first, 700 for
+// a block's dependent reads, 1.3 per histogram word, 2,400 per wave and tree for
+// counts in memory.
+static WalkPlan plan_direct(const Ctx *ctx, const mh_dataset *ds, uint32_t n_sub, bool gather,
+                            uint32_t P, uint32_t D) {
+  const uint32_t SB = (1u << D) - 1u, SL = 1u << D, K = ds->K, F = ds->F;
+  WalkPlan w;
+  w.direct = true;
+  const size_t budget = std::max<size_t>(48 * 1024, (ctx->max_lds - 4096) / 3);
+  const size_t tree_nodes = (size_t)SB * 8, tree_hist = (size_t)SL * K * 4;
+  size_t TG = budget / (tree_nodes + tree_hist);
+  w.hist_in_lds = TG > 0;
+  if (!TG) TG = budget / tree_nodes;
+  TG = std::min<size_t>({TG, 32, P});
+  const uint32_t GI = TG >= 8 ? 8u : 4u;
+  if (TG > GI) TG -= TG % GI;
+  w.T = GI;
+  w.TG = (uint32_t)TG;
+  w.groups = (P + w.TG - 1) / w.TG;
+  if (w.groups > 65535) return w;  // (a grid's second dimension)
+  w.lds = TG * (tree_nodes + (w.hist_in_lds ? tree_hist : 0));
+  const uint32_t cus = (uint32_t)ctx->num_cu;
+  const uint32_t per_cu = std::max<uint32_t>(
+      1u, std::min<uint32_t>(8u, (uint32_t)(ctx->max_lds / std::max<size_t>(w.lds, 1))));
+  const uint32_t tiles = (uint32_t)(((uint64_t)n_sub + WD_THREADS - 1) / WD_THREADS);
+  w.ranges = std::max(1u, std::min(tiles, per_cu * cus / w.groups));
+  if (w.ranges >= 8) w.ranges &= ~7u;
+  const uint32_t rows = (tiles + w.ranges - 1) / w.ranges;  // of 256 samples, per block
+  w.per = rows * (WD_THREADS / 64);
+  w.ranges = (tiles + rows - 1) / rows;
+  const double lines = walk_lines(ds, n_sub, gather), units = ((double)n_sub + 63) / 64;
+  double touched = 0, cols = 0;  // of one tree, per 64 samples
+  for (uint32_t lv = 0; lv < D; ++lv) {
+    touched += std::min(64.0, (double)(1u << lv) * lines);
+    cols += std::min(64u, 1u << lv);
+  }
+  const double first = std::min(std::min<double>(F, w.TG * cols) * lines, w.TG * touched);
+  const double blocks = (double)w.groups * w.ranges;
+  w.cycles = units / cus * (P * (12.0 * D + 0.8 * touched) + 5.0 * w.groups * first) +
+             700.0 * rows * ((w.TG + GI - 1) / GI) * D * std::max(1.0, blocks / (per_cu * cus)) +
+             (w.hist_in_lds ? 1.3 * w.TG * SL * K * std::max(1.0, blocks / cus)
+                            : 2400.0 * units * P / cus);
+  return w;
+}
+
+// The faster form as expected; k_walk_direct for rows wider than 48 columns
+// (narrower ones leave a tile's columns room for many trees).
+static WalkPlan walk_plan(const Ctx *ctx, const mh_dataset *ds, uint32_t n_sub, bool gather,
+                          uint32_t P, uint32_t D) {
+  const WalkPlan t = plan_tiles(ctx, ds, n_sub, gather, P, D);
+  if (ds->F <= 48 && t.groups) return t;
+  const WalkPlan d = plan_direct(ctx, ds, n_sub, gather, P, D);
+  return d.cycles < t.cycles ? d : t;
+}
+
+// A subset can also be walked as all samples in order, each counted as often as
+// the subset names it: the columns then stream in, where a gather reads a line of
+// 128 bytes per rank, but the samples outside it are walked as well.  Counting
+// takes two launches, 10,000 cycles, and 4.4 and 5 per 256 samples and entries.
+// Measured: a random half of n = 2.7 10^5, F = 46, K = 3, depth 6, P = 196: 126 us
+// so, 185 through the index; a sorted quarter of n = 1.8 10^6, F = 4, P = 169: 640
+// and 160.
+bool walk_weighs(const Ctx *ctx, const mh_dataset *ds, uint32_t n_sub, uint32_t P, uint32_t D,
+                 uint32_t evaluations) {
+  if (n_sub == 0 || ds->n == 0 || P == 0) return false;
+  const double count = 10000.0 + (4.4 * ds->n + 5.0 * n_sub) / ctx->num_cu;
+  return plan_tiles(ctx, ds, ds->n, false, P, D).cycles + count / evaluations <
+         walk_plan(ctx, ds, n_sub, true, P, D).cycles;
+}
+
+const uint32_t *walk_weights(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub) {
+  uint32_t *w = (uint32_t *)arena_get(ctx, "walk_weight", (size_t)ds->n * 4);
+  if (!w) {
+    (void)hipGetLastError();  // no room for it: the subset is gathered
+    return nullptr;
+  }
+  if (launch_zero(ctx, {{w, (size_t)ds->n * 4}})) return nullptr;
+  const uint32_t blocks = (uint32_t)std::min<uint64_t>(((uint64_t)n_sub + 255) / 256, 1u << 16);
+  k_walk_weight<<<blocks, 256, 0, ctx->stream>>>(idx, n_sub, ds->n, w);
+  return w;
+}
+
 mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub,
                               const uint8_t *feat, const uint32_t *tau, uint32_t P, uint32_t D,
                               uint32_t n_min, double alpha, const FitnessOut &out,
-                              uint32_t *leafcnt) {
-  const uint32_t SB = (1u << D) - 1u, SL = 1u << D, K = ds->K, F = ds->F;
+                              uint32_t *leafcnt, const uint32_t *weight) {
+  const uint32_t K = ds->K;
   // only the context's own buffer is known to stay clear between calls (a
   // caller's scratch may have held anything since)
   const size_t bytes = walk_scratch_bytes(P, D, K);
@@ -811,122 +1057,60 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     if (mh_status zs = launch_zero(ctx, {{leafcnt, bytes}})) return zs;
   if (own) ctx->walk_zero = nullptr;
   if (n_sub > 0 && P > 0 && ds->n > 0) {
+    const WalkPlan w = weight ? plan_tiles(ctx, ds, ds->n, false, P, D)
+                              : walk_plan(ctx, ds, n_sub, idx != nullptr, P, D);
+    if (w.groups == 0)
+      return fail(ctx, MH_EDEVICE, "the device's LDS is too small for the walk kernel");
     WalkArgs a;
     a.ranks = ds->ranks;
     a.ld = ds->ld;
     a.labels = ds->labels;
-    a.idx = idx;
-    a.weight = nullptr;
+    a.idx = weight ? nullptr : idx;
+    a.weight = weight;
     a.n_unique = ds->n_unique;
-    a.n_sub = n_sub;
+    a.n_sub = weight ? ds->n : n_sub;
     a.n = ds->n;
     a.feat = feat;
     a.tau = tau;
     a.P = P;
     a.D = D;
-    a.F = F;
+    a.F = ds->F;
     a.K = K;
-    a.leafcnt = leafcnt;
+    a.TG = w.TG;
+    a.per = w.per;
+    a.hist_in_lds = w.hist_in_lds ? 1u : 0u;
     a.vec4 = (ds->n >= 4 && ds->ld % 4 == 0 && ((uintptr_t)ds->ranks & 15u) == 0) ? 1u : 0u;
-    // few trees on a wide data set stage only the columns they split on, at
-    // most one per node (Fs: the columns a block stages, at most)
-    const bool sel = (uint64_t)P * SB <= F && ds->n < WT_RANK_MAX;
-    const uint32_t Fs = sel ? P * SB : F;
-    if (idx && own && n_sub >= ds->n / 4 && (uint64_t)n_sub * Fs >= (1u << 20)) {
-      // A subset of a good part of the samples: all samples in order, each
-      // counted as often as the subset names it.  The columns then stream in,
-      // where a gather reads a line of 64 bytes or more per rank: at a quarter
-      // of the samples both move about as much.  (Two more launches, about 5
-      // us: a gather of 2^20 ranks takes 64 MB of lines.)
-      uint32_t *w = (uint32_t *)arena_get(ctx, "walk_weight", (size_t)ds->n * 4);
-      if (w) {
-        if (mh_status zs = launch_zero(ctx, {{w, (size_t)ds->n * 4}})) return zs;
-        const uint32_t blocks = (uint32_t)std::min<uint64_t>(((uint64_t)n_sub + 255) / 256, 1u << 16);
-        k_walk_weight<<<blocks, 256, 0, st>>>(idx, n_sub, ds->n, w);
-        MH_LAUNCHED(ctx, "k_walk_weight");
-        a.idx = nullptr;
-        a.weight = w;
-        a.n_sub = ds->n;
-      } else {
-        (void)hipGetLastError();  // no room for it: the subset is gathered
-      }
-    }
-    // LDS, one block per CU: a tile of T samples with its labels and weights,
-    // TG trees' nodes and, when it fits, their histograms.  The largest tile
-    // that leaves the trees at least 60 KiB: its waves then share nothing but
-    // the trees, and a tile's barriers are paid for by more walks.
-    const bool wide = ds->n >= WT_RANK_MAX;
-    const uint32_t T = Fs <= 24 ? 1024u : Fs <= 48 ? 512u : Fs <= 128 ? 256u : 128u;
-    const uint32_t NG = WT_THREADS / T;
-    const size_t budget = ctx->max_lds - 4096;
-    const size_t tile_bytes = (size_t)Fs * T * 4 + T * 4 + T;
-    const size_t tree_nodes = (size_t)SB * (wide ? 8 : 4), tree_hist = (size_t)SL * K * 4;
-    if (tile_bytes + tree_nodes + 16 > budget)
-      return fail(ctx, MH_EDEVICE, "the device's LDS is too small for the walk kernel");
-    a.hist_in_lds = 1;
-    size_t TG = (budget - tile_bytes - 16) / (tree_nodes + tree_hist);
-    if (TG == 0) {
-      // histograms in memory: the nodes alone decide the trees per block
-      a.hist_in_lds = 0;
-      TG = (budget - tile_bytes - 16) / tree_nodes;
-    }
-    // Groups of trees times ranges of samples, at most one block per CU: the
-    // choice with the least work for a block, counted in CU cycles (measured):
-    // 8.4 per 64 samples, tree (in batches of four) and level, 12 per 64
-    // samples and column staged, 2,000 per tile for its barriers and the
-    // chains' latency, and 1.5 per histogram word cleared and added to memory.
-    // With a multiple of 8 ranges every block of one range is on the same XCD
-    // (blocks go round-robin over the 8 XCDs in launch order), whose L2 then
-    // serves the range's ranks to all groups but one; that saves 4 per column.
-    const uint32_t cus = (uint32_t)ctx->num_cu, units = (uint32_t)(((uint64_t)a.n_sub + 63) / 64);
-    const uint32_t g_min = (uint32_t)((P + TG - 1) / TG);
-    uint32_t groups = g_min, ranges = 1;
-    double best = 0;
-    for (uint32_t g = g_min; g <= std::max(g_min, std::min(P, cus)); ++g) {
-      const uint32_t tg = (P + g - 1) / g;
-      if (g > g_min && tg == (P + g - 2) / (g - 1)) continue;
-      uint32_t rg = std::max(1u, std::min(units, cus / g));
-      const uint32_t chains = tg > 2 * NG ? (tg + 3) / 4 * 4 : tg;
-      for (uint32_t r = rg;; r &= ~7u) {
-        const uint32_t per = (units + r - 1) / r;
-        const double c =
-            per * (8.4 * chains * D + (r % 8 ? 12.0 : 8.0) * Fs + 2000.0 * 64 / T) +
-            1.5 * tg * SL * K;
-        if (best == 0 || c < best) {
-          best = c;
-          groups = g;
-          ranges = r;
-        }
-        if (r < 8 || r % 8 == 0) break;
-      }
-    }
-    a.TG = (P + groups - 1) / groups;
-    groups = (P + a.TG - 1) / a.TG;
-    const size_t lds = tile_bytes + ((a.TG * tree_nodes + 7) & ~(size_t)7) +
-                       (a.hist_in_lds ? a.TG * tree_hist : 0);
-    const size_t lds_al = (lds + 15) & ~(size_t)15;
-    a.per = (units + ranges - 1) / ranges;
-    ranges = (units + a.per - 1) / a.per;
-    // trees a lane walks at once
-    const uint32_t gi = (a.TG + NG - 1) / NG;
+    a.leafcnt = leafcnt;
+    const size_t lds = (w.lds + 15) & ~(size_t)15;
+    if (ctx->debug)
+      std::fprintf(stderr, "%s: grid %u x %u, %u trees and %u samples per block, LDS %zu bytes%s\n",
+                   w.direct ? "k_walk_direct" : "k_walk_tiles", w.ranges, w.groups, w.TG,
+                   64u * w.per, lds, weight ? ", weights" : "");
     hipEvent_t e0, e1;
     const bool timed = prof_pair(ctx, &e0, &e1);
-    const dim3 grid(ranges, groups);
-#define MH_WALK(TV, GIV, WV, SV)                                                             \
-  hipExtLaunchKernelGGL((k_walk_tiles<TV, GIV, WV, SV>), grid, dim3(WT_THREADS), lds_al, st, e0, \
+    const dim3 grid(w.ranges, w.groups);
+#define MH_WALK(TV, GIV, WV, SV)                                                              \
+  hipExtLaunchKernelGGL((k_walk_tiles<TV, GIV, WV, SV>), grid, dim3(WT_THREADS), lds, st, e0, \
                         e1, 0, a)
 #define MH_WALK_T(GIV, WV, SV)                    \
-  switch (T) {                                    \
+  switch (w.T) {                                  \
     case 1024: MH_WALK(1024, GIV, WV, SV); break; \
     case 512: MH_WALK(512, GIV, WV, SV); break;   \
     case 256: MH_WALK(256, GIV, WV, SV); break;   \
     default: MH_WALK(128, GIV, WV, SV); break;    \
   }
-    if (wide) {
+    // trees a lane walks at once
+    const uint32_t NG = WT_THREADS / w.T, gi = (w.TG + NG - 1) / NG;
+    if (w.direct) {
+      if (w.T == 8)
+        hipExtLaunchKernelGGL(k_walk_direct<8>, grid, dim3(WD_THREADS), lds, st, e0, e1, 0, a);
+      else
+        hipExtLaunchKernelGGL(k_walk_direct<4>, grid, dim3(WD_THREADS), lds, st, e0, e1, 0, a);
+    } else if (w.wide) {
       MH_WALK_T(4, true, false);
-    } else if (sel && gi <= 2) {
+    } else if (w.sel && gi <= 2) {
       MH_WALK_T(1, false, true);
-    } else if (sel) {
+    } else if (w.sel) {
       MH_WALK_T(4, false, true);
     } else if (gi <= 1) {
       MH_WALK_T(1, false, false);
@@ -937,7 +1121,7 @@ mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *id
     }
 #undef MH_WALK_T
 #undef MH_WALK
-    MH_LAUNCHED(ctx, "k_walk_tiles");
+    MH_LAUNCHED(ctx, w.direct ? "k_walk_direct" : "k_walk_tiles");
     if (timed) ctx->prof_launches += 1;
     ctx->prof_evals += (uint64_t)n_sub * P;
   }

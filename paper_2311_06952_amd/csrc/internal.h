@@ -290,12 +290,19 @@ mh_status launch_fitness_jobs(Ctx *ctx, uint32_t D, uint32_t waves, uint32_t F_m
 // Direct per-sample walk for any depth (1..10): one tree at a time, leaf
 // counts per (tree, leaf, class), then the same epilogue.
 // leafcnt: walk_scratch_bytes(P, D, K) of device scratch the call may use
-// (null: the context arena's): the leaf counts.
+// (null: the context arena's): the leaf counts.  weight: how often idx names
+// each sample (walk_weights), to walk all samples by; null: the samples of idx.
 size_t walk_scratch_bytes(uint32_t P, uint32_t D, uint32_t K);
+// Whether counting that pays for `evaluations` of P trees on the subset; and the
+// counts, in the context's arena until the next call (null: no room for them).
+bool walk_weighs(const Ctx *ctx, const mh_dataset *ds, uint32_t n_sub, uint32_t P, uint32_t D,
+                 uint32_t evaluations);
+const uint32_t *walk_weights(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx, uint32_t n_sub);
 mh_status launch_fitness_walk(Ctx *ctx, const mh_dataset *ds, const uint32_t *idx,
                               uint32_t n_sub, const uint8_t *feat, const uint32_t *tau,
                               uint32_t P, uint32_t D, uint32_t n_min, double alpha,
-                              const FitnessOut &out, uint32_t *leafcnt = nullptr);
+                              const FitnessOut &out, uint32_t *leafcnt = nullptr,
+                              const uint32_t *weight = nullptr);
 
 // de.hip
 // Population layouts: row-major [P][m] (the C ABI) or gene-major [m][P]

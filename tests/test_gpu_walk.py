@@ -184,3 +184,78 @@ def test_walk_subset_near_the_32_bit_limit(static):
     torch.cuda.empty_cache()
     want = 4095 * _near_limit_counts(n, tau) + _near_limit_counts(n - 5, tau)
     np.testing.assert_array_equal(got, want)
+
+
+# The form of the walk by shape and by kind of call (all samples; a random half,
+# counted in the call's own scratch or gathered in a caller's; every sample three
+# times over): tiles, direct or weights.  One tree to a group's remainder, four
+# and eight chains, counts in LDS and (many classes at depth 9 and 10) in memory.
+@pytest.mark.parametrize("n,F,K,P,D,forms", [
+    (1, 49, 2, 1, 6, ("direct", "direct", "direct")),
+    (255, 100, 2, 7, 6, ("direct", "direct", "direct")),
+    (257, 200, 3, 8, 5, ("direct", "direct", "direct")),
+    (4097, 255, 4, 33, 1, ("direct", "direct", "direct")),
+    (1500, 120, 254, 5, 10, ("direct", "direct", "direct")),
+    (2000, 90, 200, 13, 9, ("direct", "direct", "direct")),
+    (70_001, 130, 2, 3, 7, ("tiles", "direct", "weights")),
+    (3000, 60, 2, 65, 6, ("tiles", "tiles", "weights")),
+    (513, 128, 20, 70, 7, ("tiles", "direct", "direct")),
+])
+def test_walk_forms(mh_mod, monkeypatch, capfd, n, F, K, P, D, forms):
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")
+    ctx = mh_mod.Context(0)
+    X, y = synth.random_small(n + F, n, F, K, levels=None if n % 2 else 30)
+    ods = oracle.dataset_from_X(X, y, K)
+    ds = mh_mod.dataset(X, y, K, ctx=ctx)
+    rng = np.random.default_rng(n + P)
+    feat, tau = random_trees(rng, P, D, F, ods.n_unique)
+    half = rng.integers(0, n, size=n // 2 + 1).astype(np.uint32)
+    thrice = np.tile(np.arange(n, dtype=np.uint32), 3)
+    for idx, form in zip((None, half, thrice), forms):
+        want = oracle.fitness(ods, feat, tau, D, idx=idx, n_min=2, alpha=0.5)
+        for static in (False, True):
+            capfd.readouterr()
+            got = mh_mod.fitness_eval(ds, dev(feat), dev(tau), D, ctx=ctx,
+                                      idx=None if idx is None else dev(idx),
+                                      n_min=2, alpha=0.5, static=static)
+            line = [e for e in capfd.readouterr().err.splitlines() if e.startswith("k_walk")]
+            assert len(line) == 1
+            assert ("k_walk_direct" in line[0]) == (form == "direct") or static
+            assert ("weights" in line[0]) == (form == "weights" and not static)
+            for k in range(2):
+                np.testing.assert_array_equal(u32(got[k]), want[k])
+            for k in (2, 3):
+                np.testing.assert_array_equal(np_(got[k]), want[k])
+    # entries past n are left out
+    bad = np.concatenate([half, np.array([n, 2**32 - 1], np.uint32)])
+    want = oracle.fitness(ods, feat, tau, D, idx=half, n_min=2, alpha=0.5)
+    for static in (False, True):
+        got = mh_mod.fitness_eval(ds, dev(feat), dev(tau), D, idx=dev(bad), ctx=ctx,
+                                  n_min=2, alpha=0.5, static=static)
+        np.testing.assert_array_equal(u32(got[0]), want[0])
+    ctx.close()
+
+
+def test_walk_weights_of_a_run(mh_mod, monkeypatch, capfd):
+    """A run counts its subset once for all generations; the next run's subset
+    replaces it, also one that is gathered."""
+    n, F, K, D, prm = 4001, 9, 3, 7, (21, 40, 0.5, 0.7, 5, 1, 0.0)
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")
+    ctx = mh_mod.Context(0)
+    X, y = synth.random_small(11, n, F, K)
+    ods = oracle.dataset_from_X(X, y, K)
+    ds = mh_mod.dataset(X, y, K, ctx=ctx)
+    rng = np.random.default_rng(12)
+    for size in (12_003, 11_000, 50, 12_003):
+        idx = rng.integers(0, n, size=size).astype(np.uint32)
+        want = oracle.deoct(ods, D, oracle.de_params(*prm), idx=idx, with_pop=True)
+        capfd.readouterr()
+        got = mh_mod.subtree_solve(ds, D, mh_mod.de_params(*prm), idx=dev(idx), ctx=ctx,
+                                   with_pop=True)
+        lines = [e for e in capfd.readouterr().err.splitlines() if e.startswith("k_walk")]
+        assert len(lines) == 42  # the first population, 40 trials and the best tree
+        assert all(("weights" in e) == (size > 50) for e in lines)
+        for key in ("feat", "tau", "label", "pop", "pop_cost"):
+            np.testing.assert_array_equal(got[key], want[key])
+        assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
+    ctx.close()
