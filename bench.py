@@ -114,6 +114,8 @@ def ds_of(mh, Xd, yd, w, ctx):
 def kernel_name(w, form, tuned):
     waves = min(8, max(1, (w.P + 63) // 64))
     waves = 8 if waves > 4 else (4 if waves > 2 else waves)
+    if form == "persistent" and tuned["persist_blocks_per_cu"] == 0:
+        return f"k_deoct_resident<{w.D},{waves}> or k_deoct_persist<{w.D},{waves},...>, by size"
     if form == "persistent":
         return f"k_deoct_persist<{w.D},{waves},{tuned['halves']},...>"
     return f"k_fitness_bits<{w.D},{waves},false>"

@@ -557,8 +557,10 @@ mh_status mh_ctx_create(int device, void *hip_stream, mh_ctx **out) {
   if (const char *v = std::getenv("MHDEOCT_PERSIST")) c->c.persist = atoi(v) != 0;
   if (const char *v = std::getenv("MHDEOCT_PERSIST_RESIDENT"))
     c->c.persist_resident = atoi(v) != 0;
-  if (const char *v = std::getenv("MHDEOCT_PERSIST_HALVES"))
+  if (const char *v = std::getenv("MHDEOCT_PERSIST_HALVES")) {
     c->c.persist_halves = atoi(v) >= 4 ? 4u : (atoi(v) == 1 ? 1u : 2u);
+    c->c.persist_halves_set = true;
+  }
   if (const char *v = std::getenv("MHDEOCT_PERSIST_BLOCKS_PER_CU"))
     c->c.persist_blocks_per_cu = (uint32_t)std::max(1, atoi(v));
   if (const char *v = std::getenv("MHDEOCT_RESIDENT_BLOCKS"))
@@ -788,16 +790,18 @@ static mh_status deoct_tuned(Ctx *c, const mh_dataset *ds, const uint32_t *idx, 
   const uint32_t tb = tiles_bucket(tile_layout(n_sub, ds->F, ds->K, 1).max_tiles, (uint32_t)c->num_cu);
   for (const Ctx::Tuned &t : c->tuned) {
     if (t.D == D && t.P == prm->P && t.F == ds->F && t.K == ds->K && t.tiles_bucket == tb) {
-      const bool p0 = c->persist;
+      const bool p0 = c->persist, hs0 = c->persist_halves_set;
       const uint32_t h0 = c->persist_halves, b0 = c->persist_blocks_per_cu,
                      f0 = c->fit_blocks_per_cu;
       c->persist = t.persist != 0;
       c->persist_halves = t.halves;
+      c->persist_halves_set = t.persist_bpc != 0;
       c->persist_blocks_per_cu = t.persist_bpc;
       c->fit_blocks_per_cu = t.fit_bpc;
       const mh_status s = deoct(c, ds, idx, n_sub, D, prm, warm, W, prob, out);
       c->persist = p0;
       c->persist_halves = h0;
+      c->persist_halves_set = hs0;
       c->persist_blocks_per_cu = b0;
       c->fit_blocks_per_cu = f0;
       return s;
@@ -856,19 +860,24 @@ mh_status mh_autotune(mh_ctx *ctx, const mh_dataset *ds, uint32_t D, const mh_de
   if (generations == 0) return fail(c, MH_EINVAL, "generations must be >= 1");
   s = check_ds_status(c, ds);
   if (s) return s;
-  // candidates: the whole-run kernel with one or two tile streams per block
-  // and 1, 2 or 4 blocks per CU, and the per-generation kernels with 1, 2 or
-  // 4 fitness blocks per CU
+  // candidates: the whole-run kernel with one, two or four tile streams per
+  // block and 1, 2 or 4 blocks per CU, and the per-generation kernels with 1, 2
+  // or 4 fitness blocks per CU.  Where the run's own form is none of these (0
+  // blocks per CU) it takes the place of the one that suits such a size least:
+  // the most waves for tiles that fit the LDS, the fewest for tiles that do not.
   struct Cand {
     uint32_t persist, halves, persist_bpc, fit_bpc;
   };
   std::vector<Cand> cands;
   for (uint32_t hv : {4u, 2u, 1u})
     for (uint32_t b : {1u, 2u, 4u}) cands.push_back({1u, hv, b, c->fit_blocks_per_cu});
+  const WholeRunForm form = whole_run_form(c, ds->F, ds->K, ds->n, D, prm->P);
+  if (form == WholeRunForm::resident) cands[2] = {1u, 2u, 0u, c->fit_blocks_per_cu};
+  if (form == WholeRunForm::four_staged) cands[6] = {1u, 2u, 0u, c->fit_blocks_per_cu};
   for (uint32_t b : {1u, 2u, 4u}) cands.push_back({0u, 2u, 0u, b});
   mh_de_params p = *prm;
   p.G = generations;
-  const bool p0 = c->persist;
+  const bool p0 = c->persist, hs0 = c->persist_halves_set;
   const uint32_t h0 = c->persist_halves, b0 = c->persist_blocks_per_cu, f0 = c->fit_blocks_per_cu;
   std::memset(out, 0, sizeof(*out));
   out->n_candidates = (uint32_t)std::min<size_t>(cands.size(), 16);
@@ -879,6 +888,7 @@ mh_status mh_autotune(mh_ctx *ctx, const mh_dataset *ds, uint32_t D, const mh_de
     const Cand &cd = cands[i];
     c->persist = cd.persist != 0;
     c->persist_halves = cd.halves;
+    c->persist_halves_set = cd.persist_bpc != 0;
     c->persist_blocks_per_cu = cd.persist_bpc;
     c->fit_blocks_per_cu = cd.fit_bpc;
     // one untimed run, then the median of three timed ones (each run
@@ -900,6 +910,7 @@ mh_status mh_autotune(mh_ctx *ctx, const mh_dataset *ds, uint32_t D, const mh_de
   }
   c->persist = p0;
   c->persist_halves = h0;
+  c->persist_halves_set = hs0;
   c->persist_blocks_per_cu = b0;
   c->fit_blocks_per_cu = f0;
   if (s) return s;

@@ -55,6 +55,10 @@ struct Ctx {
   bool persist = true;   // whole DEOCT runs as one cooperative launch (MHDEOCT_PERSIST=0 turns off)
   uint32_t persist_blocks_per_cu = 0;  // its blocks per CU; 0 = by size (MHDEOCT_PERSIST_BLOCKS_PER_CU)
   uint32_t persist_halves = 2;         // tile streams per block, 1, 2 or 4 (MHDEOCT_PERSIST_HALVES)
+  bool persist_halves_set = false;     // asked for (environment, tuner), not the default
+  // (streams or blocks asked for: neither the resident form of resident.hip nor
+  // four streams by size, which have none of the two to choose, is taken)
+  bool persist_asked() const { return persist_blocks_per_cu != 0 || persist_halves_set; }
   bool persist_resident = true;        // tiles kept in LDS when they fit (MHDEOCT_PERSIST_RESIDENT)
   uint32_t resident_blocks = 0;  // blocks of a resident run; 0 = by size (MHDEOCT_RESIDENT_BLOCKS)
   bool coop = false;     // the device supports cooperative launches
@@ -421,6 +425,11 @@ mh_status launch_deoct_persist(Ctx *ctx, const void *tiles, uint32_t F, uint32_t
 // per problem), cost ([P] per problem) and best ([n_problems]).
 // class_counts: HOST [n_problems][K] samples per class (as in the layout);
 // prob_ids: device [n_problems]; host_ids: the same on the host.
+// The form a lone run takes when no streams or blocks per CU are asked for:
+// resident (resident.hip), four staged streams, or streams and blocks by size.
+enum class WholeRunForm { by_size, resident, four_staged };
+WholeRunForm whole_run_form(const Ctx *ctx, uint32_t F, uint32_t K, uint32_t n, uint32_t D,
+                            uint32_t P);
 mh_status launch_deoct_persist_multi(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K,
                                      uint32_t n_sub, uint32_t n_problems,
                                      const uint32_t *class_counts, uint32_t D,

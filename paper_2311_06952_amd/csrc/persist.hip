@@ -758,7 +758,7 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
                    // per-generation kernels
   // four groups by the rule of four_staged (fewer were asked for): staged, and
   // only where they put more waves on a CU than two groups per block
-  const bool auto4 = H == 4 && ctx->persist_halves < 4;
+  const bool auto4 = H == 4 && !ctx->persist_asked();
   if constexpr (H == 4 && D <= 3) {
     const void *two = pa.F >= PERSIST_COMPACT_MIN_F
                           ? reinterpret_cast<const void *>(k_deoct_persist<D, WAVES, 2, false, true>)
@@ -897,9 +897,15 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
 bool four_staged(const Ctx *ctx, uint32_t D, uint32_t waves, uint32_t F, uint32_t P,
                  uint32_t max_tiles) {
   const uint64_t tile = align16u(mask_region(F) + F * MCOL);
-  return D <= 3 && waves <= 4 && ctx->persist_halves == 2 &&
+  return D <= 3 && waves <= 4 && !ctx->persist_asked() &&
          persist_lds_bytes(F, P, (1u << D) - 1u, 4) <= ctx->max_lds &&
          max_tiles * tile > (uint64_t)ctx->num_cu * ctx->max_lds;
+}
+
+// Waves of a group: those of the population, rounded up to 1, 2, 4 or 8.
+uint32_t wave_width(uint32_t P) {
+  const uint32_t w = pad64(P) / 64;
+  return w > 4 ? 8 : (w > 2 ? 4 : w);
 }
 
 template <int D, int H>
@@ -927,6 +933,12 @@ mh_status launch_dh(Ctx *ctx, uint32_t waves, uint32_t H, const PersistArgs &pa,
   return launch_d<D, 1>(ctx, waves, pa, lds, max_tiles, gr, used);
 }
 
+// (the bound counts a ragged tile for every class: half of a tile each, likely,
+// and a tile at least)
+uint32_t likely_tiles(uint32_t max_tiles, uint32_t K, uint32_t n_sub) {
+  return std::max(std::min(K, n_sub), max_tiles - K / 2);
+}
+
 // The same run with its tiles resident in LDS (resident.hip), when every
 // problem's share fits.
 mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint32_t n_sub,
@@ -943,10 +955,8 @@ mh_status resident_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint
   const uint32_t max_tiles = tile_layout(n_sub, F, K, n_problems).max_tiles;
   std::vector<RunShape> sh(n_problems);
   auto tiles_of = [&](uint32_t i) { return ptiles ? (*ptiles)[i] : max_tiles; };
-  // (the bound counts a ragged tile for every class: half of a tile each,
-  // likely, and a tile at least)
   auto likely = [&](uint32_t i) {
-    return ptiles ? (*ptiles)[i] : std::max(std::min(K, n_sub), max_tiles - K / 2);
+    return ptiles ? (*ptiles)[i] : likely_tiles(max_tiles, K, n_sub);
   };
   uint64_t total = 0, all_tiles = 0;
   for (uint32_t i = 0; i < n_problems; ++i) {
@@ -1047,13 +1057,12 @@ mh_status persist_run(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K, uint3
   // barrier targets (G + 2) * blocks, up to two barriers per generation, must
   // fit the 32-bit arrival counters
   if ((uint64_t)(prm->G + 2) * (uint64_t)ctx->num_cu * 8u >= (1ull << 31)) return MH_OK;
-  if (ctx->persist_resident) {
+  if (ctx->persist_resident && !ctx->persist_asked()) {
     const mh_status rs = resident_run(ctx, tiles, F, K, n_sub, n_eval, n_problems, D, prm, prob,
                                       host_ids, ptiles, n_unique, pop, cost, best, err, fin, used);
     if (rs || *used) return rs;
   }
-  uint32_t waves = pad64(P) / 64;
-  waves = waves > 4 ? 8 : (waves > 2 ? 4 : waves);
+  const uint32_t waves = wave_width(P);
   // up to persist_halves tile streams per block, as the LDS and the
   // 1024-thread limit allow
   const uint32_t max_lds = ctx->max_lds;
@@ -1144,6 +1153,19 @@ mh_status launch_deoct_persist(Ctx *ctx, const void *tiles, uint32_t F, uint32_t
                                bool *used) {
   return persist_run(ctx, tiles, F, K, n_sub, n_sub, 1, D, prm, prob, nullptr, nullptr, nullptr, n_unique,
                      pop, cost, best, err, fin, used);
+}
+
+WholeRunForm whole_run_form(const Ctx *ctx, uint32_t F, uint32_t K, uint32_t n, uint32_t D,
+                            uint32_t P) {
+  if (!ctx->coop || D < 1 || D > 5 || P > 512 || F > 80 || ctx->persist_asked())
+    return WholeRunForm::by_size;
+  const uint32_t max_tiles = tile_layout(n, F, K, 1).max_tiles;
+  if (ctx->persist_resident && resident_shape(ctx, D, P, F, K, max_tiles,
+                                              likely_tiles(max_tiles, K, n),
+                                              (uint32_t)ctx->num_cu).nblk)
+    return WholeRunForm::resident;
+  return four_staged(ctx, D, wave_width(P), F, P, max_tiles) ? WholeRunForm::four_staged
+                                                             : WholeRunForm::by_size;
 }
 
 mh_status launch_deoct_persist_multi(Ctx *ctx, const void *tiles, uint32_t F, uint32_t K,

@@ -72,3 +72,54 @@ def test_problems_of_unequal_size(mh, monkeypatch, share):
     for key in ("feat", "tau", "label"):
         np.testing.assert_array_equal(got[key], want[key])
     assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
+
+
+# (D, P, K, n, F): a run that is resident when nothing is asked for, and one of
+# four staged groups
+@pytest.mark.parametrize("D,P,K,n,F", [(3, 100, 2, 2000, 4), (2, 9, 3, 175_000, 20)])
+@pytest.mark.parametrize("switch,value,groups", [
+    ("MHDEOCT_PERSIST_HALVES", "1", 1), ("MHDEOCT_PERSIST_HALVES", "2", 2),
+    ("MHDEOCT_PERSIST_BLOCKS_PER_CU", "1", 2)])
+def test_asked_groups_and_blocks_run(mh, monkeypatch, capfd, switch, value, groups, D, P, K, n, F):
+    """Groups or blocks per CU that are asked for are those that run."""
+    from paper_2311_06952_amd import capi
+    monkeypatch.setenv(switch, value)
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")
+    X, y = synth.random_small(D * 100 + P, n, F, K)
+    ctx = capi.Context(0)
+    capfd.readouterr()
+    _check(mh, ctx, X, y, K, D, (P, 3, 0.5, 0.9, 3, 1, 0.0))
+    err = capfd.readouterr().err
+    ctx.close()
+    assert "k_deoct_resident" not in err
+    assert f"k_deoct_persist<{D},{(P + 63) // 64},{groups}," in err
+
+
+@pytest.mark.parametrize("D,P,K,n,F,form", [
+    (3, 100, 2, 2000, 4, "k_deoct_resident<"), (2, 9, 3, 175_000, 20, "k_deoct_persist<2,1,4,")])
+def test_tuner_times_the_form_of_its_own_choice(mh, monkeypatch, capfd, D, P, K, n, F, form):
+    """Twelve candidates, one of them the form that runs when nothing is tuned
+    (0 blocks per CU); later runs take the winner's form."""
+    from paper_2311_06952_amd import capi
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")
+    X, y = synth.random_small(D * 100 + P, n, F, K)
+    ctx = capi.Context(0)
+    ds = mh.dataset(X, y, K, ctx=ctx)
+    capfd.readouterr()
+    tuned = mh.autotune(ds, D, mh.de_params(P, 5, 0.5, 0.9, 3), generations=5, ctx=ctx)
+    lines = [e for e in capfd.readouterr().err.splitlines() if e.startswith("k_deoct")]
+    own = [e for e in lines if e.startswith(form)]
+    assert len(tuned["ms"]) == 12
+    # each candidate runs four times; four groups are asked for at 1, 2 and 4 blocks too
+    assert len(own) == (4 if "resident" in form else 16)
+    assert len(lines) == 36
+    prm = (P, 5, 0.5, 0.9, 8, 1, 0.0)
+    _check(mh, ctx, X, y, K, D, prm)
+    err = capfd.readouterr().err
+    ctx.close()
+    if tuned["persist"] == 0:
+        assert "k_deoct" not in err
+    elif tuned["persist_blocks_per_cu"] == 0:
+        assert form in err
+    else:
+        assert f"k_deoct_persist<{D},{(P + 63) // 64},{tuned['halves']}," in err
