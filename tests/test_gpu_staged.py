@@ -123,3 +123,38 @@ def test_tuner_times_the_form_of_its_own_choice(mh, monkeypatch, capfd, D, P, K,
         assert form in err
     else:
         assert f"k_deoct_persist<{D},{(P + 63) // 64},{tuned['halves']}," in err
+
+
+@pytest.mark.parametrize("D,D_MH", [(4, 2), (5, 3)])
+@pytest.mark.parametrize("share", [0.004, 0.31, 0.97])
+@pytest.mark.parametrize("resident", ["0", "1"])
+def test_runs_of_unequal_problems(mh, monkeypatch, capfd, resident, share, D, D_MH):
+    """Several problems of very different sizes in one launch of the staged
+    whole-run kernel and, its blocks scaled down to the CUs, of the resident
+    one."""
+    from paper_2311_06952_amd import capi
+    monkeypatch.setenv("MHDEOCT_PERSIST", "1")
+    monkeypatch.setenv("MHDEOCT_PERSIST_RESIDENT", resident)
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")
+    n, F, K = 120_000, 5, 3
+    rng = np.random.default_rng(int(share * 1000) + D_MH)
+    X = rng.normal(size=(n, F)).astype(np.float32)
+    cut = np.quantile(X[:, 0], share)
+    y = np.where(X[:, 0] < cut, 2, (X[:, 1] > 0.3).astype(int)).astype(np.uint8)
+    y[rng.random(n) < 0.05] = 1
+    prm = (20, 6, 0.5, 0.8, 11, 1, 0.0)
+    want = oracle.mh_train(oracle.dataset_from_X(X, y, K), D, D_MH, oracle.de_params(*prm))
+    ctx = capi.Context(0)
+    ds = mh.dataset(X, y, K, ctx=ctx)
+    capfd.readouterr()
+    got = mh.mh_train(ds, D, D_MH, mh.de_params(*prm), batched=True, ctx=ctx)
+    err = capfd.readouterr().err
+    ctx.close()
+    runs = [int(e.split()[1]) for e in err.splitlines() if e.startswith("k_deoct_resident")]
+    assert bool(runs) == (resident == "1" and D_MH == 3)
+    if runs and share > 0.3:  # (their own best numbers of blocks add up to more than the CUs)
+        assert max(runs) >= 3
+    assert len(runs) + err.count("k_deoct_persist") == D - 1
+    for key in ("feat", "tau", "label"):
+        np.testing.assert_array_equal(got[key], want[key])
+    assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
