@@ -516,9 +516,7 @@ mh_status launch_de_gen(Ctx *ctx, const DeDev &de, const uint64_t *prob_ids, uin
                         uint32_t n_min, double alpha) {
   StepArgs a = make_args(de, prob_ids, prob_base, g, pop, cost, trial, nullptr, best, next_trial,
                          feat, tau);
-  const uint32_t rp = step_threads(de.P);
-  const uint32_t tpi = 1;  // more threads per individual measured slower
-  GenArgs e{cnt, ctot, K, n_min, alpha, init ? 1 : 0, tpi, n_problems};
+  GenArgs e{cnt, ctot, K, n_min, alpha, init ? 1 : 0, n_problems};
   if (de.P >= DE_SPLIT_MIN_P || de.D >= DE_SPLIT_MIN_D) {
     // large populations: the generation as two launches spread over the chip
     hipStream_t st = ctx->stream;
@@ -540,7 +538,8 @@ mh_status launch_de_gen(Ctx *ctx, const DeDev &de, const uint64_t *prob_ids, uin
     MH_LAUNCHED(ctx, "k_de_select/k_de_mutate");
     return MH_OK;
   }
-  const uint32_t threads = rp * tpi;
+  // (one thread per individual: more measured slower)
+  const uint32_t threads = step_threads(de.P);
   const size_t lds = rows_lds_bytes(de.P, de.D, de_rows_limit(ctx));
   a.rows_in_lds = lds > 0;
   hipStream_t st = ctx->stream;
@@ -568,7 +567,7 @@ GenJob make_gen_job(const DeDev &de, uint64_t prob, uint32_t g, bool init, doubl
   j.a = make_args(de, nullptr, prob, g, pop, cost, trial, nullptr, best, next_trial, feat, tau);
   // every job of a launch shares the dynamic LDS sized for the largest one
   j.a.rows_in_lds = rows_lds_bytes(P_max, de.D) > 0;
-  j.e = GenArgs{cnt, ctot, K, n_min, alpha, init ? 1 : 0, 1u, 1u};
+  j.e = GenArgs{cnt, ctot, K, n_min, alpha, init ? 1 : 0, 1u};
   return j;
 }
 
@@ -605,7 +604,7 @@ FuseArgs make_fuse(const DeDev &de, const uint64_t *prob_ids, uint64_t prob_base
   FuseArgs f;
   f.a = make_args(de, prob_ids, prob_base, g, pop, cost, trial, nullptr, best, next_trial, feat,
                   tau);
-  f.e = GenArgs{cnt, ctot, K, n_min, alpha, init ? 1 : 0, 1u, n_problems};
+  f.e = GenArgs{cnt, ctot, K, n_min, alpha, init ? 1 : 0, n_problems};
   f.done = done;
   f.segoff = segoff;
   f.rows_in_lds = rows_lds_bytes(de.P, de.D) > 0 ? 1u : 0u;

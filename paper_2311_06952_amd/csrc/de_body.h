@@ -159,7 +159,6 @@ struct GenArgs {
   uint32_t K, n_min;
   double alpha;
   int init;
-  uint32_t tpi;         // threads per individual
   uint32_t n_problems;  // problems in the count buffer (replica stride)
 };
 

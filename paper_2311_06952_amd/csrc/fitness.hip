@@ -243,12 +243,9 @@ constexpr uint32_t EPI_THREADS = 256;
 // and the soft-constraint fitness of Section 3.2), by a block of EPI_THREADS
 // threads: labels (lowest class of the largest count, an empty leaf class
 // 0), correct count and cost, and the counts cleared after they are read.
-// COH: the counts were added by other blocks of the same launch (read with
-// agent-scope loads).  Called by every thread of the block.  (Scoring a
-// group's trees in the walk launch's last block instead of this separate
-// launch was measured slower: that block's coherent loads ran one after
-// another at the end of the launch.)
-template <bool COH>
+// Called by every thread of the block.  (Scoring a group's trees in the walk
+// launch's last block instead of this separate launch was measured slower: that
+// block's coherent loads ran one after another at the end of the launch.)
 __device__ __forceinline__ void leaf_epilogue_tree(uint32_t *__restrict__ leafcnt,
                                                    const uint8_t *__restrict__ feat, uint32_t r,
                                                    uint32_t D, uint32_t K, uint32_t n_min,
@@ -260,7 +257,7 @@ __device__ __forceinline__ void leaf_epilogue_tree(uint32_t *__restrict__ leafcn
     uint32_t *c = leafcnt + ((size_t)r * SL + l) * K;
     uint32_t best = 0, bk = 0, nl = 0;
     for (uint32_t k = 0; k < K; ++k) {
-      const uint32_t v = cnt_load<COH>(c + k);
+      const uint32_t v = c[k];
       c[k] = 0;
       if (out.counts) out.counts[((size_t)r * SL + l) * K + k] = v;
       nl += v;
@@ -709,7 +706,7 @@ __global__ __launch_bounds__(EPI_THREADS) void k_epilogue_leaves(
     uint32_t K, uint32_t n_min, double alpha, FitnessOut out) {
   __shared__ uint32_t s_red[4][EPI_THREADS / 64];
   if (blockIdx.x >= P) return;
-  leaf_epilogue_tree<false>(leafcnt, feat, blockIdx.x, D, K, n_min, alpha, out, s_red);
+  leaf_epilogue_tree(leafcnt, feat, blockIdx.x, D, K, n_min, alpha, out, s_red);
 }
 
 // Launches on st; when e0/e1 are given the launch records them at the
