@@ -53,3 +53,11 @@ def test_class_read_from_labels(mh):
     X = rng.random((n, 2), dtype=np.float32)
     y = ((X[:, 0] > 0.4).astype(np.uint8) + (rng.random(n) < 0.1)).astype(np.uint8)
     _check(mh, X, y, 3, 2)
+
+
+# rows of spans around the last one a wave scans (256) and the steps of the
+# block that scans longer ones (4,096)
+@pytest.mark.parametrize("spans", [255, 256, 257, 4095, 4096, 4097, 8193])
+def test_row_scan_lengths(mh, spans):
+    X, y = synth.random_small(spans, spans * 512 - 100, 1, 3, 5000 if spans % 2 else None)
+    _check(mh, X, y, 3, 2)
