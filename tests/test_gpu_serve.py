@@ -339,7 +339,7 @@ def test_served_small_groups_use_idle_units(mh, monkeypatch, capfd):
     assert blocks[0] > 32 and blocks[1] > 32 and blocks[3] <= 4 and max(blocks) <= 256
 
 
-def test_stepped_request_advances_beside_a_stream_of_small_ones(mh):
+def test_stepped_request_advances_beside_a_stream_of_small_ones(mh, monkeypatch, capfd):
     """A request that is stepped has the device between two groups for as long as
     a group took: few small requests, submitted one a round, run before it ends
     (with a group every round it would be one for each of its generations)."""
@@ -348,10 +348,12 @@ def test_stepped_request_advances_beside_a_stream_of_small_ones(mh):
     G, small = 300, (91, 6000, 8, 3, 4, 100, 60, 0.5)
     X, y = _data(*small[:4])
     Xd, yd = torch.as_tensor(X).cuda(), torch.as_tensor(y).cuda()
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")  # a line for each group
     ctx = capi.Context(0)
     srv = mh.Server(1 << 30, 64, ctx=ctx)
     _submit(mh, srv, (90, 3000, 6, 3, 3, 200, G, 0.5))
-    res, k, before = {}, 0, None
+    res, k, before, groups = {}, 0, None, 0
+    capfd.readouterr()
     for _ in range(20 * G):
         if before is None:
             k += 1
@@ -361,15 +363,14 @@ def test_stepped_request_advances_beside_a_stream_of_small_ones(mh):
             res[r["req_id"]] = r
             if r["req_id"] == 90:
                 before = len(res) - 1
+                groups = capfd.readouterr().err.count("k_deoct_resident_queue")
         if left == (0, 0):
             break
     srv.close()
     ctx.close()
     assert before is not None and len(res) == k + 1
     assert all(r["status"] == 0 for r in res.values())
-    # a round admits what has queued up, so count the groups by their ends
-    groups = len({r["t_done_ns"] // 1000 for r in res.values() if r["t_done_ns"] <= res[90]["t_done_ns"]})
-    assert groups < G // 3
+    assert 0 < groups < G // 3
     Xl, yl = _data(90, 3000, 6, 3)
     want = oracle.deoct(oracle.dataset_from_X(Xl, yl, 3), 3, oracle.de_params(200, G, 0.5, 0.9, 7090))
     _same(res[90]["tree"], want)
