@@ -101,6 +101,7 @@ bool coop_is_bad(const Ctx *ctx, const void *kern, uint32_t grid) {
 }
 
 void coop_note_bad(Ctx *ctx, const void *kern, uint32_t grid) {
+  if (ctx->debug) std::fprintf(stderr, "a grid barrier gave up: grid %u\n", grid);
   if (kern && !coop_is_bad(ctx, kern, grid)) ctx->coop_bad.push_back({kern, grid});
 }
 

@@ -862,12 +862,22 @@ mh_status launch_w(Ctx *ctx, const PersistArgs &pa, uint32_t lds, uint32_t max_t
   if (!a.tph && !kstage) return MH_OK;  // no staged form
   if (!a.tph) kern = kstage;
   if (coop_is_bad(ctx, kern, grid)) return MH_OK;
+  // Several blocks of four groups fill a CU's registers.  Waves of another
+  // stream's kernel that are there when the first of them starts can spread its
+  // waves over the SIMDs so that the next finds no place, also when they are
+  // gone, and the barrier waits for it in vain: a third of runs of 2,000 served
+  // requests, whose data other kernels make meanwhile, stood still for 2 s (two
+  // groups: none of 12).  Such a launch gives up sooner, far above what blocks
+  // that run wait for each other (a tile takes about 2 us), and its work is done
+  // by fewer groups from then on.
+  if (H == 4 && grid > (uint32_t)ctx->num_cu)
+    a.wait_ticks = std::min<uint64_t>(a.wait_ticks, 2000000ull + 2000ull * per_block);
   if (ctx->debug)
     std::fprintf(stderr,
                  "k_deoct_persist<%d,%d,%d,%s>: grid %u (per CU %d by occupancy), tiles %u "
-                 "(per block %u), LDS %u bytes\n",
+                 "(per block %u), LDS %u bytes, waits up to %u ms\n",
                  D, WAVES, H, a.tph ? "true" : "false", grid, per_cu, max_tiles, per_block,
-                 lds_use);
+                 lds_use, (uint32_t)(a.wait_ticks / 100000u));
   void *args[] = {&a};
   hipError_t e = launch_grid_sync(ctx, kern, dim3(grid), dim3(H * WAVES * 64), args, lds_use);
   if (e == hipErrorInvalidValue || e == hipErrorCooperativeLaunchTooLarge ||

@@ -158,3 +158,20 @@ def test_runs_of_unequal_problems(mh, monkeypatch, capfd, resident, share, D, D_
     for key in ("feat", "tau", "label"):
         np.testing.assert_array_equal(got[key], want[key])
     assert got["correct"] == want["correct"] and got["cost"] == want["cost"]
+
+
+@pytest.mark.parametrize("halves,ms", [("", 20), ("2", 2000)])
+def test_four_groups_give_up_sooner(mh, monkeypatch, capfd, halves, ms):
+    """Blocks of four groups that fill a CU can be kept from starting by waves
+    of another stream: they wait for each other 20 ms, not 2 s."""
+    from paper_2311_06952_amd import capi
+    if halves:
+        monkeypatch.setenv("MHDEOCT_PERSIST_HALVES", halves)
+    monkeypatch.setenv("MHDEOCT_DEBUG", "1")
+    X, y = synth.random_small(5, 175_000, 20, 3)
+    ctx = capi.Context(0)
+    capfd.readouterr()
+    _check(mh, ctx, X, y, 3, 3, (9, 3, 0.5, 0.9, 3, 1, 0.0))
+    err = capfd.readouterr().err
+    ctx.close()
+    assert f"waits up to {ms} ms" in err
