@@ -279,13 +279,13 @@ mh_status subtree_solve_pop(mh_ctx *ctx, const mh_dataset *ds, const uint32_t *i
  * short runs (G = generations, on all of ds) of each candidate (the whole-run
  * cooperative kernel with one, two or four tile streams per block and 1, 2 or 4
  * blocks per CU, or in the form it takes without tuning; the per-generation
- * kernels with 1, 2 or 4 fitness blocks per CU) and keeps the fastest in the context for this shape (depth, P, F, K and
- * the power-of-two bucket of tiles per CU); later subtree_solve calls of that
- * shape use it.  Configurations change timing only: results are identical.
- * Fills *out (host).  Synchronises. */
+ * kernels with 1, 2 or 4 fitness blocks per CU) and keeps the fastest in the
+ * context for this shape (depth, P, F, K and the power-of-two bucket of tiles
+ * per CU); later subtree_solve calls of that shape use it.  Configurations
+ * change timing only: results are identical.  Fills *out (host).  Synchronises. */
 typedef struct {
-  uint32_t persist, halves, persist_blocks_per_cu, fit_blocks_per_cu;  /* the winner */
-                              /* (0 blocks per CU: the form without tuning) */
+  /* the winner (0 whole-run blocks per CU: the form without tuning) */
+  uint32_t persist, halves, persist_blocks_per_cu, fit_blocks_per_cu;
   double ms_per_generation;   /* its time per generation */
   uint32_t n_candidates;
   double ms[16];              /* median run time of each candidate, ms */

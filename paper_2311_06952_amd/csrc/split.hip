@@ -201,7 +201,10 @@ __global__ __launch_bounds__(1024) void k_split_row_scan_long(uint32_t *__restri
   uint32_t *p = v + (size_t)blockIdx.x * len;
   uint32_t run = 0, next[4];
 #pragma unroll
-  for (uint32_t i = 0; i < 4; ++i) next[i] = 4u * threadIdx.x + i < len ? p[4u * threadIdx.x + i] : 0u;
+  for (uint32_t i = 0; i < 4; ++i) {
+    const uint32_t q = 4u * threadIdx.x + i;
+    next[i] = q < len ? p[q] : 0u;
+  }
   for (uint32_t q0 = 0, b = 0; q0 < len; q0 += SCAN_LONG, b ^= 1u) {
     const uint32_t q = q0 + 4u * threadIdx.x;
     uint32_t mine[4], x = 0;
